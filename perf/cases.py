@@ -134,8 +134,8 @@ def _batch(c, seed):
     return tok, pos, cu, max(len(s) for s in seqs)
 
 
-def _model(c, seed):
-    """Random-init weights of the shape, drawn on the GPU, handed to the library (which keeps its own copy)."""
+def _weights(c, seed):
+    """Random-init weights of the shape, drawn on the GPU."""
     m = MODELS[c["model"]]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
@@ -150,8 +150,14 @@ def _model(c, seed):
     layers = [{"g1": gain(m.d), "wq": mat(m.dq, m.d), "wk": mat(m.dkv, m.d), "wv": mat(m.dkv, m.d),
                "gq": gain(m.head_dim), "gk": gain(m.head_dim), "wo": mat(m.d, m.dq), "g2": gain(m.d),
                "wg": mat(m.d_int, m.d), "wu": mat(m.d_int, m.d), "wd": mat(m.d, m.d_int)} for _ in range(m.n_layers)]
-    embed, gf = mat(m.vocab, m.d), gain(m.d)
-    return binding.radix_model_create(m, embed, gf, layers, compute_dtype=c["compute"], lm_head_mode=1 if c["head"] else 0)
+    return layers, mat(m.vocab, m.d), gain(m.d)
+
+
+def _model(c, seed):
+    """The weights handed to the library, which keeps its own copy."""
+    layers, embed, gf = _weights(c, seed)
+    return binding.radix_model_create(MODELS[c["model"]], embed, gf, layers, compute_dtype=c["compute"],
+                                      lm_head_mode=1 if c["head"] else 0)
 
 
 def prepare(case, seed):
@@ -191,6 +197,89 @@ def run(state):
         fused_attention=False if c["attention"] == "three_kernels" else None)
     if c["head"]:
         got["logits"] = binding.radix_lm_head(s["model"], got["hidden"], s["last"], s["ws"], out=s["logits"])
+    return got
+
+
+# ------------------------------------------------------------------------------------------ the same in 64 bits
+def _norm(x, g, eps):
+    return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + eps) * g.double()
+
+
+def exact(case, seed):
+    """The hidden states (and logits) of `run` in plain torch and float64.  Every distinct (prefix, block, suffix)
+    segment of the batch is a run of rows that is computed once, behind the segments it continues; how the segments
+    lie in the batch is known from the way it was made."""
+    c = case
+    if c["op"] == "index" or work(c)["flops"] > 2e14:       # whole numbers; over about 20 seconds
+        return None
+    m = MODELS[c["model"]]
+    tok, pos, cu, _ = _batch(c, seed)
+    B, P, G = c["B"], c["prefix"], c["group_len"]
+    if pos is None:
+        pos = np.concatenate([np.arange(n) for n in np.diff(cu)])
+    take, segments, where = [], [], np.empty(len(tok), dtype=np.int64)     # segment: (first row, rows, rows in front of it)
+    n_rows = 0
+    for b in range(B):
+        block = b * c["groups"] // B
+        new_block = b == 0 or block != (b - 1) * c["groups"] // B
+        behind, at = [], cu[b]
+        for length, fresh, known in ((P, b == 0, "prefix"), (G, new_block, "block"), (cu[b + 1] - cu[b] - P - G, True, "")):
+            if fresh:
+                row = n_rows
+                take.append(np.arange(at, at + length))
+                segments.append((row, int(length), list(behind)))
+                n_rows += int(length)
+                if known == "prefix":
+                    prefix_row = row
+                elif known == "block":
+                    block_row = row
+            else:
+                row = prefix_row if known == "prefix" else block_row
+            where[at:at + length] = row + np.arange(length)
+            behind.append((row, int(length)))
+            at += length
+    take = torch.from_numpy(np.concatenate(take)).cuda()
+    ids, at = torch.from_numpy(tok).cuda().long()[take], torch.from_numpy(pos).cuda()[take].double()
+    layers, embed, gf = _weights(c, seed)
+    half, hd, rep = m.head_dim // 2, m.head_dim, m.n_q_heads // m.n_kv_heads
+    angle = at[:, None] * float(m.rope_base) ** (-2.0 * torch.arange(half, device="cuda", dtype=torch.float64) / hd)
+    cos, sin = angle.cos()[:, None], angle.sin()[:, None]
+
+    def rotate(x):
+        a, b = x[..., :half], x[..., half:]
+        return torch.cat([a * cos - b * sin, b * cos + a * sin], -1)
+
+    h = embed[ids].double()
+    for w in layers:
+        a = _norm(h, w["g1"], m.eps)
+        q, k, v = ((a @ w[n].double().T).view(n_rows, -1, hd) for n in ("wq", "wk", "wv"))
+        if m.qk_norm:
+            q, k = _norm(q, w["gq"], m.eps), _norm(k, w["gk"], m.eps)
+        q, k = rotate(q), rotate(k)
+        o = torch.empty_like(q)
+        for row, n, behind in segments:
+            if n == 0:
+                continue
+            spans = behind + [(row, n)]
+            kk, vv = (torch.cat([x[r:r + t] for r, t in spans]).transpose(0, 1) for x in (k, v))       # [kv heads, keys, hd]
+            qq = q[row:row + n].transpose(0, 1).reshape(m.n_kv_heads, rep * n, hd)
+            s = torch.bmm(qq, kk.transpose(1, 2).contiguous()) / hd ** 0.5
+            s = s.view(m.n_q_heads, n, -1)
+            keys = s.shape[-1]
+            s.masked_fill_(torch.ones(n, keys, dtype=torch.bool, device="cuda").triu(keys - n + 1), float("-inf"))
+            p = torch.softmax(s, -1).view(m.n_kv_heads, rep * n, keys)
+            o[row:row + n] = torch.bmm(p, vv.contiguous()).view(m.n_q_heads, n, hd).transpose(0, 1)
+        h = h + o.reshape(n_rows, -1) @ w["wo"].double().T
+        a = _norm(h, w["g2"], m.eps)
+        gate = a @ w["wg"].double().T
+        h = h + (gate * torch.sigmoid(gate) * (a @ w["wu"].double().T)) @ w["wd"].double().T
+    hidden = _norm(h, gf, m.eps)[torch.from_numpy(where).cuda()]
+    if c["op"] == "nodedup":
+        return hidden
+    got = {"I_scatter": None, "I_gather": None, "n": None, "hidden": hidden}
+    if c["head"]:
+        last = hidden[torch.from_numpy(cu[1:] - 1).cuda().long()]
+        got["logits"] = torch.cat([last @ part.double().T for part in embed.split(16384)], -1)
     return got
 
 
