@@ -31,42 +31,12 @@
 //   * Workgroups are numbered so that the 8 XCDs (round-robin dispatch) each work on a compact
 //     band of row tiles, sweeping the weight tiles in step with the other XCDs (details at the tile
 //     assignment), which keeps an XCD's L2 on few A rows and the shared memory-side cache on few W rows.
-#include "common.h"
+#include "gemm_async.h"
 #include "kernels.h"
 
 namespace {
 
 constexpr int BK = 32;            // k-tile: 64 bytes = 4 chunks of 16 bytes per row
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt = imm[15:14|3:0],
-// expcnt = imm[6:4], lgkmcnt = imm[11:8]).
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-// the same, and all LDS reads of this wavefront have returned (lgkmcnt = 0)
-template <int N> __device__ __forceinline__ void wait_vmcnt_and_lds() {
-    static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
-}
-
-// Asynchronous 16-byte-per-lane copy global -> LDS: lane L of the wavefront writes LDS bytes
-// [lds_base + 16 L, +16).  lds_base must be wave-uniform.  (s_nop: M0 write -> LDS-DMA hazard.)
-// The global address is (uniform 64-bit base) + (per-lane 32-bit byte offset).
-__device__ __forceinline__ void dma16(const void* base, uint32_t lane_off, uint32_t lds_base) {
-    // the base is wave-uniform by construction; readfirstlane states that where the compiler has parked it in
-    // vector registers (it must reach the instruction in a scalar register pair)
-    const uint64_t b = (uint64_t)(uintptr_t)base;
-    // (the builtin returns a signed int: through uint32_t, or a low half with its top bit set would sign-extend
-    // over the high half)
-    const uint64_t bs = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
-                        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 ::"v"(lane_off), "s"(bs), "s"(lds_base) : "memory");
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
-}
 
 // LDS slot (in 16-byte units) of chunk c of tile row `row`.  Rows are 4 chunks (64 bytes), so rows
 // r, r+4, r+8, r+12 start in the same 64-byte window of the 256-byte bank line; XORing the chunk
@@ -694,7 +664,7 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
 template <int DT>
 int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out, int variant,
               const QkvEpilogue& qe, const ARowMap& amap, const NormFusion& nf, hipStream_t stream) {
-    // Tile choice by a small cost model: workgroups run one per CU in rounds, a round costs a fixed part
+    // Tile choice for launches with a folded norm (the others: plan_gemm): workgroups run one per CU in rounds, a round costs a fixed part
     // (launch, first loads, epilogue) plus the k-tiles at the rate measured for that shape (microseconds per
     // 32-wide k-tile on MI355X, random fp16 operands): a launch that does not fill its last round pays for it
     // in full, which is what decides between the shapes for small M * Nout.  Eight wavefronts (two per SIMD,
@@ -735,6 +705,82 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     return launch_cfg<DT, 128, 128, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
 }
 
+// ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
+// in rounds; a round costs fixed_us (first loads, epilogue) and, per 64 columns of K, step_us (what a k-tile takes
+// when nothing else runs on the CU: a chain of latencies) or, with n of them sharing the CU, n share_us if that is more.
+// A launch that does not fill its last round pays for it in full, until there are many rounds.  The constants are
+// least-squares fits of the logarithm to 240 launches on MI355X (M 8 .. 8240, the four projections of the 0.6B, 4B and
+// 8B shapes, fp16 operands, weights from HBM; typical error 15 %); picking by them costs 1.5 % over the best
+// tile of each launch.  The 256x256 tiles of this file win once they fill the chip, their k-loop being the better one
+// (N 24576, K 4096, M 8240: 1480 us against 1640 for 256x256 built like the small ones); below, the smaller ones.
+struct TileShape { int variant, bm, bn, per_cu; double launch_us, fixed_us, step_us, share_us; };
+const TileShape tile_shapes[] = {
+    { 1, 256, 256, 1, 0.00, 10.78, 1.424, 0.000},
+    { 4, 256, 256, 1, 0.00, 5.33, 1.446, 0.000},
+    {11,  32,  16, 3, 0.00, 0.40, 0.132, 0.105},
+    {12,  32,  32, 2, 0.00, 0.68, 0.142, 0.123},
+    {13,  32, 128, 2, 2.01, 0.00, 0.313, 0.274},
+    {14,  32,  64, 2, 2.40, 0.00, 0.000, 0.171},
+    {15,  64,  32, 2, 0.00, 0.00, 0.000, 0.208},
+    {16,  64,  64, 2, 0.52, 0.63, 0.257, 0.257},
+    {17,  64, 128, 2, 0.91, 1.48, 0.413, 0.362},
+    {18, 128, 128, 1, 0.00, 4.24, 0.512, 0.000},
+    {19, 128, 256, 1, 0.00, 7.75, 0.797, 0.000},
+    {20, 256, 128, 1, 0.00, 8.71, 0.748, 0.000},
+};
+constexpr int N_CU = 256;
+
+double tile_time(const TileShape& sh, int M, int Nout, int K) {
+    const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
+    double per = (double)tiles / N_CU;
+    if (per < 8.0) per = (double)((tiles + N_CU - 1) / N_CU);
+    const double kt = K / 64;
+    const double full = (double)(long long)(per / sh.per_cu), rest = per - full * sh.per_cu;
+    auto round_us = [&](double n) { return sh.fixed_us + kt * (n * sh.share_us > sh.step_us ? n * sh.share_us : sh.step_us); };
+    return sh.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
+}
+
+bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
+    if (Nout % sh.bn != 0) return false;
+    if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT) return sh.bn % 128 == 0;      // whole heads
+    if (epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_SPLIT) return sh.bn % 64 == 0;           // gate/up pairs
+    return true;
+}
+
+int best_tile(int M, int Nout, int K, int epilogue, double* us) {
+    int v = 0;
+    for (const TileShape& sh : tile_shapes) {
+        if (!tile_usable(sh, Nout, epilogue)) continue;
+        const double t = tile_time(sh, M, Nout, K);
+        if (v == 0 || t < *us) { *us = t; v = sh.variant; }
+    }
+    return v;
+}
+
+// Tiles of a product: rows [0, m1) in tiles of shape v1, the rest (if any) in a second launch of shape v2.  The large
+// tiles are at their best when the last round of workgroups is full; where M leaves a round nearly empty - 8240 rows
+// are 33 row tiles of 256, and 32 of them are whole rounds of the chip - the rows past the last full round go to smaller
+// tiles (M 8240, K 1024, N 4096: 111 us in one launch of 256x256, 93 us split; K 3072, N 1024: 79 and 62 us).
+struct GemmPlan { int v1, m1, v2; };
+GemmPlan plan_gemm(int M, int Nout, int K, int epilogue) {
+    double best = 0.0;
+    GemmPlan p = {best_tile(M, Nout, K, epilogue, &best), M, 0};
+    if (M <= 256) return p;
+    for (const TileShape& sh : tile_shapes) {
+        if (sh.bm < 128 || !tile_usable(sh, Nout, epilogue)) continue;
+        const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
+        const long long rounds = row_tiles * per_row / N_CU;
+        if (rounds < 1 || rounds >= 8) continue;
+        const long long m1 = rounds * N_CU / per_row * sh.bm;
+        if (m1 < sh.bm || m1 >= M) continue;
+        double t2 = 0.0;
+        const int v2 = best_tile(M - (int)m1, Nout, K, epilogue, &t2);
+        const double t = tile_time(sh, (int)m1, Nout, K) + t2;
+        if (t < 0.97 * best) { best = t; p.v1 = sh.variant; p.m1 = (int)m1; p.v2 = v2; }
+    }
+    return p;
+}
+
 }  // namespace
 
 int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int epilogue, void* out, int op_dtype,
@@ -763,9 +809,33 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
         if ((((uintptr_t)nf.a16 | (uintptr_t)nf.gain) & 15) != 0) return RADIX_ERR_MISALIGNED;
     }
     if (nf.ss_in && (nf.n_slots_in <= 0 || nf.n_slots_in % 2 != 0 || ((uintptr_t)nf.ss_in & 7) != 0)) return RADIX_ERR_UNSUPPORTED;
-    if (op_dtype == RADIX_BF16) return launch_dt<RADIX_BF16>(A, W, M, Nout, K, w_k, epilogue, out, variant, qe, amap, nf, stream);
-    if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(A, W, M, Nout, K, w_k, epilogue, out, variant, qe, amap, nf, stream);
-    return RADIX_ERR_UNSUPPORTED;
+    const bool folded = nf.ss_in != nullptr || epilogue == EPI_RESIDUAL_NORM;
+    if (folded && variant >= 11) return RADIX_ERR_UNSUPPORTED;
+    auto launch = [&](int v, const void* a, int m, void* o) -> int {
+        if (v >= 11) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
+        if (op_dtype == RADIX_BF16) return launch_dt<RADIX_BF16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
+        if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
+        return RADIX_ERR_UNSUPPORTED;
+    };
+    if (variant != 0 || folded) return launch(variant, A, M, out);
+    if (K % (2 * BK) != 0) return RADIX_ERR_UNSUPPORTED;
+    const GemmPlan plan = plan_gemm(M, Nout, K, epilogue);
+    if (plan.v1 == 0) return RADIX_ERR_UNSUPPORTED;
+    const int rc = launch(plan.v1, A, plan.m1, out);
+    if (rc != RADIX_OK || plan.m1 == M) return rc;
+    // the second launch sees the rows from m1 on
+    size_t out_row = (size_t)Nout * 4;                             // EPI_RESIDUAL, EPI_STORE_F32, EPI_QKV_ROPE_SPLIT
+    if (epilogue == EPI_STORE || epilogue == EPI_QKV_ROPE || epilogue == EPI_SWIGLU_SPLIT) out_row = (size_t)Nout * 2;
+    else if (epilogue == EPI_SWIGLU) out_row = (size_t)Nout;
+    if (qe.pos_c) qe.pos_c += plan.m1;
+    const void* a2 = A;
+    if (amap.rows) {
+        amap.rows += plan.m1;
+        amap.n_valid = amap.n_valid > plan.m1 ? amap.n_valid - plan.m1 : 0;
+    } else {
+        a2 = (const char*)A + (size_t)plan.m1 * K * 2;
+    }
+    return launch(plan.v2, a2, M - plan.m1, (char*)out + (size_t)plan.m1 * out_row);
 }
 
 // Host-side views of the tile numbering, for tests (declared in radixmlp_bench.h).
@@ -780,4 +850,17 @@ extern "C" int radix_debug_gemm_tile(int32_t bid, int32_t tiles_m, int32_t tiles
 extern "C" int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles_n) {
     if (tile_rows <= 0 || K <= 0 || tiles_n <= 0) return RADIX_ERR_BAD_SIZE;
     return gemm_band_rows(tile_rows, K, 2, tiles_n);
+}
+extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
+                                     int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2) {
+    if (!v1 || !bm1 || !bn1 || !m1 || !v2 || !bm2 || !bn2) return RADIX_ERR_NULL_POINTER;
+    if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0) return RADIX_ERR_BAD_SIZE;
+    const GemmPlan p = plan_gemm(M, Nout, K, epilogue);
+    *v1 = p.v1; *m1 = p.m1; *v2 = p.v2;
+    *bm1 = *bn1 = *bm2 = *bn2 = 0;
+    for (const TileShape& sh : tile_shapes) {
+        if (sh.variant == p.v1) { *bm1 = sh.bm; *bn1 = sh.bn; }
+        if (sh.variant == p.v2) { *bm2 = sh.bm; *bn2 = sh.bn; }
+    }
+    return p.v1 ? RADIX_OK : RADIX_ERR_UNSUPPORTED;
 }

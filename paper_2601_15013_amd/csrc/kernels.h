@@ -156,6 +156,12 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
                      int op_dtype, int variant, hipStream_t stream, const QkvEpilogue* qkv = nullptr, int w_k = 0,
                      const ARowMap* a_rows = nullptr, const NormFusion* norm = nullptr);
 
+// The same product in the small tiles of gemm_small.hip (variant 11 ..; arguments already checked by
+// launch_gemm_mfma, which is the only caller; no folded norms).  Same results bit for bit.
+int launch_gemm_small(const void* A, const void* W, int M, int Nout, int K, int epilogue, void* out_or_resid,
+                      int op_dtype, int variant, hipStream_t stream, const QkvEpilogue& qkv, int w_k,
+                      const ARowMap& a_rows);
+
 // ---- causal varlen GQA attention on the full ragged layout.
 // qkv[N, dq + 2 dkv] rows hold q | k | v of one token; out[N, dq].
 void launch_attention_f32(const float* qkv, const int32_t* cu, int B, int N, int max_seqlen, int n_q_heads,
