@@ -1,64 +1,94 @@
 // fp32 GEMM C[M, Nout] = A[M, K] * W[Nout, K]^T for the fp32 model configuration (small,
-// parity-oriented).  Plain LDS-tiled FMA kernel: 64x64 output tile, 256 threads, 4x4 outputs
-// per thread, K consumed in order so every output element is reduced in the same order
-// wherever its row sits in the matrix.
+// parity-oriented).  LDS-tiled FMA kernel, K consumed in order by one fused multiply-add chain per output element,
+// so every element is reduced in the same order whatever the tile and wherever its row sits in the matrix.
+//
+// These launches are latency-bound: a few hundred rows give a few dozen workgroups, and the time is the number of
+// k-tiles times what one costs.  So a k-tile is 64 wide, the next one is fetched into registers (16 bytes per lane) while
+// the present one is multiplied, LDS is read 16 bytes along k, and the tile is TM x TM outputs with TM = 16 R, the smaller
+// the fewer workgroups the launch has.  At M 160, N 256, K 768: 75 us with a 64 x 64 tile, k-tiles of 16 and no
+// prefetch, 7.7 us (mean of it and the K 256 one) with this kernel.
 #include "common.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16;
+constexpr int TK = 64, PK = TK + 4;      // k-tile and its pitch in LDS: 16 rows start in 16 different 16-byte bank groups
 
-template <int EPI>
+// 256 threads = 16 x 16; thread (tx, ty) owns rows ty + 16 i and columns tx + 16 j, i, j < R.
+template <int R, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        int M, int Nout, int K, float* __restrict__ out) {
-    __shared__ float As[TK][TM + 1];
-    __shared__ float Ws[TK][TN + 1];
+    static_assert(EPI != EPI_SWIGLU || R == 4 || R == 2, "gate and up blocks of 32 columns meet in one tile");
+    // SwiGLU with a 32-wide tile takes 16 gate columns and the 16 matching up columns, else 64 = 32 gate + 32 up
+    constexpr bool PAIR16 = EPI == EPI_SWIGLU && R == 2;
+    constexpr int TM = 16 * R, LD = TM * TK / 4 / 256;
+    __shared__ float As[TM * PK];
+    __shared__ float Ws[TM * PK];
     const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;        // 16 x 16 threads
-    const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-    // thread's rows: ty*4 .. +3 ; columns: {2 tx, 2 tx + 1, 32 + 2 tx, 33 + 2 tx}
-    float acc[4][4] = {};
+    const int tx = tid & 15, ty = tid >> 4;
+    const int m0 = blockIdx.y * TM;
+    // weight row of tile column c
+    const int n0 = PAIR16 ? ((int)blockIdx.x >> 1) * 64 + ((int)blockIdx.x & 1) * 16 : (int)blockIdx.x * TM;
+    auto w_row = [&](int c) { return PAIR16 ? n0 + (c & 15) + (c >> 4) * 32 : n0 + c; };
+    float4 av[LD], wv[LD];
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto fetch = [&](int k0) {                                   // K is a multiple of 4, rows are 16-byte aligned
+#pragma unroll
+        for (int u = 0; u < LD; ++u) {
+            const int e = tid + 256 * u, r = e / (TK / 4), gk = k0 + 4 * (e % (TK / 4));
+            const int gm = m0 + r, gn = w_row(r);
+            av[u] = gm < M && gk < K ? *reinterpret_cast<const float4*>(A + (size_t)gm * K + gk) : zero;
+            wv[u] = gn < Nout && gk < K ? *reinterpret_cast<const float4*>(W + (size_t)gn * K + gk) : zero;
+        }
+    };
+    float acc[R][R] = {};
+    fetch(0);
     for (int k0 = 0; k0 < K; k0 += TK) {
-        for (int e = tid; e < TM * TK; e += 256) {
-            int r = e / TK, k = e % TK;
-            int gm = m0 + r, gk = k0 + k;
-            As[k][r] = (gm < M && gk < K) ? A[(size_t)gm * K + gk] : 0.f;
-            int gn = n0 + r;
-            Ws[k][r] = (gn < Nout && gk < K) ? W[(size_t)gn * K + gk] : 0.f;
+#pragma unroll
+        for (int u = 0; u < LD; ++u) {
+            const int e = tid + 256 * u, r = e / (TK / 4), k = 4 * (e % (TK / 4));
+            *reinterpret_cast<float4*>(As + r * PK + k) = av[u];
+            *reinterpret_cast<float4*>(Ws + r * PK + k) = wv[u];
         }
         __syncthreads();
+        if (k0 + TK < K) fetch(k0 + TK);
 #pragma unroll
-        for (int k = 0; k < TK; ++k) {
-            float a[4], b[4];
+        for (int k = 0; k < TK; k += 4) {
+            float4 a[R], b[R];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-            b[0] = Ws[k][2 * tx]; b[1] = Ws[k][2 * tx + 1]; b[2] = Ws[k][32 + 2 * tx]; b[3] = Ws[k][33 + 2 * tx];
+            for (int i = 0; i < R; ++i) a[i] = *reinterpret_cast<const float4*>(As + (ty + 16 * i) * PK + k);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int j = 0; j < R; ++j) b[j] = *reinterpret_cast<const float4*>(Ws + (tx + 16 * j) * PK + k);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    acc[i][j] = fmaf(a[i].x, b[j].x, acc[i][j]);
+                    acc[i][j] = fmaf(a[i].y, b[j].y, acc[i][j]);
+                    acc[i][j] = fmaf(a[i].z, b[j].z, acc[i][j]);
+                    acc[i][j] = fmaf(a[i].w, b[j].w, acc[i][j]);
+                }
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int gm = m0 + ty * 4 + i;
+    for (int i = 0; i < R; ++i) {
+        const int gm = m0 + ty + 16 * i;
         if (gm >= M) continue;
         if (EPI == EPI_SWIGLU) {
-            // tile columns 0..31 are gate, 32..63 the matching up columns
+            // tile columns [0, TM / 2) are gate, the others the matching up columns
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int oc = (n0 >> 1) + 2 * tx + j;
-                if (n0 + 32 + 2 * tx + j < Nout) {
-                    const float gte = acc[i][j], up = acc[i][j + 2];
-                    out[(size_t)gm * (Nout >> 1) + oc] = gte / (1.0f + expf(-gte)) * up;
+            for (int j = 0; j < R / 2; ++j) {
+                const int gn = w_row(tx + 16 * j);              // gate row of W; its up row is gn + 32
+                if (gn + 32 < Nout) {
+                    const float gte = acc[i][j], up = acc[i][j + R / 2];
+                    out[(size_t)gm * (Nout >> 1) + (gn >> 6) * 32 + (gn & 31)] = gte / (1.0f + expf(-gte)) * up;
                 }
             }
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int gn = n0 + (j & 1) + 2 * tx + (j >> 1) * 32;
+            for (int j = 0; j < R; ++j) {
+                const int gn = n0 + tx + 16 * j;
                 if (gn >= Nout) continue;
                 float* o = out + (size_t)gm * Nout + gn;
                 if (EPI == EPI_RESIDUAL) *o = *o + acc[i][j]; else *o = acc[i][j];
@@ -67,16 +97,35 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
 }
 
+template <int R, int EPI>
+void launch_r(const float* A, const float* W, int M, int Nout, int K, float* out, hipStream_t stream) {
+    const int tiles_m = ceil_div(M, 16 * R);
+    // SwiGLU columns come in blocks of 64 (32 gate + 32 up)
+    const int tiles_n = EPI == EPI_SWIGLU ? ceil_div(Nout, 64) * (4 / R) : ceil_div(Nout, 16 * R);
+    // the grid's y extent is 16 bits: taller outputs go in several launches
+    for (int t0 = 0; t0 < tiles_m; t0 += 65535) {
+        const int rows0 = t0 * 16 * R, n = tiles_m - t0 < 65535 ? tiles_m - t0 : 65535;
+        hipLaunchKernelGGL((gemm_f32_kernel<R, EPI>), dim3(tiles_n, n), dim3(256), 0, stream, A + (size_t)rows0 * K, W,
+                           M - rows0, Nout, K, out + (size_t)rows0 * (EPI == EPI_SWIGLU ? Nout / 2 : Nout));
+    }
+}
+
+// Tile by workgroup count: a larger tile reads LDS less per multiply-add (the bound once every CU has work), a smaller
+// one shortens the k-tile while CUs would be idle.
+template <int EPI>
+void launch_epi(const float* A, const float* W, int M, int Nout, int K, float* out, hipStream_t stream) {
+    const long long t64 = (long long)ceil_div(M, 64) * ceil_div(Nout, 64), t32 = (long long)ceil_div(M, 32) * ceil_div(Nout, 32);
+    if (t64 >= 256) launch_r<4, EPI>(A, W, M, Nout, K, out, stream);
+    else if (EPI == EPI_SWIGLU || t32 >= 256) launch_r<2, EPI>(A, W, M, Nout, K, out, stream);
+    else launch_r<EPI == EPI_SWIGLU ? 2 : 1, EPI>(A, W, M, Nout, K, out, stream);
+}
+
 }  // namespace
 
 void launch_gemm_f32(const float* A, const float* W, int M, int Nout, int K, int epilogue, float* out,
                      hipStream_t stream) {
     if (M <= 0 || Nout <= 0) return;
-    dim3 grid(ceil_div(Nout, TN), ceil_div(M, TM)), block(256);
-    if (epilogue == EPI_STORE)
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_STORE>, grid, block, 0, stream, A, W, M, Nout, K, out);
-    else if (epilogue == EPI_RESIDUAL)
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESIDUAL>, grid, block, 0, stream, A, W, M, Nout, K, out);
-    else
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, stream, A, W, M, Nout, K, out);
+    if (epilogue == EPI_STORE) launch_epi<EPI_STORE>(A, W, M, Nout, K, out, stream);
+    else if (epilogue == EPI_RESIDUAL) launch_epi<EPI_RESIDUAL>(A, W, M, Nout, K, out, stream);
+    else launch_epi<EPI_SWIGLU>(A, W, M, Nout, K, out, stream);
 }
