@@ -22,7 +22,8 @@
 //     wavefront scan of (len_s - b_s) over sequences: exactly first-occurrence order.
 //
 // The chain phase runs in one 1024-thread workgroup (it is latency-bound bookkeeping over B
-// sequences; the data is 4N bytes); the final map write-out is a chip-wide kernel over tokens.
+// sequences), but for the comparisons of its first round in large batches; the final map write-out is a chip-wide
+// kernel over tokens.
 #include <mutex>
 
 #include "common.h"
@@ -47,19 +48,47 @@ __device__ __forceinline__ uint32_t key_hash(int l, int m, int t, int pp) {
     return (uint32_t)x;
 }
 
-__global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
-    const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
-    int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr, int32_t* dep, int32_t* bdep,
-    int32_t* mis, int32_t* myslot, int32_t* cbase, int32_t* slot_owner, int32_t* slot_min, int H,
-    int32_t* n_compact_dev) {
-    __shared__ int sh_first;
-    __shared__ int sh_wave_tot[IDX_WAVES];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Comparison of follower s with its leader l from position st on, by one wavefront: the first position where they
+// differ (or the shorter length); lead[] of the equal positions is written on the way.
+template <int UNROLL>
+__device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int bs,
+                                             int bl, int st, int lim, int l, int32_t* __restrict__ lead, int lane) {
+    for (int p0 = st; p0 < lim; p0 += 64 * UNROLL) {
+        int neq[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            int p = p0 + u * 64 + lane;
+            bool valid = p < lim;
+            int a = valid ? tok[bs + p] : 0;
+            int b = valid ? tok[bl + p] : 1;
+            int d = (a != b);
+            if (pos != nullptr && valid) d |= (pos[bs + p] != pos[bl + p]);
+            neq[u] = d;
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            int p = p0 + u * 64 + lane;
+            unsigned long long mask = __ballot(neq[u]);
+            if (mask != 0ull) {
+                int first = __ffsll((long long)mask) - 1;
+                if (lane < first) lead[bs + p] = l;
+                return p0 + u * 64 + first;
+            }
+            lead[bs + p] = l;
+        }
+    }
+    return lim;
+}
 
+// Validation of cu_seqlens (before anything is dereferenced through it) and the initial state, by one workgroup.
+// Returns the first non-empty sequence, which everybody else follows, or -1 on a malformed array.
+__device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr, int32_t* ldr,
+                                          int32_t* dep, int32_t* bdep, int32_t* mis, int32_t* slot_owner,
+                                          int32_t* slot_min, int H, int32_t* n_compact_dev) {
+    __shared__ int sh_first;
+    const int tid = threadIdx.x;
     // every call starts with a clean status word
     if (tid == 0) hdr[0] = 0;
-
-    // ---- validate cu_seqlens before anything is dereferenced through it
     int bad = 0;
     for (int i = tid; i <= B; i += IDX_THREADS) {
         int c = cu[i];
@@ -75,10 +104,8 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
             hdr[1] = 0;
             *n_compact_dev = 0;
         }
-        return;
+        return -1;
     }
-
-    // ---- initial state: everybody follows the first non-empty sequence
     if (tid == 0) sh_first = B;
     __syncthreads();
     for (int s = tid; s < B; s += IDX_THREADS)
@@ -102,49 +129,67 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
         slot_min[h] = 0x7FFFFFFF;
     }
     __syncthreads();
+    return s0;
+}
+
+__global__ __launch_bounds__(IDX_THREADS) void index_init_kernel(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr,
+                                                                 int32_t* ldr, int32_t* dep, int32_t* bdep, int32_t* mis,
+                                                                 int32_t* slot_owner, int32_t* slot_min, int H,
+                                                                 int32_t* n_compact_dev) {
+    index_init(cu, B, N, hdr, ldr, dep, bdep, mis, slot_owner, slot_min, H, n_compact_dev);
+}
+
+// The comparisons of the first round, one wavefront per sequence over the whole chip: all sequences start by following
+// the first one, so this is where the prefix that a batch shares is read, and most of what there is to compare.
+__global__ __launch_bounds__(256) void index_first_round_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos,
+                                                                const int32_t* __restrict__ cu, int B, int32_t* __restrict__ lead,
+                                                                const int32_t* hdr, int32_t* ldr, int32_t* bdep, int32_t* mis) {
+    const int lane = threadIdx.x & 63;
+    const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (s >= B || hdr[0] != 0 || bdep[s] != -1) return;
+    const int l = ldr[s];
+    const int bs = cu[s], bl = cu[l];
+    const int len_s = cu[s + 1] - bs, len_l = cu[l + 1] - bl;
+    const int m = common_prefix<8>(tok, pos, bs, bl, 0, len_s < len_l ? len_s : len_l, l, lead, lane);
+    if (lane == 0) {
+        if (m == len_s) {           // as in the rounds of the chain kernel
+            bdep[s] = len_s;
+            ldr[s] = -1;
+        } else {
+            mis[s] = m;
+        }
+    }
+}
+
+// first_done: index_init_kernel and index_first_round_kernel ran before
+__global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
+    const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
+    int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr, int32_t* dep, int32_t* bdep,
+    int32_t* mis, int32_t* myslot, int32_t* cbase, int32_t* slot_owner, int32_t* slot_min, int H,
+    int32_t* n_compact_dev, int first_done) {
+    __shared__ int sh_wave_tot[IDX_WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (first_done) {
+        if (hdr[0] != 0) return;
+    } else if (index_init(cu, B, N, hdr, ldr, dep, bdep, mis, slot_owner, slot_min, H, n_compact_dev) < 0) {
+        return;
+    }
 
     // ---- rounds.  Each active follower's matched depth grows by >= 1 per round, so the loop
     // ends after at most (longest sequence + 1) rounds; N + 2 is a hard upper bound.
     for (int round = 0; round < N + 2; ++round) {
         // step 1: longest common prefix with the leader, one wavefront per follower
         int any = 0;
+        if (round == 0 && first_done) {
+            for (int s = tid; s < B; s += IDX_THREADS) any |= bdep[s] == -1;
+        } else
         for (int s = wave; s < B; s += IDX_WAVES) {
             if (bdep[s] != -1) continue;
             any = 1;
             const int l = ldr[s], st = dep[s];
             const int bs = cu[s], bl = cu[l];
             const int len_s = cu[s + 1] - bs, len_l = cu[l + 1] - bl;
-            const int lim = len_s < len_l ? len_s : len_l;
-            int m = lim;
-            for (int p0 = st; p0 < lim; p0 += 64 * LCP_UNROLL) {
-                int neq[LCP_UNROLL];
-#pragma unroll
-                for (int u = 0; u < LCP_UNROLL; ++u) {
-                    int p = p0 + u * 64 + lane;
-                    bool valid = p < lim;
-                    int a = valid ? tok[bs + p] : 0;
-                    int b = valid ? tok[bl + p] : 1;
-                    int d = (a != b);
-                    if (pos != nullptr && valid) d |= (pos[bs + p] != pos[bl + p]);
-                    neq[u] = d;
-                }
-                bool stop = false;
-#pragma unroll
-                for (int u = 0; u < LCP_UNROLL; ++u) {
-                    if (stop) continue;
-                    int p = p0 + u * 64 + lane;
-                    unsigned long long mask = __ballot(neq[u]);
-                    if (mask == 0ull) {
-                        lead[bs + p] = l;
-                    } else {
-                        int first = __ffsll((long long)mask) - 1;
-                        if (lane < first) lead[bs + p] = l;
-                        m = p0 + u * 64 + first;
-                        stop = true;
-                    }
-                }
-                if (stop) break;
-            }
+            const int m = common_prefix<LCP_UNROLL>(tok, pos, bs, bl, st, len_s < len_l ? len_s : len_l, l, lead, lane);
             if (lane == 0) {
                 if (m == len_s) {       // s ran out while still equal to its leader: no new node
                     bdep[s] = len_s;
@@ -311,8 +356,17 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
 
     // the chain kernel initialises every word of builder state it reads (status word, per-sequence arrays, both
     // slot tables), so the buffer may hold anything when the call starts
+    // More sequences than the chain kernel has wavefronts: its first round, which reads the shared prefix of every
+    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in one kernel, 117 us from call to call with the wait for the count, kernels 93 us, in four.
+    const int first_done = B > IDX_WAVES && N > 0;
+    if (first_done) {
+        hipLaunchKernelGGL(index_init_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr, ldr, dep, bdep,
+                           mis, slot_owner, slot_min, H, n_compact_dev);
+        hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B,
+                           I_scatter, hdr, ldr, bdep, mis);
+    }
     hipLaunchKernelGGL(index_chain_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N,
-                       I_scatter, hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev);
+                       I_scatter, hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done);
     if (N > 0) {
         hipLaunchKernelGGL(index_finalize_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, stream, tok, pos,
                            cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase);
