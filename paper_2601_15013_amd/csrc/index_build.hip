@@ -34,6 +34,7 @@ namespace {
 constexpr int IDX_THREADS = 1024;
 constexpr int IDX_WAVES = IDX_THREADS / RADIX_WAVE;
 constexpr int LCP_UNROLL = 4;
+constexpr int LDS_TABLE = 8192;       // slots of a grouping table kept in LDS (64 KB): batches of up to 4096 sequences
 
 __device__ __forceinline__ int ld_agent(const int* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -83,8 +84,7 @@ __device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, co
 // Validation of cu_seqlens (before anything is dereferenced through it) and the initial state, by one workgroup.
 // Returns the first non-empty sequence, which everybody else follows, or -1 on a malformed array.
 __device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr, int32_t* ldr,
-                                          int32_t* dep, int32_t* bdep, int32_t* mis, int32_t* slot_owner,
-                                          int32_t* slot_min, int H, int32_t* n_compact_dev) {
+                                          int32_t* dep, int32_t* bdep, int32_t* mis, int32_t* n_compact_dev) {
     __shared__ int sh_first;
     const int tid = threadIdx.x;
     // every call starts with a clean status word
@@ -124,19 +124,14 @@ __device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B,
             dep[s] = 0;
         }
     }
-    for (int h = tid; h < H; h += IDX_THREADS) {
-        slot_owner[h] = -1;
-        slot_min[h] = 0x7FFFFFFF;
-    }
     __syncthreads();
     return s0;
 }
 
 __global__ __launch_bounds__(IDX_THREADS) void index_init_kernel(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr,
                                                                  int32_t* ldr, int32_t* dep, int32_t* bdep, int32_t* mis,
-                                                                 int32_t* slot_owner, int32_t* slot_min, int H,
                                                                  int32_t* n_compact_dev) {
-    index_init(cu, B, N, hdr, ldr, dep, bdep, mis, slot_owner, slot_min, H, n_compact_dev);
+    index_init(cu, B, N, hdr, ldr, dep, bdep, mis, n_compact_dev);
 }
 
 // The comparisons of the first round, one wavefront per sequence over the whole chip: all sequences start by following
@@ -161,19 +156,30 @@ __global__ __launch_bounds__(256) void index_first_round_kernel(const int32_t* _
     }
 }
 
-// first_done: index_init_kernel and index_first_round_kernel ran before
+// first_done: index_init_kernel and index_first_round_kernel ran before.
+// LDS: the grouping table (H slots, a power of two <= LDS_TABLE) lives in LDS instead of the workspace: a probe is an
+// LDS atomic instead of a round trip to L2.
+template <bool LDS>
 __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
     int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr, int32_t* dep, int32_t* bdep,
-    int32_t* mis, int32_t* myslot, int32_t* cbase, int32_t* slot_owner, int32_t* slot_min, int H,
+    int32_t* mis, int32_t* myslot, int32_t* cbase, int32_t* slot_owner_ws, int32_t* slot_min_ws, int H,
     int32_t* n_compact_dev, int first_done) {
     __shared__ int sh_wave_tot[IDX_WAVES];
+    __shared__ int32_t sh_table[LDS ? 2 * LDS_TABLE : 1];
+    int32_t* const slot_owner = LDS ? sh_table : slot_owner_ws;
+    int32_t* const slot_min = LDS ? sh_table + LDS_TABLE : slot_min_ws;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (first_done) {
         if (hdr[0] != 0) return;
-    } else if (index_init(cu, B, N, hdr, ldr, dep, bdep, mis, slot_owner, slot_min, H, n_compact_dev) < 0) {
+    } else if (index_init(cu, B, N, hdr, ldr, dep, bdep, mis, n_compact_dev) < 0) {
         return;
     }
+    for (int h = tid; h < H; h += IDX_THREADS) {
+        slot_owner[h] = -1;
+        slot_min[h] = 0x7FFFFFFF;
+    }
+    __syncthreads();
 
     // ---- rounds.  Each active follower's matched depth grows by >= 1 per round, so the loop
     // ends after at most (longest sequence + 1) rounds; N + 2 is a hard upper bound.
@@ -201,21 +207,31 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
         }
         if (!__syncthreads_or(any)) break;
 
-        // step 2: group the leavers by (leader, depth, token, position) - exact comparison
+        // step 2: group the leavers by (leader, depth, token, position) - exact comparison, of full keys only where the
+        // 32-bit hashes agree.  dep[] holds the hash meanwhile: the depth it keeps was used in step 1 and step 3 sets
+        // the next one.
         for (int s = tid; s < B; s += IDX_THREADS) {
             if (bdep[s] != -1) continue;
-            const int l = ldr[s], m = mis[s];
-            const int t = tok[cu[s] + m];
-            const int pp = pos ? pos[cu[s] + m] : m;
-            uint32_t h = key_hash(l, m, t, pp) & (uint32_t)(H - 1);
+            const int m = mis[s], i = cu[s] + m;
+            dep[s] = (int)key_hash(ldr[s], m, tok[i], pos ? pos[i] : m);
+        }
+        __syncthreads();
+        for (int s = tid; s < B; s += IDX_THREADS) {
+            if (bdep[s] != -1) continue;
+            const int hash = dep[s];
+            uint32_t h = (uint32_t)hash & (uint32_t)(H - 1);
             for (int probe = 0; probe < H; ++probe) {
-                int o = ld_agent(&slot_owner[h]);
+                int o = LDS ? __hip_atomic_load(&slot_owner[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
+                            : ld_agent(&slot_owner[h]);
                 if (o == -1) {
                     o = atomicCAS(&slot_owner[h], -1, s);
                     if (o == -1) o = s;
                 }
                 if (o == s) break;
-                if (ldr[o] == l && mis[o] == m && tok[cu[o] + m] == t && (pos ? pos[cu[o] + m] : m) == pp) break;
+                if (dep[o] == hash) {
+                    const int l = ldr[s], m = mis[s], i = cu[s] + m, j = cu[o] + m;
+                    if (ldr[o] == l && mis[o] == m && tok[j] == tok[i] && (pos == nullptr || pos[j] == pos[i])) break;
+                }
                 h = (h + 1) & (uint32_t)(H - 1);
             }
             atomicMin(&slot_min[h], s);
@@ -226,7 +242,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
         // step 3: lowest member leads the new node, the others follow it
         for (int s = tid; s < B; s += IDX_THREADS) {
             if (bdep[s] != -1) continue;
-            const int c = ld_agent(&slot_min[myslot[s]]);
+            const int c = LDS ? slot_min[myslot[s]] : ld_agent(&slot_min[myslot[s]]);
             const int m = mis[s];
             if (c == s) {
                 bdep[s] = m;
@@ -357,16 +373,17 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     // the chain kernel initialises every word of builder state it reads (status word, per-sequence arrays, both
     // slot tables), so the buffer may hold anything when the call starts
     // More sequences than the chain kernel has wavefronts: its first round, which reads the shared prefix of every
-    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in one kernel, 117 us from call to call with the wait for the count, kernels 93 us, in four.
+    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in one kernel, 57 us in four (85 us from call to call, with the wait for the count).
     const int first_done = B > IDX_WAVES && N > 0;
     if (first_done) {
         hipLaunchKernelGGL(index_init_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr, ldr, dep, bdep,
-                           mis, slot_owner, slot_min, H, n_compact_dev);
+                           mis, n_compact_dev);
         hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B,
                            I_scatter, hdr, ldr, bdep, mis);
     }
-    hipLaunchKernelGGL(index_chain_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N,
-                       I_scatter, hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done);
+    auto chain = H <= LDS_TABLE ? index_chain_kernel<true> : index_chain_kernel<false>;
+    hipLaunchKernelGGL(chain, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N, I_scatter,
+                       hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done);
     if (N > 0) {
         hipLaunchKernelGGL(index_finalize_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, stream, tok, pos,
                            cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase);
