@@ -373,7 +373,8 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     // the chain kernel initialises every word of builder state it reads (status word, per-sequence arrays, both
     // slot tables), so the buffer may hold anything when the call starts
     // More sequences than the chain kernel has wavefronts: its first round, which reads the shared prefix of every
-    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in one kernel, 57 us in four (85 us from call to call, with the wait for the count).
+    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in
+    // one kernel, 57 us in four (85 us from call to call, with the wait for the count).
     const int first_done = B > IDX_WAVES && N > 0;
     if (first_done) {
         hipLaunchKernelGGL(index_init_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr, ldr, dep, bdep,

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(1024) void sum_squares_bf16_kernel(const bf16_t* __
 size_t esize(int dtype) { return dtype == RADIX_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t pos_full, ids_c, pos_c, plan, h, ss, a, qkv, qkv_full, attn_full, attn_c, mlp, ynorm, total;
+    size_t pos_c, plan, h, ss, a, qkv, qkv_full, attn_full, attn_c, mlp, ynorm, total;
 };
 
 WsLayout ws_layout(const radix_model_config& c, int hilo_layers, size_t N, size_t B) {
@@ -106,8 +106,6 @@ WsLayout ws_layout(const radix_model_config& c, int hilo_layers, size_t N, size_
     size_t off = radix_index_ws_bytes((int)B);
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes ? bytes : 1, 256); return o; };
     WsLayout L;
-    L.pos_full = take(N * 4);
-    L.ids_c = take(M * 4);
     L.pos_c = take(M * 4);
     L.plan = take(attn_plan_layout(N, B).total * 4);
     L.h = take(M * c.d * 4);
@@ -325,15 +323,16 @@ int forward_impl(const radix_model* model, const int32_t* tok, const int32_t* po
     if (ws_bytes < L.total) return RADIX_ERR_WORKSPACE_TOO_SMALL;
     char* w = (char*)ws;
     int32_t* hdr = (int32_t*)w;
-    hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, stream, hdr);
-    if (N == 0) { HIP_TRY(hipGetLastError()); return RADIX_OK; }
+    if (N == 0) {
+        hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, stream, hdr);
+        HIP_TRY(hipGetLastError());
+        return RADIX_OK;
+    }
     launch_validate_cu(cu, B, N, max_seqlen, hdr, stream);
 
     const int dt = c.compute_dtype;          // activation / operand type
     const size_t es = esize(dt);
     const int d = c.d, hd = c.head_dim, dq = c.n_q_heads * hd, dkv = c.n_kv_heads * hd, row = dq + 2 * dkv;
-    int32_t* pos_full = (int32_t*)(w + L.pos_full);
-    int32_t* ids_c = (int32_t*)(w + L.ids_c);
     int32_t* pos_c = (int32_t*)(w + L.pos_c);
     int32_t* plan = (int32_t*)(w + L.plan);
     float* h = (float*)(w + L.h);
@@ -356,13 +355,9 @@ int forward_impl(const radix_model* model, const int32_t* tok, const int32_t* po
         if (M < M_valid) M = M_valid;
     }
 
-    // Token compaction: positions and ids of the representatives (Algorithm 1, first block)
-    if (!pos) {
-        launch_default_positions(cu, B, N, pos_full, stream);
-        pos = pos_full;
-    }
-    launch_compact_ids(tok, pos, dedup ? Ig : nullptr, M, M_valid, N, c.vocab, c.max_pos, ids_c, pos_c, hdr, stream);
-    launch_embed(model->embed, c.dtype, ids_c, M, d, h, stream);
+    // Token compaction and embedding: positions and embedding rows of the representatives (Algorithm 1, first block)
+    launch_compact_embed(model->embed, c.dtype, tok, pos, cu, dedup ? Ig : nullptr, M, M_valid, N, B, c.vocab, c.max_pos, d,
+                         pos_c, h, hdr, stream);
     if (fused) launch_attn_plan(cu, Is, Ig, B, N, M_valid, c.n_q_heads, c.n_kv_heads, plan, stream);
 
     // C = A W^T over K columns of A; w_k = row length of W (K, or K / 2 when A rows are (hi, lo) pairs)

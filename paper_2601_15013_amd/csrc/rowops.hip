@@ -37,56 +37,71 @@ __global__ __launch_bounds__(256) void index_select_kernel(const V* __restrict__
     for (; c < row_vecs; c += 64) dp[c] = sp[c];
 }
 
-// cu_seqlens must run from 0 to N without decreasing and no sequence may exceed max_seqlen.
-__global__ void validate_cu_kernel(const int32_t* __restrict__ cu, int B, int N, int max_seqlen, int32_t* status) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > B) return;
-    const int c = cu[i];
-    bool bad = c < 0 || c > N || (i == 0 && c != 0) || (i == B && c != N);
-    if (i < B) {
-        const int len = cu[i + 1] - c;
-        bad = bad || len < 0 || len > max_seqlen;
+// Clears the status word, then: cu_seqlens must run from 0 to N without decreasing and no sequence may exceed
+// max_seqlen.  One workgroup, so that the clearing comes before every report.
+__global__ __launch_bounds__(1024) void validate_cu_kernel(const int32_t* __restrict__ cu, int B, int N, int max_seqlen, int32_t* status) {
+    if (threadIdx.x == 0) atomicExch(status, 0);
+    __syncthreads();
+    for (int i = threadIdx.x; i <= B; i += 1024) {
+        const int c = cu[i];
+        bool bad = c < 0 || c > N || (i == 0 && c != 0) || (i == B && c != N);
+        if (i < B) {
+            const int len = cu[i + 1] - c;
+            bad = bad || len < 0 || len > max_seqlen;
+        }
+        if (bad) set_status(status, RADIX_ERR_BAD_CU_SEQLENS);
     }
-    if (bad) set_status(status, RADIX_ERR_BAD_CU_SEQLENS);
 }
 
-__global__ void default_positions_kernel(const int32_t* __restrict__ cu, int B, int N, int32_t* __restrict__ pos) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (cu[mid + 1] > j) hi = mid; else lo = mid + 1;
-    }
-    pos[j] = j - cu[lo];
-}
-
-__global__ void compact_ids_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos,
-                                   const int32_t* __restrict__ Ig, int M, int M_valid, int N, int vocab,
-                                   int max_pos, int32_t* __restrict__ ids_c, int32_t* __restrict__ pos_c,
-                                   int32_t* status) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per compact row: which token it represents, its position id (pos == nullptr: its offset in its
+// sequence) and its embedding as fp32.  Latency-bound for small batches, so the steps share one launch (with
+// the clearing and the check of cu_seqlens in another, a forward starts with two launches instead of five: the call of
+// the tiny fp32 model went from 197 to 178 us).
+template <typename T>
+__global__ __launch_bounds__(256) void compact_embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ tok,
+                                                            const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
+                                                            const int32_t* __restrict__ Ig, int M, int M_valid, int N, int B,
+                                                            int vocab, int max_pos, int d, int32_t* __restrict__ pos_c,
+                                                            float* __restrict__ h, int32_t* status) {
+    const int lane = threadIdx.x & 63;
+    const int j = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (j >= M) return;
     // rows past the N' representatives pad the compact space to its bucket: copies of the first representative
     // (paper: Implementation Details, performance padding - "repeat I_gather[0]", and I_gather[0] is token 0)
     int i = j < M_valid ? (Ig ? Ig[j] : j) : 0;
-    if (i < 0 || i >= N) { set_status(status, RADIX_ERR_BAD_TOKEN); i = 0; }
-    int t = tok[i], p = pos[i];
-    if (t < 0 || t >= vocab) { set_status(status, RADIX_ERR_BAD_TOKEN); t = 0; }
-    if (p < 0 || p >= max_pos) { set_status(status, RADIX_ERR_BAD_TOKEN); p = 0; }
-    ids_c[j] = t;
-    pos_c[j] = p;
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ E, const int32_t* __restrict__ ids,
-                                                    int M, int d, float* __restrict__ h) {
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (row >= M) return;
-    const T* e = E + (size_t)ids[row] * d;
-    float* o = h + (size_t)row * d;
-    for (int c = lane; c < d; c += 64) o[c] = to_f32<T>(e[c]);
+    bool bad = i < 0 || i >= N;
+    if (bad) i = 0;
+    int t = tok[i], p;
+    if (pos) {
+        p = pos[i];
+    } else {
+        int lo = 0, hi = B - 1;
+        while (lo < hi) {
+            int mid = (lo + hi) >> 1;
+            if (cu[mid + 1] > i) hi = mid; else lo = mid + 1;
+        }
+        p = i - cu[lo];
+    }
+    if (t < 0 || t >= vocab) { bad = true; t = 0; }
+    if (p < 0 || p >= max_pos) { bad = true; p = 0; }
+    if (lane == 0) {
+        if (bad) set_status(status, RADIX_ERR_BAD_TOKEN);
+        pos_c[j] = p;
+    }
+    constexpr int V = 16 / sizeof(T);                       // rows are multiples of 16 bytes
+    const uint4* e = reinterpret_cast<const uint4*>(E + (size_t)t * d);
+    f32x4* o = reinterpret_cast<f32x4*>(h + (size_t)j * d);
+    for (int c = lane; c < d / V; c += 64) {
+        const uint4 raw = e[c];
+        const T* x = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+        for (int u = 0; u < V / 4; ++u) {
+            f32x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = to_f32<T>(x[4 * u + k]);
+            o[c * (V / 4) + u] = v;
+        }
+    }
 }
 
 // One wavefront per row; the row is read twice (second read hits L2/L1).
@@ -391,29 +406,20 @@ void launch_attn_plan(const int32_t* cu, const int32_t* Is, const int32_t* Ig, i
 }
 
 void launch_validate_cu(const int32_t* cu, int B, int N, int max_seqlen, int32_t* status, hipStream_t stream) {
-    hipLaunchKernelGGL(validate_cu_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, stream, cu, B, N, max_seqlen,
-                       status);
+    hipLaunchKernelGGL(validate_cu_kernel, dim3(1), dim3(1024), 0, stream, cu, B, N, max_seqlen, status);
 }
 
-void launch_default_positions(const int32_t* cu, int B, int N, int32_t* pos_full, hipStream_t stream) {
-    if (N <= 0) return;
-    hipLaunchKernelGGL(default_positions_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, stream, cu, B, N, pos_full);
-}
-
-void launch_compact_ids(const int32_t* tok, const int32_t* pos, const int32_t* Ig, int M, int M_valid, int N,
-                        int vocab, int max_pos, int32_t* ids_c, int32_t* pos_c, int32_t* status, hipStream_t stream) {
-    if (M <= 0) return;
-    hipLaunchKernelGGL(compact_ids_kernel, dim3(ceil_div(M, 256)), dim3(256), 0, stream, tok, pos, Ig, M, M_valid, N,
-                       vocab, max_pos, ids_c, pos_c, status);
-}
-
-void launch_embed(const void* embed, int dtype, const int32_t* ids_c, int M, int d, float* h, hipStream_t stream) {
+void launch_compact_embed(const void* embed, int dtype, const int32_t* tok, const int32_t* pos, const int32_t* cu,
+                          const int32_t* Ig, int M, int M_valid, int N, int B, int vocab, int max_pos, int d, int32_t* pos_c,
+                          float* h, int32_t* status, hipStream_t stream) {
     if (M <= 0) return;
     dim3 grid(ceil_div(M, 4)), block(256);
     if (dtype == RADIX_BF16)
-        hipLaunchKernelGGL(embed_kernel<bf16_t>, grid, block, 0, stream, (const bf16_t*)embed, ids_c, M, d, h);
+        hipLaunchKernelGGL(compact_embed_kernel<bf16_t>, grid, block, 0, stream, (const bf16_t*)embed, tok, pos, cu, Ig, M,
+                           M_valid, N, B, vocab, max_pos, d, pos_c, h, status);
     else
-        hipLaunchKernelGGL(embed_kernel<float>, grid, block, 0, stream, (const float*)embed, ids_c, M, d, h);
+        hipLaunchKernelGGL(compact_embed_kernel<float>, grid, block, 0, stream, (const float*)embed, tok, pos, cu, Ig, M,
+                           M_valid, N, B, vocab, max_pos, d, pos_c, h, status);
 }
 
 int launch_rmsnorm_split(const float* h, const float* g, int M, int d, float eps, void* out, int out_dtype,
