@@ -641,11 +641,20 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
         hipLaunchKernelGGL(kfn, grid, block, 0, stream, (const T*)A, (const T*)W, M, Nout, K, out, tiles_m,   \
                            tiles_n, w_k, qe, amap, nf, band_cfg);                                             \
     } while (0)
+    // the 128-row tiles serve folded norms only: the epilogues that consume or produce one
+    constexpr bool ALL = BM == 256;
     if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE);
-    else if (epilogue == EPI_RESIDUAL) RADIX_LAUNCH(EPI_RESIDUAL);
     else if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU);
-    else if (epilogue == EPI_SWIGLU_SPLIT) RADIX_LAUNCH(EPI_SWIGLU_SPLIT);
-    else if (epilogue == EPI_STORE_F32) RADIX_LAUNCH(EPI_STORE_F32);
+    else if (epilogue == EPI_RESIDUAL) {
+        if constexpr (ALL) RADIX_LAUNCH(EPI_RESIDUAL);
+        else return RADIX_ERR_UNSUPPORTED;
+    } else if (epilogue == EPI_SWIGLU_SPLIT) {
+        if constexpr (ALL) RADIX_LAUNCH(EPI_SWIGLU_SPLIT);
+        else return RADIX_ERR_UNSUPPORTED;
+    } else if (epilogue == EPI_STORE_F32) {
+        if constexpr (ALL) RADIX_LAUNCH(EPI_STORE_F32);
+        else return RADIX_ERR_UNSUPPORTED;
+    }
     else if (epilogue == EPI_RESIDUAL_NORM) {
         if constexpr (BN / WAVES_N == 128 && WAVES_M * WAVES_N == 4) RADIX_LAUNCH(EPI_RESIDUAL_NORM);
         else return RADIX_ERR_UNSUPPORTED;
@@ -654,7 +663,7 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
         if constexpr (BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE);
         else return RADIX_ERR_UNSUPPORTED;
     } else if (epilogue == EPI_QKV_ROPE_SPLIT) {
-        if constexpr (BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT);
+        if constexpr (ALL && BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT);
         else return RADIX_ERR_UNSUPPORTED;
     } else return RADIX_ERR_UNSUPPORTED;
 #undef RADIX_LAUNCH

@@ -381,7 +381,7 @@ template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int NS>
 int launch_small_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out,
                      const QkvEpilogue& qe, const ARowMap& amap, hipStream_t stream) {
     typedef typename Op<DT>::T T;
-    if (Nout % BN != 0) return RADIX_ERR_UNSUPPORTED;
+    if (Nout % BN != 0 || K % SBK != 0 || w_k % SBK != 0) return RADIX_ERR_UNSUPPORTED;
     const int tiles_m = ceil_div(M, BM), tiles_n = Nout / BN;
     if ((long long)tiles_m * tiles_n > 0x7FFFFFFFLL) return RADIX_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * WAVES_M * WAVES_N);

@@ -103,6 +103,17 @@ def test_index_first_round_over_the_chip(B, with_pos):
     U.assert_index_parity(tok, cu, pos)
 
 
+@pytest.mark.parametrize("B", [4095, 4096, 4097, 9000])
+def test_index_table_in_lds_and_in_memory(B):
+    # around the number of sequences whose grouping table still fits LDS: many followers leave a leader at one depth,
+    # with few (collisions of equal keys) and with many (collisions of slots) distinct tokens
+    rng = np.random.default_rng(B)
+    seqs = [np.concatenate([[7, 7], rng.integers(0, 3 if b % 2 else 100000, size=int(rng.integers(0, 4)))]).astype(np.int32)
+            for b in range(B)]
+    cu = np.concatenate([[0], np.cumsum([len(s) for s in seqs])]).astype(np.int32)
+    U.assert_index_parity(np.concatenate(seqs), cu)
+
+
 @pytest.mark.parametrize("B", [17, 300])
 def test_malformed_cu_seqlens_leaves_the_maps_untouched(B):
     n = 10 * B
