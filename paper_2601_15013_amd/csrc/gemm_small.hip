@@ -1,17 +1,25 @@
-// 16-bit MFMA GEMM for launches that the large tiles of gemm_mfma.hip leave most of the chip idle on:
-// C[M, Nout] = A[M, K] * W[Nout, K]^T with the same fused epilogues, in tiles of 32x32 to 128x64.
+// 16-bit MFMA GEMM for launches that the large tiles of gemm_mfma.hip leave much of the chip idle on:
+// C[M, Nout] = A[M, K] * W[Nout, K]^T with the same fused epilogues, in tiles of 32x16 to 256x128.
 //
-// What bounds these launches is latency: a few dozen to a few hundred rows against a weight matrix that has to
+// What bounds these launches is latency: a few dozen to a few thousand rows against a weight matrix that has to
 // come from HBM once.  A 128-row tile gives such a launch 8 to 100 workgroups of 256 CUs, each of which walks all
 // of K alone.  Splitting K over workgroups would shorten the walk, but an output element must be summed in the
 // same order whatever M is (a row of the deduplicated and of the plain pass agree bit for bit), so the tiles get
-// smaller instead: every element is the same chain of v_mfma_f32_32x32x16 over k = 0, 16, 32, ... as in the large
-// kernel, with the same epilogue expressions, and the results are identical.
+// smaller instead: every element is the chain of matrix instructions of the large kernel (one v_mfma_f32_16x16x32
+// rounds like two v_mfma_f32_32x32x16) with the same epilogue expressions, and the results are identical.
 //
 // Structure: k-tiles of 64 (a row is one 128-byte line) travel global -> LDS by global_load_lds_dwordx4 through a
-// ring of NS stages; the fragments of tile t+1 are read into a second register set before the MFMAs of tile t, so
-// neither the LDS latency nor, with NS - 1 tiles in flight, that of the memory is on the MFMA chain.  One barrier
-// per k-tile.  The epilogue goes through LDS as fp32, from where every thread takes whole 16-byte pieces of a row.
+// ring of NS stages; the fragments of the next tile (small wavefront blocks) or k-step (large ones) are read ahead of
+// the MFMAs, so neither the LDS latency nor, with NS - 1 tiles in flight, that of the memory is on the MFMA chain.  One
+// barrier per k-tile.  What is left per k-tile is the issue of the loads, about 40 cycles each in the wavefront that
+// issues it: the smallest tiles spread them over the most CUs (32x16 with two wavefronts: three loads each).  The
+// epilogue goes through LDS as fp32, from where every thread takes whole 16-byte pieces of a row.
+//
+// us per launch, fp16, weights from HBM, best 128-row tile of gemm_mfma.hip -> this kernel:
+//   M 21:   N 4096 K 1024 (q|k|v) 21.6 -> 7.1, N 1024 K 2048 14.0 -> 5.4, N 6144 K 1024 (gate/up) 11.0 -> 6.2,
+//           N 1024 K 3072 19.4 -> 6.8, N 4096 K 12288 96 -> 25
+//   M 1072: N 1024 K 2048 19.7 -> 13.8, N 1024 K 3072 27.3 -> 18.7, N 4096 K 12288 169 -> 141
+//   M 768:  N 24576 K 4096 183 -> 163, N 4096 K 12288 131 -> 112
 #include <type_traits>
 
 #include "gemm_async.h"
