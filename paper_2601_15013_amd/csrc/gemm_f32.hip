@@ -2,17 +2,19 @@
 // parity-oriented).  LDS-tiled FMA kernel, K consumed in order by one fused multiply-add chain per output element,
 // so every element is reduced in the same order whatever the tile and wherever its row sits in the matrix.
 //
-// These launches are latency-bound: a few hundred rows give a few dozen workgroups, and the time is the number of
-// k-tiles times what one costs.  So a k-tile is 64 wide, the next one is fetched into registers (16 bytes per lane) while
-// the present one is multiplied, LDS is read 16 bytes along k, and the tile is TM x TM outputs with TM = 16 R, the smaller
-// the fewer workgroups the launch has.  At M 160, N 256, K 768: 75 us with a 64 x 64 tile, k-tiles of 16 and no
-// prefetch, 7.7 us (mean of it and the K 256 one) with this kernel.
+// Two regimes.  With few rows the launch is latency-bound: a few dozen workgroups, and the time is the number of k-tiles
+// times what one costs.  So the outputs of a tile are TM x TM with TM = 16 R, the smaller the fewer workgroups there
+// are, the k-tile of the small ones is 64 wide, the next one is fetched into registers (16 bytes per lane) while the
+// present one is multiplied, and LDS is read 16 bytes along k.  M 300, K 768, N 256: 27.9 us with R = 2, against 88.5 us
+// with a 64 x 64 tile of scalar LDS reads, k-tiles of 16 and no prefetch.
+// With many rows every CU has several workgroups that hide each other's latency, and what counts is how many fit: the
+// 64 x 64 tile (R = 4) takes k-tiles of 16 (10 KB of LDS and 88 registers against 35 KB and 116 with k-tiles of 64).
+// us with k-tiles of 64 / 32 / 16 / the kernel of scalar reads: M 24000 N 1536 K 256 (gate/up) 410 / 377 / 270 / 345;
+// M 65000 N 256 K 768 641 / 595 / 355 / 478 (72 TFLOP/s); M 12000 N 6144 K 1024 3066 / 2912 / 1902 / 2444 (79 TFLOP/s).
 #include "common.h"
 #include "kernels.h"
 
 namespace {
-
-constexpr int TK = 64, PK = TK + 4;      // k-tile and its pitch in LDS: 16 rows start in 16 different 16-byte bank groups
 
 // 256 threads = 16 x 16; thread (tx, ty) owns rows ty + 16 i and columns tx + 16 j, i, j < R.
 template <int R, int EPI>
@@ -21,7 +23,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     static_assert(EPI != EPI_SWIGLU || R == 4 || R == 2, "gate and up blocks of 32 columns meet in one tile");
     // SwiGLU with a 32-wide tile takes 16 gate columns and the 16 matching up columns, else 64 = 32 gate + 32 up
     constexpr bool PAIR16 = EPI == EPI_SWIGLU && R == 2;
+    constexpr int TK = R == 4 ? 16 : 64, PK = TK + 4;      // k-tile and its pitch in LDS: 16 rows start in 16 different 16-byte bank groups
     constexpr int TM = 16 * R, LD = TM * TK / 4 / 256;
+    static_assert(LD >= 1 && LD * 256 * 4 == TM * TK, "every thread fetches whole pieces of 16 bytes");
     __shared__ float As[TM * PK];
     __shared__ float Ws[TM * PK];
     const int tid = threadIdx.x;
@@ -110,12 +114,14 @@ void launch_r(const float* A, const float* W, int M, int Nout, int K, float* out
     }
 }
 
-// Tile by workgroup count: a larger tile reads LDS less per multiply-add (the bound once every CU has work), a smaller
-// one shortens the k-tile while CUs would be idle.
+// Tile by workgroup count: the largest one reads LDS least per multiply-add, the smaller ones shorten the walk along K
+// while CUs would be idle.  Measured at the line between 64 x 64 and 32 x 32 tiles (us): 176 large tiles 67.4 / 62.9 (M 700, N
+// 1024, K 1024) and 194 / 173 (K 3072), 192 tiles 18.7 / 19.9 (M 1500, N 512, K 256), 240 tiles 65.3 / 80.2 (M 300, N 3072,
+// K 1024).
 template <int EPI>
 void launch_epi(const float* A, const float* W, int M, int Nout, int K, float* out, hipStream_t stream) {
     const long long t64 = (long long)ceil_div(M, 64) * ceil_div(Nout, 64), t32 = (long long)ceil_div(M, 32) * ceil_div(Nout, 32);
-    if (t64 >= 256) launch_r<4, EPI>(A, W, M, Nout, K, out, stream);
+    if (t64 >= 192) launch_r<4, EPI>(A, W, M, Nout, K, out, stream);
     else if (EPI == EPI_SWIGLU || t32 >= 256) launch_r<2, EPI>(A, W, M, Nout, K, out, stream);
     else launch_r<EPI == EPI_SWIGLU ? 2 : 1, EPI>(A, W, M, Nout, K, out, stream);
 }
