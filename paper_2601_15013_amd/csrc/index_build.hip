@@ -8,7 +8,7 @@
 //   * Every sequence s follows a leader: the lowest-numbered sequence known to share s's path
 //     so far.  All sequences start by following the first non-empty sequence.
 //   * One round = one trie branching level on each follower's path.  A wavefront compares the
-//     follower with its leader 256 tokens at a time (coalesced loads + ballot) until the first
+//     follower with its leader 256 tokens (first round over the chip: 512) at a time (coalesced loads + ballot) until the first
 //     (token, position) mismatch m.  Positions below m are duplicates of the leader's nodes.
 //   * Followers that leave the same leader at the same depth with the same (token, position)
 //     key enter the same child node.  They are grouped by an exact open-addressing table
@@ -28,6 +28,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "radixmlp_bench.h"
 
 namespace {
 
@@ -354,6 +355,19 @@ extern "C" int radix_index_workspace_bytes(int32_t max_B, size_t* bytes_out) {
 
 namespace {
 
+// Whether the comparisons of the first round get a launch over the whole chip (two launches more, 3.5 us).  In the chain
+// kernel IDX_WAVES followers are compared at a time; every further step of that loop costs 0.9 us and 4 ns per token
+// compared.  How many tokens that will be is not known before; half of the mean length is counted.  A line 1 us above
+// break-even keeps batches that share less from losing.  Measured (us, one kernel / over the chip): 24 sequences of a
+// shared prefix of 16 tokens 37.4 / 39.8, of 2048 tokens 51.8 / 47.4; 48 of 16 tokens 38.9 / 40.8, of 1024 50.5 / 44.3;
+// 64 of 16 tokens 41.0 / 41.6, of 512 48.5 / 43.2; 96 of 16 tokens 43.2 / 42.3; nothing shared, 48 of 300 to 600 tokens
+// 40.4 / 41.4.
+bool first_round_over_the_chip(int B, int N) {
+    if (B <= IDX_WAVES) return false;
+    const long long more_steps = (B - 2) / IDX_WAVES;           // B - 1 followers
+    return more_steps * (900 + 4 * (long long)(N / B) / 2) >= 4500;
+}
+
 int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_seqlens, int32_t B, int32_t N,
                      int32_t* I_scatter, int32_t* I_gather, int32_t* n_compact_dev, int32_t* n_compact_host,
                      void* ws, hipStream_t stream) {
@@ -370,12 +384,11 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     int32_t* slot_owner = cbase + Bn;
     int32_t* slot_min = slot_owner + H;
 
-    // the chain kernel initialises every word of builder state it reads (status word, per-sequence arrays, both
-    // slot tables), so the buffer may hold anything when the call starts
-    // More sequences than the chain kernel has wavefronts: its first round, which reads the shared prefix of every
-    // sequence, is spread over the chip.  Two launches more; 2048 sequences of 512 tokens with 256 shared: 655 us in
-    // one kernel, 57 us in four (85 us from call to call, with the wait for the count).
-    const int first_done = B > IDX_WAVES && N > 0;
+    // The launches of one call together initialise every word of builder state that they read, so the buffer may hold
+    // anything when the call starts: index_init (in the launch of its own or inside the chain kernel) writes the status word
+    // and the per-sequence arrays, the chain kernel its slot table (in LDS up to LDS_TABLE slots; the tables in the
+    // workspace are for larger batches).
+    const int first_done = N > 0 && first_round_over_the_chip(B, N);
     if (first_done) {
         hipLaunchKernelGGL(index_init_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr, ldr, dep, bdep,
                            mis, n_compact_dev);
@@ -411,6 +424,11 @@ int check_index_args(const int32_t* tok, const int32_t* cu_seqlens, int32_t B, i
 }
 
 }  // namespace
+
+extern "C" int radix_debug_index_first_round(int32_t B, int32_t N) {
+    if (B <= 0 || N <= 0) return RADIX_ERR_BAD_SIZE;
+    return first_round_over_the_chip(B, N) ? 1 : 0;
+}
 
 extern "C" int radix_build_index(const int32_t* tok, const int32_t* pos, const int32_t* cu_seqlens,
                                  int32_t B, int32_t N, int32_t* I_scatter, int32_t* I_gather,

@@ -77,7 +77,7 @@ def test_lm_head_rows_do_not_depend_on_their_number(n_rows):
 @pytest.mark.parametrize("B", [1, 15, 16, 17, 18, 63, 257, 1025])
 @pytest.mark.parametrize("with_pos", [False, True])
 def test_index_first_round_over_the_chip(B, with_pos):
-    # around the number of sequences from which on the first round of comparisons has a launch of its own: shared
+    # on both sides of where the first round of comparisons gets a launch of its own (by the amount to compare): shared
     # prefixes longer than a wavefront's stride, empty sequences in front and between, duplicates, whole prefixes
     rng = np.random.default_rng(B)
     base = rng.integers(0, 50, size=1300, dtype=np.int32)
