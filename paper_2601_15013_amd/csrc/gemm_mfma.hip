@@ -756,10 +756,11 @@ bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
     return true;
 }
 
-int best_tile(int M, int Nout, int K, int epilogue, double* us) {
+// whole: only tiles that divide the rows
+int best_tile(int M, int Nout, int K, int epilogue, bool whole, double* us) {
     int v = 0;
     for (const TileShape& sh : tile_shapes) {
-        if (!tile_usable(sh, Nout, epilogue)) continue;
+        if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
         const double t = tile_time(sh, M, Nout, K);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
     }
@@ -772,9 +773,10 @@ int best_tile(int M, int Nout, int K, int epilogue, double* us) {
 // tiles (M 8240, K 1024, N 4096: 111 us in one launch of 256x256, 93 us split; K 3072, N 1024: 79 and 62 us).
 struct GemmPlan { int v1, m1, v2; };
 GemmPlan plan_gemm(int M, int Nout, int K, int epilogue) {
-    double best = 0.0;
-    GemmPlan p = {best_tile(M, Nout, K, epilogue, &best), M, 0};
+    double whole = 0.0;
+    GemmPlan p = {best_tile(M, Nout, K, epilogue, false, &whole), M, 0};
     if (M <= 256) return p;
+    double best = 0.97 * whole;             // what a split has to beat: a launch more, and the model's own error
     for (const TileShape& sh : tile_shapes) {
         if (sh.bm < 128 || !tile_usable(sh, Nout, epilogue)) continue;
         const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
@@ -782,10 +784,9 @@ GemmPlan plan_gemm(int M, int Nout, int K, int epilogue) {
         if (rounds < 1 || rounds >= 8) continue;
         const long long m1 = rounds * N_CU / per_row * sh.bm;
         if (m1 < sh.bm || m1 >= M) continue;
-        double t2 = 0.0;
-        const int v2 = best_tile(M - (int)m1, Nout, K, epilogue, &t2);
-        const double t = tile_time(sh, (int)m1, Nout, K) + t2;
-        if (t < 0.97 * best) { best = t; p.v1 = sh.variant; p.m1 = (int)m1; p.v2 = v2; }
+        double t1 = 0.0, t2 = 0.0;              // rows that fill rounds of this tile may still run faster in another one
+        const int v1 = best_tile((int)m1, Nout, K, epilogue, true, &t1), v2 = best_tile(M - (int)m1, Nout, K, epilogue, false, &t2);
+        if (t1 + t2 < best) { best = t1 + t2; p = {v1, (int)m1, v2}; }
     }
     return p;
 }
@@ -872,4 +873,19 @@ extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t
         if (sh.variant == p.v2) { *bm2 = sh.bm; *bn2 = sh.bn; }
     }
     return p.v1 ? RADIX_OK : RADIX_ERR_UNSUPPORTED;
+}
+extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t v1, int32_t m1, int32_t v2,
+                                        double* us) {
+    if (!us) return RADIX_ERR_NULL_POINTER;
+    if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0 || m1 <= 0 || m1 > M) return RADIX_ERR_BAD_SIZE;
+    double t = 0.0;
+    int parts = 0;
+    for (const TileShape& sh : tile_shapes) {
+        if (!tile_usable(sh, Nout, epilogue)) continue;
+        if (sh.variant == v1) { t += tile_time(sh, m1, Nout, K); ++parts; }
+        if (m1 < M && sh.variant == v2) { t += tile_time(sh, M - m1, Nout, K); ++parts; }
+    }
+    if (parts != (m1 < M ? 2 : 1)) return RADIX_ERR_UNSUPPORTED;
+    *us = t;
+    return RADIX_OK;
 }

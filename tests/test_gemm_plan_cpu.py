@@ -49,3 +49,34 @@ def test_every_size_has_a_plan_that_covers_its_rows(plan, epilogue):
 
 def test_plan_rejects_bad_sizes(plan):
     assert plan(0, 128, 64, 0)[0] == -2 and plan(8, 128, 0, 0)[0] == -2
+
+
+# rows and widths of the projections (output projection, down, gate/up, q|k|v) of the 0.6B, 4B and 8B shapes
+PROJECTIONS = [(1024, 2048, RESIDUAL), (1024, 3072, RESIDUAL), (6144, 1024, SWIGLU), (4096, 1024, QKV_ROPE),
+               (2560, 4096, RESIDUAL), (2560, 9728, RESIDUAL), (19456, 2560, SWIGLU), (6144, 2560, QKV_ROPE),
+               (4096, 4096, RESIDUAL), (4096, 12288, RESIDUAL), (24576, 4096, SWIGLU), (6144, 4096, QKV_ROPE)]
+VARIANTS = {1: 256, 4: 256, 11: 32, 12: 32, 13: 32, 14: 32, 15: 64, 16: 64, 17: 64, 18: 128, 19: 128, 20: 256}      # rows of a tile
+
+
+def test_plan_is_the_fastest_that_the_cost_model_knows(plan):
+    lib = binding.load_library()
+
+    def us(m, nout, k, epi, v1, m1, v2):
+        t = C.c_double(-1.0)
+        rc = lib.radix_debug_gemm_plan_us(m, nout, k, epi, v1, m1, v2, C.byref(t))
+        return t.value if rc == 0 else float("inf")
+
+    for nout, k, epi in PROJECTIONS:
+        for m in list(range(257, 20000, 223)) + [7916, 9216, 8672, 939, 658, 33792, 50645]:
+            rc, (v1, bm1, _, m1, v2, _, _) = plan(m, nout, k, epi)
+            assert rc == 0
+            t = us(m, nout, k, epi, v1, m1, v2)
+            whole = min(us(m, nout, k, epi, v, m, 0) for v in VARIANTS)
+            assert t == whole if m1 == m else t < 0.97 * whole, (m, nout, k)
+            # no other tile in either part of the chosen split is faster (in the first part: of those that divide its rows)
+            for v, bm in VARIANTS.items():
+                assert (m1 < m and m1 % bm) or us(m, nout, k, epi, v, m1, v2) >= t, (m, nout, k, v1, v)
+                if m1 < m:
+                    assert us(m, nout, k, epi, v1, m1, v) >= t, (m, nout, k, v2, v)
+            # the four-wavefront 256x256 tile pays from 16000 columns on only
+            assert 1 not in (v1, v2 if m1 < m else 0), (m, nout, k)
