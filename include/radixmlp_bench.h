@@ -44,12 +44,15 @@ int radix_timing_collect(float* total_ms_host, int32_t* launches_host);
  * rows of K elements (>= 1), or a negative status.
  * radix_debug_gemm_plan: the tiles a 16-bit product C[M, Nout] = A[M, K] W^T with epilogue code `epilogue` runs in: rows
  * [0, *m1) in tiles of shape *v1 (*bm1 x *bn1), the rest, if *m1 < M, in tiles of shape *v2 (*bm2 x *bn2).
+ * radix_debug_gemm_plan_cus: the same for a device (a partition) of `cus` CUs instead of the present one.
  * radix_debug_gemm_plan_us: the time that the cost model behind that choice gives such a split (v2 is not read if m1 == M).
  * radix_debug_index_first_round: 1 if the index builder spreads its first round over the whole chip for B sequences of N
  * tokens together, 0 if one workgroup runs it, or a negative status.
  */
 int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1, int32_t* bn1,
                           int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2);
+int radix_debug_gemm_plan_cus(int32_t cus, int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
+                              int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2);
 int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t v1, int32_t m1, int32_t v2, double* us);
 int radix_debug_gemm_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n, int32_t band, int32_t* tm, int32_t* tn);
 int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles_n);

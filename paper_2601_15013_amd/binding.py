@@ -24,7 +24,8 @@ EXPORTS = (
     "radix_dedup_decision",
     "radix_lm_head_workspace_bytes", "radix_lm_head",
     "radix_index_select_rows", "radix_device_status", "radix_status_string",
-    "radix_timing_enable", "radix_timing_collect", "radix_debug_gemm_tile", "radix_debug_gemm_band", "radix_debug_gemm_plan", "radix_debug_gemm_plan_us",
+    "radix_timing_enable", "radix_timing_collect", "radix_debug_gemm_tile", "radix_debug_gemm_band", "radix_debug_gemm_plan", "radix_debug_gemm_plan_cus",
+    "radix_debug_gemm_plan_us",
     "radix_debug_index_first_round",
 )
 
@@ -91,6 +92,7 @@ def _lib() -> C.CDLL:
         lib.radix_debug_gemm_tile.argtypes = [i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
         lib.radix_debug_gemm_band.argtypes = [i32, i32, i32]
         lib.radix_debug_gemm_plan.argtypes = [i32] * 4 + [C.POINTER(i32)] * 7
+        lib.radix_debug_gemm_plan_cus.argtypes = [i32] * 5 + [C.POINTER(i32)] * 7
         lib.radix_debug_gemm_plan_us.argtypes = [i32] * 7 + [C.POINTER(C.c_double)]
         lib.radix_debug_index_first_round.argtypes = [i32] * 2
         lib.radix_status_string.argtypes = [C.c_int]

@@ -670,6 +670,19 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
     return RADIX_OK;
 }
 
+// CUs of the device (a partition has fewer than the chip's 256); 256 where there is no device to ask
+int device_cus() {
+    static int n_cu = 0;
+    if (n_cu == 0) {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+            cus = 256;
+        n_cu = cus;
+    }
+    return n_cu;
+}
+
 template <int DT>
 int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out, int variant,
               const QkvEpilogue& qe, const ARowMap& amap, const NormFusion& nf, hipStream_t stream) {
@@ -680,14 +693,7 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     // 256 registers each) lose nothing in the main loop and overlap each other's epilogue and first loads:
     // 1 to 4 us less per round; the four-wavefront tile is only chosen at K > 16000.
     if (variant == 0) {
-        static int n_cu = 0;
-        if (n_cu == 0) {
-            int dev = 0, cus = 0;
-            if (hipGetDevice(&dev) != hipSuccess ||
-                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-                cus = 256;
-            n_cu = cus;
-        }
+        const int n_cu = device_cus();
         struct Shape { int variant, bm, bn, wave_cols; double fixed_us, ktile_us; };
         static const Shape shapes[5] = {{4, 256, 256, 128, 8.0, 0.832}, {1, 256, 256, 128, 9.0, 0.83},
                                         {5, 128, 256, 64, 6.5, 0.54},   {3, 128, 256, 128, 7.0, 0.57},
@@ -737,12 +743,11 @@ const TileShape tile_shapes[] = {
     {19, 128, 256, 1, 0.00, 7.75, 0.797, 0.000},
     {20, 256, 128, 1, 0.00, 8.71, 0.748, 0.000},
 };
-constexpr int N_CU = 256;
 
-double tile_time(const TileShape& sh, int M, int Nout, int K) {
+double tile_time(const TileShape& sh, int cus, int M, int Nout, int K) {
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
-    double per = (double)tiles / N_CU;
-    if (per < 8.0) per = (double)((tiles + N_CU - 1) / N_CU);
+    double per = (double)tiles / cus;
+    if (per < 8.0) per = (double)((tiles + cus - 1) / cus);
     const double kt = K / 64;
     const double full = (double)(long long)(per / sh.per_cu), rest = per - full * sh.per_cu;
     auto round_us = [&](double n) { return sh.fixed_us + kt * (n * sh.share_us > sh.step_us ? n * sh.share_us : sh.step_us); };
@@ -757,11 +762,11 @@ bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
 }
 
 // whole: only tiles that divide the rows
-int best_tile(int M, int Nout, int K, int epilogue, bool whole, double* us) {
+int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double* us) {
     int v = 0;
     for (const TileShape& sh : tile_shapes) {
         if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
-        const double t = tile_time(sh, M, Nout, K);
+        const double t = tile_time(sh, cus, M, Nout, K);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
     }
     return v;
@@ -772,20 +777,21 @@ int best_tile(int M, int Nout, int K, int epilogue, bool whole, double* us) {
 // are 33 row tiles of 256, and 32 of them are whole rounds of the chip - the rows past the last full round go to smaller
 // tiles (M 8240, K 1024, N 4096: 111 us in one launch of 256x256, 93 us split; K 3072, N 1024: 79 and 62 us).
 struct GemmPlan { int v1, m1, v2; };
-GemmPlan plan_gemm(int M, int Nout, int K, int epilogue) {
+GemmPlan plan_gemm(int cus, int M, int Nout, int K, int epilogue) {
     double whole = 0.0;
-    GemmPlan p = {best_tile(M, Nout, K, epilogue, false, &whole), M, 0};
+    GemmPlan p = {best_tile(cus, M, Nout, K, epilogue, false, &whole), M, 0};
     if (M <= 256) return p;
     double best = 0.97 * whole;             // what a split has to beat: a launch more, and the model's own error
     for (const TileShape& sh : tile_shapes) {
         if (sh.bm < 128 || !tile_usable(sh, Nout, epilogue)) continue;
         const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
-        const long long rounds = row_tiles * per_row / N_CU;
+        const long long rounds = row_tiles * per_row / cus;
         if (rounds < 1 || rounds >= 8) continue;
-        const long long m1 = rounds * N_CU / per_row * sh.bm;
+        const long long m1 = rounds * cus / per_row * sh.bm;
         if (m1 < sh.bm || m1 >= M) continue;
         double t1 = 0.0, t2 = 0.0;              // rows that fill rounds of this tile may still run faster in another one
-        const int v1 = best_tile((int)m1, Nout, K, epilogue, true, &t1), v2 = best_tile(M - (int)m1, Nout, K, epilogue, false, &t2);
+        const int v1 = best_tile(cus, (int)m1, Nout, K, epilogue, true, &t1);
+        const int v2 = best_tile(cus, M - (int)m1, Nout, K, epilogue, false, &t2);
         if (t1 + t2 < best) { best = t1 + t2; p = {v1, (int)m1, v2}; }
     }
     return p;
@@ -829,7 +835,7 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
     };
     if (variant != 0 || folded) return launch(variant, A, M, out);
     if (K % (2 * BK) != 0) return RADIX_ERR_UNSUPPORTED;
-    const GemmPlan plan = plan_gemm(M, Nout, K, epilogue);
+    const GemmPlan plan = plan_gemm(device_cus(), M, Nout, K, epilogue);
     if (plan.v1 == 0) return RADIX_ERR_UNSUPPORTED;
     const int rc = launch(plan.v1, A, plan.m1, out);
     if (rc != RADIX_OK || plan.m1 == M) return rc;
@@ -861,11 +867,11 @@ extern "C" int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles
     if (tile_rows <= 0 || K <= 0 || tiles_n <= 0) return RADIX_ERR_BAD_SIZE;
     return gemm_band_rows(tile_rows, K, 2, tiles_n);
 }
-extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
-                                     int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2) {
+extern "C" int radix_debug_gemm_plan_cus(int32_t cus, int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1,
+                                         int32_t* bm1, int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2) {
     if (!v1 || !bm1 || !bn1 || !m1 || !v2 || !bm2 || !bn2) return RADIX_ERR_NULL_POINTER;
-    if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0) return RADIX_ERR_BAD_SIZE;
-    const GemmPlan p = plan_gemm(M, Nout, K, epilogue);
+    if (cus <= 0 || M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0) return RADIX_ERR_BAD_SIZE;
+    const GemmPlan p = plan_gemm(cus, M, Nout, K, epilogue);
     *v1 = p.v1; *m1 = p.m1; *v2 = p.v2;
     *bm1 = *bn1 = *bm2 = *bn2 = 0;
     for (const TileShape& sh : tile_shapes) {
@@ -873,6 +879,10 @@ extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t
         if (sh.variant == p.v2) { *bm2 = sh.bm; *bn2 = sh.bn; }
     }
     return p.v1 ? RADIX_OK : RADIX_ERR_UNSUPPORTED;
+}
+extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
+                                     int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2) {
+    return radix_debug_gemm_plan_cus(device_cus(), M, Nout, K, epilogue, v1, bm1, bn1, m1, v2, bm2, bn2);
 }
 extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t v1, int32_t m1, int32_t v2,
                                         double* us) {
@@ -882,8 +892,8 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
     int parts = 0;
     for (const TileShape& sh : tile_shapes) {
         if (!tile_usable(sh, Nout, epilogue)) continue;
-        if (sh.variant == v1) { t += tile_time(sh, m1, Nout, K); ++parts; }
-        if (m1 < M && sh.variant == v2) { t += tile_time(sh, M - m1, Nout, K); ++parts; }
+        if (sh.variant == v1) { t += tile_time(sh, device_cus(), m1, Nout, K); ++parts; }
+        if (m1 < M && sh.variant == v2) { t += tile_time(sh, device_cus(), M - m1, Nout, K); ++parts; }
     }
     if (parts != (m1 < M ? 2 : 1)) return RADIX_ERR_UNSUPPORTED;
     *us = t;

@@ -80,3 +80,23 @@ def test_plan_is_the_fastest_that_the_cost_model_knows(plan):
                     assert us(m, nout, k, epi, v1, m1, v) >= t, (m, nout, k, v2, v)
             # the four-wavefront 256x256 tile pays from 16000 columns on only
             assert 1 not in (v1, v2 if m1 < m else 0), (m, nout, k)
+
+
+def test_plan_counts_the_cus_of_the_device(plan):
+    # a partition with the CUs of one XCD: its rounds are full with an eighth of the rows, and tiles grow accordingly
+    lib = binding.load_library()
+
+    def on(cus, *args):
+        out = [C.c_int32(-1) for _ in range(7)]
+        assert lib.radix_debug_gemm_plan_cus(cus, *args, *[C.byref(o) for o in out]) == 0
+        return [o.value for o in out]
+
+    for nout, k, epi in PROJECTIONS:
+        for m in (939, 1072, 2200, 8672):
+            assert on(256, m, nout, k, epi) == plan(m, nout, k, epi)[1]         # no device here: the whole chip
+    one, chip = on(32, 939, 1024, 3072, RESIDUAL), on(256, 939, 1024, 3072, RESIDUAL)
+    assert one[1] * one[2] > chip[1] * chip[2]
+    # 1072 rows of N 4096: 4 row tiles of 256 are two whole rounds of 32 CUs, and 48 rows are left
+    v1, bm1, bn1, m1, v2, bm2, bn2 = on(32, 1072, 4096, 4096, RESIDUAL)
+    assert m1 == 1024 and bm2 <= 64
+    assert lib.radix_debug_gemm_plan_cus(0, 8, 128, 64, 0, *[C.byref(C.c_int32()) for _ in range(7)]) == -2
