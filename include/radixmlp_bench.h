@@ -58,6 +58,19 @@ int radix_debug_gemm_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n, int32_t
 int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles_n);
 int radix_debug_index_first_round(int32_t B, int32_t N);
 
+/*
+ * One 16-bit product out = epilogue(A[M, K] W[Nout, w_k]^T) on the device in tiles of shape `variant` (as reported by
+ * radix_debug_gemm_plan; 0: the tiles of the plan), for tests that compare the tiles with each other.  Device pointers,
+ * caller-owned; out has the type and width of the epilogue.  Epilogue codes: 0 store, 1 add to fp32 rows, 2 SwiGLU, 3 q|k|v with
+ * norm and RoPE, 4 store fp32, 5 and 7: 2 and 3 as (hi, lo) pairs.  w_k: K, or K / 2 for rows of A that are (hi, lo) pairs (0: K).
+ * The q|k|v epilogues read gq, gk [128], cos, sin [positions, 64] and pos[M].  rows (may be NULL): row m < n_valid of the product is
+ * row rows[m] of A's n_src rows, the others row 0; bad entries are clamped and reported in *status.
+ */
+int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int32_t Nout, int32_t K, int32_t w_k, int32_t epilogue, void* out,
+                         int32_t op_dtype, int32_t variant, const float* gq, const float* gk, const float* cos_tab,
+                         const float* sin_tab, const int32_t* pos, int32_t n_q_heads, int32_t n_kv_heads, int32_t qk_norm,
+                         const int32_t* rows, int32_t n_valid, int32_t n_src, int32_t* status, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

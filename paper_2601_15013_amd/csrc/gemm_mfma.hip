@@ -899,3 +899,29 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
     *us = t;
     return RADIX_OK;
 }
+// One product on the device with the tile named (0: what the plan picks), for tests that compare the tiles.
+extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int32_t Nout, int32_t K, int32_t w_k, int32_t epilogue,
+                                    void* out, int32_t op_dtype, int32_t variant, const float* gq, const float* gk,
+                                    const float* cos_tab, const float* sin_tab, const int32_t* pos, int32_t n_q_heads,
+                                    int32_t n_kv_heads, int32_t qk_norm, const int32_t* rows, int32_t n_valid, int32_t n_src,
+                                    int32_t* status, void* stream) {
+    if (!A || !W || !out) return RADIX_ERR_NULL_POINTER;
+    if (M <= 0 || Nout <= 0 || K <= 0) return RADIX_ERR_BAD_SIZE;
+    const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
+    if (epilogue == EPI_RESIDUAL_NORM || epilogue < 0) return RADIX_ERR_UNSUPPORTED;
+    if (rope && (!gq || !gk || !cos_tab || !sin_tab || !pos)) return RADIX_ERR_NULL_POINTER;
+    if (rope && (n_q_heads < 0 || n_kv_heads < 0 || Nout != (n_q_heads + 2 * n_kv_heads) * 128)) return RADIX_ERR_BAD_SIZE;
+    if (rows && (!status || n_valid < 0 || n_valid > M)) return RADIX_ERR_BAD_SIZE;
+    if (variant != 0) {
+        bool known = false;
+        for (const TileShape& sh : tile_shapes) known = known || (sh.variant == variant && tile_usable(sh, Nout, epilogue));
+        if (!known) return RADIX_ERR_UNSUPPORTED;
+    }
+    const QkvEpilogue qe = {gq, gk, cos_tab, sin_tab, pos, n_q_heads, n_kv_heads, qk_norm, 1e-6f};
+    const ARowMap amap = {rows, n_valid, n_src, status};
+    const int rc = launch_gemm_mfma(A, W, M, Nout, K, epilogue, out, op_dtype, variant, (hipStream_t)stream, rope ? &qe : nullptr,
+                                    w_k, rows ? &amap : nullptr);
+    if (rc != RADIX_OK) return rc;
+    HIP_TRY(hipGetLastError());
+    return RADIX_OK;
+}
