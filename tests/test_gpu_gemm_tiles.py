@@ -2,6 +2,8 @@
 operands, split a product into two launches) by the row count, so a sequence alone, in a small batch and in a large one
 meets different kernels.  Every batch is compared with the same rows of the largest one bit for bit, and the largest one
 with the fp64 oracle."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -53,6 +55,31 @@ def test_rows_do_not_depend_on_the_batch(cfg, compute, hilo, tol):
         ref = oracle_forward.forward_nodedup(cfg, w.embed, w.layers, w.gf, t, np.array([0, len(t)], dtype=np.int32))
         got = full[cu[s]:cu[s + 1]]
         assert np.max(np.abs(got - ref)) <= tol * np.sqrt(np.mean(ref * ref)), s
+
+
+@pytest.mark.parametrize("own,pads", [(164, (64, 512)), (163, (1000,))])
+def test_padding_of_a_compact_space_whose_products_are_split(own, pads):
+    # 8230 or 8180 unique rows: the padded products are cut at 8192 rows, before the last representative and among the padding;
+    # the output projection of the three-kernel path reads its rows through I_gather on both sides of the cut
+    rng = np.random.default_rng(own)
+    prefix = rng.integers(0, 512, 30, dtype=np.int32)
+    seqs = [np.concatenate([prefix, [b], rng.integers(0, 512, own - 1)]).astype(np.int32) for b in range(50)]
+    cu = torch.from_numpy(np.concatenate([[0], np.cumsum([len(x) for x in seqs])]).astype(np.int32)).cuda()
+    tok = torch.from_numpy(np.concatenate(seqs)).cuda()
+    model = harness.upload_model(synth.SynthWeights(dataclasses.replace(WIDE, max_pos=256), 79))
+    try:
+        run = harness.Runner(model, tok.numel(), len(seqs))
+        maps = run.build_index(tok, cu)
+        assert maps[3] == 30 + 50 * own
+        longest = 30 + own
+        plain = run.forward_nodedup(tok, cu, longest)
+        for fused in (False, True):
+            for pad in (0,) + pads:
+                y = run.forward(tok, cu, longest, maps, force_dedup=True, fused_attention=fused, pad_compact_to=pad)
+                assert run.status() == 0
+                assert torch.equal(y, plain), (pad, fused)
+    finally:
+        model.close()
 
 
 @pytest.mark.parametrize("n_rows", [1, 33, 300])
