@@ -721,37 +721,53 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 }
 
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
-// in rounds; a round costs fixed_us (first loads, epilogue) and, per 64 columns of K, step_us (what a k-tile takes
-// when nothing else runs on the CU: a chain of latencies) or, with n of them sharing the CU, n share_us if that is more.
-// A launch that does not fill its last round pays for it in full, until there are many rounds.  The constants are
-// least-squares fits of the logarithm to 240 launches on MI355X (M 8 .. 8240, the four projections of the 0.6B, 4B and
-// 8B shapes, fp16 operands, weights from HBM; typical error 15 %); picking by them costs 1.5 % over the best
-// tile of each launch.  The 256x256 tiles of this file win once they fill the chip, their k-loop being the better one
-// (N 24576, K 4096, M 8240: 1480 us against 1640 for 256x256 built like the small ones); below, the smaller ones.
-struct TileShape { int variant, bm, bn, per_cu; double launch_us, fixed_us, step_us, share_us; };
+// in rounds.  A round of n workgroups per CU costs fixed_us (first loads, epilogue), n epi_us (what of the epilogue grows with
+// n, by what it writes: 16-bit rows, q|k|v heads, fp32 rows) and, per 64 columns of K, step_us (what a k-tile takes when
+// nothing else runs on the CU: a chain of latencies) or n share_us if that is more.  A launch that does not fill its last round
+// pays for it in full, until there are many rounds.
+// The constants are least-squares fits of the logarithm to timed launches on MI355X (fp16 operands), in two sets because rows
+// of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about (fits there even end
+// with zeros for some):
+//   long_k, K >= 1024: 240 launches of the four projections of the 0.6B, 4B and 8B shapes, M 8 .. 8240, weights from HBM.  Over
+//     29 products of six shapes at 25 row counts from 1 to 130000 they are within 15 % of a launch, and the tile they pick
+//     takes 0.8 % longer than the best one (a tenth of the launches more than 2 %, the worst 21 %).
+//   short_k: 24 products of K 64 .. 768 at the same row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
+//     takes 2.4 % (K 64 and 128), 1.3 % (256 to 384) and 0.7 % (512 to 768) longer than the best, where long_k's pick took 13,
+//     10 and 6 %; bf16 operands, not in the fit, 2.7, 1.2 and 0.7 %.
+// The four-wavefront 256x256 tile is entered in short_k by its ratio to the eight-wavefront one.  The 256x256 tiles of this
+// file win once they fill the chip, their k-loop being the better one (N 24576, K 4096, M 8240: 1480 us against 1640 for
+// 256x256 built like the small ones); below, the smaller ones.
+struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[3]; };
+struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
+constexpr int LONG_K = 1024;
 const TileShape tile_shapes[] = {
-    { 1, 256, 256, 1, 0.00, 10.78, 1.424, 0.000},
-    { 4, 256, 256, 1, 0.00, 5.33, 1.446, 0.000},
-    {11,  32,  16, 3, 0.00, 0.40, 0.132, 0.105},
-    {12,  32,  32, 2, 0.00, 0.68, 0.142, 0.123},
-    {13,  32, 128, 2, 2.01, 0.00, 0.313, 0.274},
-    {14,  32,  64, 2, 2.40, 0.00, 0.000, 0.171},
-    {15,  64,  32, 2, 0.00, 0.00, 0.000, 0.208},
-    {16,  64,  64, 2, 0.52, 0.63, 0.257, 0.257},
-    {17,  64, 128, 2, 0.91, 1.48, 0.413, 0.362},
-    {18, 128, 128, 1, 0.00, 4.24, 0.512, 0.000},
-    {19, 128, 256, 1, 0.00, 7.75, 0.797, 0.000},
-    {20, 256, 128, 1, 0.00, 8.71, 0.748, 0.000},
+    { 1, 256, 256, 1, {0.00, 10.78, 1.424, 0.000, {0.00, 0.00, 0.00}}, {0.30, 0.00, 1.590, 0.000, {5.86, 18.25, 22.79}}},
+    { 4, 256, 256, 1, {0.00,  5.33, 1.446, 0.000, {0.00, 0.00, 0.00}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
+    {11,  32,  16, 3, {0.00,  0.40, 0.132, 0.105, {0.00, 0.00, 0.00}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
+    {12,  32,  32, 2, {0.00,  0.68, 0.142, 0.123, {0.00, 0.00, 0.00}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
+    {13,  32, 128, 2, {2.01,  0.00, 0.313, 0.274, {0.00, 0.00, 0.00}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
+    {14,  32,  64, 2, {2.40,  0.00, 0.000, 0.171, {0.00, 0.00, 0.00}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
+    {15,  64,  32, 2, {0.00,  0.00, 0.000, 0.208, {0.00, 0.00, 0.00}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
+    {16,  64,  64, 2, {0.52,  0.63, 0.257, 0.257, {0.00, 0.00, 0.00}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
+    {17,  64, 128, 2, {0.91,  1.48, 0.413, 0.362, {0.00, 0.00, 0.00}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
+    {18, 128, 128, 1, {0.00,  4.24, 0.512, 0.000, {0.00, 0.00, 0.00}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
+    {19, 128, 256, 1, {0.00,  7.75, 0.797, 0.000, {0.00, 0.00, 0.00}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
+    {20, 256, 128, 1, {0.00,  8.71, 0.748, 0.000, {0.00, 0.00, 0.00}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
 };
 
-double tile_time(const TileShape& sh, int cus, int M, int Nout, int K) {
+double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
+    const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
+    const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 :
+                                epilogue == EPI_RESIDUAL || epilogue == EPI_STORE_F32 ? 2 : 0];
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
     double per = (double)tiles / cus;
     if (per < 8.0) per = (double)((tiles + cus - 1) / cus);
     const double kt = K / 64;
     const double full = (double)(long long)(per / sh.per_cu), rest = per - full * sh.per_cu;
-    auto round_us = [&](double n) { return sh.fixed_us + kt * (n * sh.share_us > sh.step_us ? n * sh.share_us : sh.step_us); };
-    return sh.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
+    auto round_us = [&](double n) {
+        return c.fixed_us + n * epi + kt * (n * c.share_us > c.step_us ? n * c.share_us : c.step_us);
+    };
+    return c.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
 }
 
 bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
@@ -766,7 +782,7 @@ int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double*
     int v = 0;
     for (const TileShape& sh : tile_shapes) {
         if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
-        const double t = tile_time(sh, cus, M, Nout, K);
+        const double t = tile_time(sh, cus, M, Nout, K, epilogue);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
     }
     return v;
@@ -892,8 +908,8 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
     int parts = 0;
     for (const TileShape& sh : tile_shapes) {
         if (!tile_usable(sh, Nout, epilogue)) continue;
-        if (sh.variant == v1) { t += tile_time(sh, device_cus(), m1, Nout, K); ++parts; }
-        if (m1 < M && sh.variant == v2) { t += tile_time(sh, device_cus(), M - m1, Nout, K); ++parts; }
+        if (sh.variant == v1) { t += tile_time(sh, device_cus(), m1, Nout, K, epilogue); ++parts; }
+        if (m1 < M && sh.variant == v2) { t += tile_time(sh, device_cus(), M - m1, Nout, K, epilogue); ++parts; }
     }
     if (parts != (m1 < M ? 2 : 1)) return RADIX_ERR_UNSUPPORTED;
     *us = t;
