@@ -686,7 +686,8 @@ int device_cus() {
 template <int DT>
 int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out, int variant,
               const QkvEpilogue& qe, const ARowMap& amap, const NormFusion& nf, hipStream_t stream) {
-    // Tile choice for launches with a folded norm (the others: plan_gemm): workgroups run one per CU in rounds, a round costs a fixed part
+    // Tile choice for launches with a folded norm (the others: plan_gemm): workgroups run one per CU in rounds, a round
+    // costs a fixed part
     // (launch, first loads, epilogue) plus the k-tiles at the rate measured for that shape (microseconds per
     // 32-wide k-tile on MI355X, random fp16 operands): a launch that does not fill its last round pays for it
     // in full, which is what decides between the shapes for small M * Nout.  Eight wavefronts (two per SIMD,
@@ -729,9 +730,10 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 // of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about (fits there even end
 // with zeros for some):
 //   long_k, K >= 1024: 240 launches of the four projections of the 0.6B, 4B and 8B shapes, M 8 .. 8240, weights from HBM.  Over
-//     29 products of six shapes at 25 row counts from 1 to 130000 they are within 15 % of a launch, and the tile they pick
-//     takes 0.8 % longer than the best one (a tenth of the launches more than 2 %, the worst 21 %).
-//   short_k: 24 products of K 64 .. 768 at the same row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
+//     30 products (N 384 .. 151936, K 1024 .. 17408) at 25 row counts from 1 to 130000 they are within 13 % of a launch (tiles
+//     within 2 of the best), and the tile they pick takes 0.8 % longer than the best one (a tenth of them more than 2 %, the
+//     worst 21 %).
+//   short_k: 23 products of K 64 .. 768 at the same row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
 //     takes 2.4 % (K 64 and 128), 1.3 % (256 to 384) and 0.7 % (512 to 768) longer than the best, where long_k's pick took 13,
 //     10 and 6 %; bf16 operands, not in the fit, 2.7, 1.2 and 0.7 %.
 // The four-wavefront 256x256 tile is entered in short_k by its ratio to the eight-wavefront one.  The 256x256 tiles of this

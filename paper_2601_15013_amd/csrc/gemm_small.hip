@@ -15,7 +15,9 @@
 // issues it: the smallest tiles spread them over the most CUs (32x16 with two wavefronts: three loads each).  The
 // epilogue goes through LDS as fp32, from where every thread takes whole 16-byte pieces of a row.
 //
-// us per launch, fp16, weights from HBM, best 128-row tile of gemm_mfma.hip -> this kernel:
+// us per launch, fp16, best 128-row tile of gemm_mfma.hip -> this kernel, in a loop over one product whose weights come from
+// HBM (the same launches inside a forward of one prompt, by the kernel trace: q|k|v 26.4 -> 10.8, mean of O and down
+// 22.2 -> 7.0, gate/up 12.1 -> 7.3):
 //   M 21:   N 4096 K 1024 (q|k|v) 21.6 -> 7.1, N 1024 K 2048 14.0 -> 5.4, N 6144 K 1024 (gate/up) 11.0 -> 6.2,
 //           N 1024 K 3072 19.4 -> 6.8, N 4096 K 12288 96 -> 25
 //   M 1072: N 1024 K 2048 19.7 -> 13.8, N 1024 K 3072 27.3 -> 18.7, N 4096 K 12288 169 -> 141
