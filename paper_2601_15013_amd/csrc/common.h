@@ -48,7 +48,8 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return
 
 // 16-bit MFMA operand types: v_mfma_f32_32x32x16_{bf16,f16}.  Lane (r = lane % 32, g = lane / 32)
 // supplies 8 consecutive k of row r (k-group g) for both operands; accumulator register e of the
-// 32x32 result is row 8 (e / 4) + 4 g + e % 4, column r.
+// 32x32 result is row 8 (e / 4) + 4 g + e % 4, column r.  v_mfma_f32_16x16x32_{bf16,f16} (mfma16): lane (r = lane % 16,
+// g = lane / 16) supplies 8 consecutive k of row r (k-group g); register e of the 16x16 result is row 4 g + e, column r.
 template <int DT> struct Op;
 template <> struct Op<RADIX_BF16> {
     typedef bf16_t T;
@@ -57,6 +58,9 @@ template <> struct Op<RADIX_BF16> {
     static __device__ __forceinline__ f32x16 mfma(V8 a, V8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ f32x4 mfma16(V8 a, V8 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
 };
 template <> struct Op<RADIX_F16> {
     typedef f16_t T;
@@ -64,6 +68,9 @@ template <> struct Op<RADIX_F16> {
     typedef f16x4 V4;
     static __device__ __forceinline__ f32x16 mfma(V8 a, V8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma16(V8 a, V8 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
     }
 };
 

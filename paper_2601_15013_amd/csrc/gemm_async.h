@@ -34,4 +34,10 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
+// k-tile of the GEMM kernels: 128 bytes = a whole cache line = 8 chunks of 16 bytes per operand row, in LDS too.
+constexpr int GEMM_BK = 64;
+// LDS chunk c of a tile row holds chunk c ^ gemm_swz(row): two rows span the 64 banks, so XORing the chunk index with bits
+// 1..3 of the row sends 16 consecutive rows of one chunk column to 16 distinct 16-byte bank groups.
+__device__ __forceinline__ int gemm_swz(int row) { return (row >> 1) & 7; }
+
 }  // namespace

@@ -4,26 +4,33 @@
 // These are the position-wise contractions of the method - Q/K/V and O projections and the
 // SwiGLU MLP (paper: Background Eq. 5; Algorithm 1 "QKVProj", "OProj", "MLP") - run on the
 // compact row count M = N' (or M = N in the no-dedup baseline).  Both operands are K-contiguous
-// ("NT" GEMM), which is exactly the per-lane operand layout of v_mfma_f32_32x32x16_{bf16,f16}:
-// lane (r = lane % 32, g = lane / 32) supplies 8 consecutive k of row r for k-group g.
+// ("NT" GEMM), which is exactly the per-lane operand layout of v_mfma_f32_16x16x32_{bf16,f16}:
+// lane (r = lane % 16, g = lane / 16) supplies 8 consecutive k of row r for k-group g.
+//
+// What bounds it is chip power: with random operands the matrix pipe alone, fed from registers, holds 1.66 PFLOP/s with
+// v_mfma_f32_32x32x16 and 1.91 with v_mfma_f32_16x16x32 (2.48 and 2.44 with all-zero operands: the clock falls with
+// switching power, and the smaller instruction reads and writes half as many accumulators per product).  The same loads and
+// LDS reads in a loop of 32x32x16 took 7119 us for M 44032, N 24576, K 4096 (1.25 PFLOP/s), this one takes 6250 to 6360
+// (1.40); K 12288, N 4096: 3714 -> 3160.  Without its global loads the loop would take 5220 of 6550 us, without its LDS
+// reads 6150 (zero operands: 4330 and 5210 of 4860).
 //
 // Structure
-//   * Workgroup tile BM x BN, k-tile 32, 4 or 8 wavefronts (one or two per SIMD) in a WAVES_M x WAVES_N
-//     grid; each wavefront owns (BM/WAVES_M) x (BN/WAVES_N) outputs as 32x32 MFMA accumulators.
+//   * Workgroup tile BM x BN, k-tile 64, 4 or 8 wavefronts (one or two per SIMD) in a WAVES_M x WAVES_N
+//     grid; each wavefront owns (BM/WAVES_M) x (BN/WAVES_N) outputs as 16x16 MFMA accumulators.
 //   * The product is formed transposed, C^T = W * A^T (weights are the MFMA "A" operand), so a
-//     lane owns one output ROW and 4 consecutive columns per register quad: the fp32 epilogues
+//     lane owns one output ROW and 4 consecutive columns per block: the fp32 epilogues
 //     (residual read-modify-write, plain fp32 store) access 16 bytes per lane straight from that
 //     layout, the 16-bit ones transpose through LDS and store whole 256-byte row segments.
 //   * Global -> LDS goes through global_load_lds_dwordx4 (no VGPR staging): a wavefront fills
 //     1 KB of LDS per instruction, lane L landing at byte 16 L; the XOR swizzle that keeps the
 //     fragment reads bank-conflict free is therefore applied to the GLOBAL address each lane
-//     fetches.  K-tiles travel in pairs through a ring of five or six LDS stages (the two 64-byte
-//     halves of a 128-byte line are requested back to back), one barrier per pair, loads spread
-//     one per MFMA slice over the pair; details at the main loop.  The
+//     fetches.  A k-tile row is a whole 128-byte line: loads alone, in this tile order, reach 22 to 24 TB/s that way
+//     (14.7 in half lines, 18.6 with the two halves requested back to back).  The
 //     load is issued from inline assembly: issued through the compiler builtin, the compiler's
 //     wait-count pass makes every later LDS read wait for ALL loads in flight (it cannot prove
-//     that the reads of one stage do not alias the fills of the others), which serialises the
+//     that the reads of one slot do not alias the fills of the others), which serialises the
 //     pipeline.  The only vector-memory waits are the explicit ones in front of the barriers.
+//   * LDS holds three k-tiles of A and two of W (all 160 KB for 256x256), one barrier per k-tile; details at the loop.
 //   * K is consumed in order and there is no split-K, so an output element is reduced in the
 //     same order wherever its row sits in the matrix: the deduplicated and the no-dedup pass
 //     give bit-identical rows.
@@ -31,19 +38,12 @@
 //   * Workgroups are numbered so that the 8 XCDs (round-robin dispatch) each work on a compact
 //     band of row tiles, sweeping the weight tiles in step with the other XCDs (details at the tile
 //     assignment), which keeps an XCD's L2 on few A rows and the shared memory-side cache on few W rows.
+#include <type_traits>
+
 #include "gemm_async.h"
 #include "kernels.h"
 
 namespace {
-
-constexpr int BK = 32;            // k-tile: 64 bytes = 4 chunks of 16 bytes per row
-
-// LDS slot (in 16-byte units) of chunk c of tile row `row`.  Rows are 4 chunks (64 bytes), so rows
-// r, r+4, r+8, r+12 start in the same 64-byte window of the 256-byte bank line; XORing the chunk
-// index with bits 2..3 of the row sends the 16 lanes that a ds_read_b128 serves per cycle (16
-// consecutive rows of one chunk column) to 16 distinct 16-byte bank groups.
-__device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
-__device__ __forceinline__ int slot(int row, int c) { return row * 4 + (c ^ swz(row)); }
 
 template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const typename Op<DT>::T* __restrict__ A,
@@ -57,24 +57,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     constexpr int NW = WAVES_M * WAVES_N;                      // wavefronts: 4 (one per SIMD) or 8 (two per SIMD)
     static_assert(NW == 4 || NW == 8, "4 or 8 wavefronts");
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
-    constexpr int MB = WTM / 32, NB = WTN / 32;
-    constexpr int A_LOADS = BM / (16 * NW), B_LOADS = BN / (16 * NW);   // 1 KB wave-loads per wavefront per k-tile
-    constexpr int LOADS = A_LOADS + B_LOADS;
-    constexpr int STAGE = (BM + BN) * 4;                       // 16-byte slots per stage
+    constexpr int MB = WTM / 16, NB = WTN / 16;
+    constexpr int A_LOADS = BM / (8 * NW), B_LOADS = BN / (8 * NW);     // 1 KB wave-loads per wavefront per k-tile
+    constexpr uint32_t A_SLOT = BM * GEMM_BK * 2, B_SLOT = BN * GEMM_BK * 2;
     constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_SPLIT;
     constexpr bool ROPE = EPI == EPI_QKV_ROPE || EPI == EPI_QKV_ROPE_SPLIT;
     constexpr int PARTS = (EPI == EPI_SWIGLU_SPLIT || EPI == EPI_QKV_ROPE_SPLIT) ? 2 : 1;     // (hi, lo) halves of the output row
-    static_assert(!SWIGLU || (NB % 2 == 0), "SwiGLU needs gate/up block pairs in one wavefront");
+    static_assert(!SWIGLU || (NB % 4 == 0), "SwiGLU needs gate/up block pairs of 32 columns in one wavefront");
     static_assert(!ROPE || WTN == 128, "Q/K-norm + RoPE epilogue: one wavefront = one 128-wide head");
     static_assert(EPI != EPI_RESIDUAL_NORM || WTN == 128, "sum-of-squares slots are 128 columns = one wavefront");
-    static_assert(LOADS * 2 + A_LOADS * 2 < 64, "vmcnt range");
+    static_assert(MB % 4 == 0 && (NB == 4 || NB == 8), "passes of 64 rows, k-step slices");
 
     constexpr int EPI_PITCH = 272;                             // epilogue row pitch in bytes (256 + 16 pad)
-    constexpr int EPI_SLOTS = NW * 64 * EPI_PITCH / 16;        // 64 rows per wavefront
-    // ring of k-tile stages: six where they fit the 160 KB of LDS (the smaller tiles), else five
-    constexpr int NS = (6 * STAGE * 16 <= 160 * 1024) ? 6 : 5;
-    constexpr int LDS_SLOTS = NS * STAGE > EPI_SLOTS ? NS * STAGE : EPI_SLOTS;
-    __shared__ uint4 lds_all[LDS_SLOTS];
+    constexpr uint32_t EPI_B = NW * 64 * EPI_PITCH;            // 64 rows per wavefront
+    constexpr uint32_t RING_B = 3 * A_SLOT + 2 * B_SLOT;       // 256x256: all 160 KB of a CU
+    __shared__ __attribute__((aligned(16))) char lds_all[RING_B > EPI_B ? RING_B : EPI_B];
 
     // ---- tile assignment (gemm_tile_of: XCD-aware bands of row tiles sweeping the column tiles)
     const GemmTile tile = gemm_tile_of((int)blockIdx.x, tiles_m, tiles_n, BAND);
@@ -84,21 +81,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-    const int r = lane & 31, g = lane >> 5;
+    const int r = lane & 15, g = lane >> 4;                     // operand row and k-group of a 16x16 block
 
     // ---- global-load assignment.  Wave-load j of this wavefront fills tile rows
-    // [16 (wave + NW j), +16): lane L -> row + L / 4, LDS chunk L % 4, global chunk (L % 4) ^ swz(row).
+    // [8 (wave + NW j), +8): lane L -> row + L / 8, LDS chunk L % 8, global chunk (L % 8) ^ swizzle.
     // Addresses are (uniform 64-bit tile base, advanced per k-tile) + (per-lane 32-bit byte offset).
     // With a row map (amap.rows != nullptr) row m of the product is row amap.rows[m] of A: the gather in front
     // of the output projection rides in these offsets instead of being a copy kernel of its own.  Rows at or
     // past amap.n_valid (padding of a bucketed compact space) take source row 0; entries outside
     // [0, amap.n_src) are clamped and reported.
-    const int lrow = lane >> 2, lpc = lane & 3;
+    const int lrow = lane >> 3, lpc = lane & 7;
     const int m_last = M - 1 - m0;                              // last valid row of this tile (ragged M)
     uint32_t a_off[A_LOADS], w_off[B_LOADS];
 #pragma unroll
     for (int j = 0; j < A_LOADS; ++j) {
-        const int row = 16 * (wave + NW * j) + lrow;
+        const int row = 8 * (wave + NW * j) + lrow;
         int src = row < m_last ? row : m_last;
         if (amap.rows != nullptr) {
             const int m = m0 + src;
@@ -108,26 +105,26 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                 src = src < 0 ? 0 : amap.n_src - 1;
             }
         }
-        a_off[j] = (uint32_t)(((size_t)src * K + 8 * (lpc ^ swz(row))) * sizeof(T));
+        a_off[j] = (uint32_t)(((size_t)src * K + 8 * (lpc ^ gemm_swz(row))) * sizeof(T));
     }
 #pragma unroll
     for (int j = 0; j < B_LOADS; ++j) {
-        const int row = 16 * (wave + NW * j) + lrow;
-        w_off[j] = (uint32_t)(((size_t)row * w_k + 8 * (lpc ^ swz(row))) * sizeof(T));
+        const int row = 8 * (wave + NW * j) + lrow;
+        w_off[j] = (uint32_t)(((size_t)row * w_k + 8 * (lpc ^ gemm_swz(row))) * sizeof(T));
     }
-    const char* a_base = (const char*)(A + (amap.rows != nullptr ? (size_t)0 : (size_t)m0 * K));
-    const char* w_base = (const char*)(W + (size_t)n0 * w_k);
-    const int WKT = w_k / BK;       // k-tiles in a weight row; tiles past it wrap (A = [hi | lo] mode)
+    const char* a_ptr = (const char*)(A + (amap.rows != nullptr ? (size_t)0 : (size_t)m0 * K));    // next k-tile of A to be loaded
+    const char* const w_base = (const char*)(W + (size_t)n0 * w_k);
+    const char* w_ptr = w_base;                                                                  // and of W
+    const int KT = K / GEMM_BK, WKT = w_k / GEMM_BK;
+    int w_left = WKT;               // k-tiles left in the weight rows; past them they start over (A = [hi | lo] mode)
 
-    f32x16 acc[NB][MB];
+    f32x4 acc[NB][MB];
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
-
-    const int KT = K / BK;
+            for (int e = 0; e < 4; ++e) acc[j][i][e] = 0.f;
 
     // EPI_QKV_ROPE: position ids of this lane's rows, fetched before the main loop so that the RoPE
     // table rows can be addressed without a dependent load when the epilogue starts
@@ -135,24 +132,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     if (ROPE) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            int gm = m0 + wm * WTM + i * 32 + r;
+            int gm = m0 + wm * WTM + i * 16 + r;
             gm = gm < M ? gm : M - 1;
             rope_pos[i] = qe.pos_c[gm];
         }
     }
 
-    // RMSNorm folded in (consumer side): the first 16 sum-of-squares slots of every row this lane owns are
+    // RMSNorm folded in (consumer side): the first sum-of-squares slots of every row this lane owns are
     // requested here, ahead of the first tile loads, and added up once those are under way; the row scales
     // then sit in MB registers through the main loop (the epilogue would otherwise start with a chain of
     // dependent loads per tile).
-    constexpr bool CONSUMES_NORM = EPI != EPI_RESIDUAL && EPI != EPI_RESIDUAL_NORM && EPI != EPI_STORE_F32;
-    constexpr int SS_EARLY = 8;                                 // float2 loads per row requested early
+    constexpr bool CONSUMES_NORM = EPI == EPI_STORE || EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
+    constexpr int SS_EARLY = 16 / MB;                           // float2 loads per row requested early
     float2 ssv[MB][SS_EARLY];
     const bool scale_rows = CONSUMES_NORM && nf.ss_in != nullptr;
     if (scale_rows) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
-            int gm = m0 + wm * WTM + i * 32 + r;
+            int gm = m0 + wm * WTM + i * 16 + r;
             gm = gm < M ? gm : M - 1;
             const float* sp = nf.ss_in + (size_t)gm * nf.n_slots_in;
 #pragma unroll
@@ -161,273 +158,168 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         }
     }
 
-    // ---- LDS addressing.  The ring has five stages of STAGE_B bytes; tile t lives in stage t % 5.
-    // Stage byte offsets are wave-uniform scalars that rotate as the loop advances, everything
-    // lane-dependent is computed once: per k-step ks the byte offset of this lane's chunk in tile row
-    // (wave row block) + r; fragment f of the block adds f * 32 rows = f * 2048 bytes.
-    constexpr uint32_t STAGE_B = STAGE * 16;
-    const char* const lds_c = (const char*)lds_all;
+    // ---- LDS: three slots for k-tiles of A, then two for k-tiles of W; tile t lives in A slot t % 3, W slot t % 2
+    // (wave-uniform offsets that rotate as the loop advances).
     const uint32_t lds_base = lds_addr(lds_all);
-    uint32_t a_rd[2], b_rd[2];
+    uint32_t rd[2];                                             // k-step ks: chunk 4 ks + g of row r
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-        a_rd[ks] = (uint32_t)slot(wm * WTM + r, ks * 2 + g) * 16;
-        b_rd[ks] = (uint32_t)(BM * 4 + slot(wn * WTN + r, ks * 2 + g)) * 16;
-    }
+    for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(r * 128 + (((4 * ks + g) ^ gemm_swz(r)) << 4));
+    const char* const a_rd = lds_all + (wm * WTM) * 128;
+    const char* const b_rd = lds_all + 3 * A_SLOT + (wn * WTN) * 128;
+    auto load_a = [&](uint32_t slot, int f) {
+        dma16(a_ptr, a_off[f], lds_base + slot + 1024 * (wave + NW * f));
+        if (f == A_LOADS - 1) a_ptr += GEMM_BK * sizeof(T);
+    };
+    auto load_b = [&](uint32_t slot, int f) {
+        dma16(w_ptr, w_off[f], lds_base + 3 * A_SLOT + slot + 1024 * (wave + NW * f));
+        if (f == B_LOADS - 1) {
+            w_ptr += GEMM_BK * sizeof(T);
+            if (--w_left == 0) { w_left = WKT; w_ptr = w_base; }
+        }
+    };
+    V8 fa0[MB], fa1[MB], fb[NB];                                // A fragments of the two k-steps, W fragments of the running one
+    auto read_a = [&](V8& f, uint32_t slot, int ks, int i) {
+        uint4 v = *reinterpret_cast<const uint4*>(a_rd + slot + rd[ks] + i * 2048);
+        f = *reinterpret_cast<V8*>(&v);
+    };
+    auto read_b = [&](uint32_t slot, int ks, int j) {
+        uint4 v = *reinterpret_cast<const uint4*>(b_rd + slot + rd[ks] + j * 2048);
+        fb[j] = *reinterpret_cast<V8*>(&v);
+    };
 
-    // fragment f of a k-step: f < MB is an activation fragment, else a weight fragment
-#define RADIX_FRAG1(SO, KS, FA, FB, F)                                                                             \
-    do {                                                                                                           \
-        if ((F) < MB) {                                                                                            \
-            uint4 v = *reinterpret_cast<const uint4*>(lds_c + (SO) + a_rd[KS] + (F) * 2048);                       \
-            FA[(F) < MB ? (F) : 0] = *reinterpret_cast<V8*>(&v);                                                   \
-        } else {                                                                                                   \
-            uint4 v = *reinterpret_cast<const uint4*>(lds_c + (SO) + b_rd[KS] + ((F) - MB) * 2048);                \
-            FB[(F) >= MB ? (F) - MB : 0] = *reinterpret_cast<V8*>(&v);                                             \
-        }                                                                                                          \
-    } while (0)
-
-#define RADIX_DMA1(KT_, SO, F)                                                                                     \
-    do {                                                                                                           \
-        if ((F) < A_LOADS)                                                                                         \
-            dma16(a_base + (size_t)(KT_) * (BK * sizeof(T)), a_off[(F) < A_LOADS ? (F) : 0],                       \
-                  lds_base + (SO) + 1024 * (wave + NW * (F)));                                                      \
-        else if ((F) < LOADS)                                                                                      \
-            dma16(w_base + (size_t)((KT_) >= WKT ? (KT_) - WKT : (KT_)) * (BK * sizeof(T)),                        \
-                  w_off[(F) >= A_LOADS && (F) < LOADS ? (F) - A_LOADS : 0],                                        \
-                  lds_base + (SO) + BM * 64 + 1024 * (wave + NW * ((F) - A_LOADS)));                                \
-    } while (0)
-
-    // loads of k-tiles T0 and T0+1, row group by row group: the two 64-byte halves of every 128-byte
-    // line are requested back to back, so the second request merges with the first one's miss in the
-    // vector L1 and the line crosses the L2 fabric once (requested a k-tile apart it crosses twice)
-#define RADIX_ISSUE2(T0, SA, SB)                                                                                   \
-    do {                                                                                                           \
-        const int ka__ = (T0) < KT ? (T0) : KT - 2;                                                                \
-        _Pragma("unroll") for (int f = 0; f < LOADS; ++f) {                                                        \
-            RADIX_DMA1(ka__, SA, f);                                                                               \
-            RADIX_DMA1(ka__ + 1, SB, f);                                                                           \
-        }                                                                                                          \
-    } while (0)
-
-    // MFMAs [lo, hi) of the MB x NB block products of one k-step, in (j, i) order
-#define RADIX_MFMA_RANGE(FA, FB, LO, HI)                                                                           \
-    do {                                                                                                           \
-        _Pragma("unroll") for (int t = (LO); t < (HI); ++t)                                                        \
-            acc[t / MB][t % MB] = Op<DT>::mfma(FB[t / MB], FA[t % MB], acc[t / MB][t % MB]);                       \
-    } while (0)
-
-    // first k-step of the tile in stage CUR: its MFMAs, led by the fragment reads of its second k-step
-#define RADIX_HALF0(CUR)                                                                           \
-        _Pragma("unroll") for (int u = 0; u < UNITS; ++u) {                                        \
-            RADIX_FRAG1(CUR, 1, fa1, fb1, u);                                                      \
-            RADIX_MFMA_RANGE(fa0, fb0, u * HALF / UNITS, (u + 1) * HALF / UNITS);                  \
-            __builtin_amdgcn_sched_barrier(0);                                                     \
-        }                                                                                          \
-        RADIX_MFMA_RANGE(fa0, fb0, HALF, MB * NB);                                                 \
-        __builtin_amdgcn_sched_barrier(0);
-
-    constexpr int UNITS = MB + NB;
-    constexpr int HALF = MB * NB / 2;      // the reads ride on the first half of a k-step's MFMAs
-    static_assert(UNITS >= A_LOADS && UNITS >= B_LOADS, "at most one pair of global->LDS loads per slice");
     // row scales from the sums of squares: slots in increasing order (the early ones, then the rest); adding the
     // zeros that stand in for slots a narrow model does not have changes nothing
     float rsr[MB];
-#define RADIX_ROW_SCALES()                                                                                         \
-    do {                                                                                                           \
-        _Pragma("unroll") for (int i = 0; i < MB; ++i) rsr[i] = 1.0f;                                              \
-        if (scale_rows) {                                                                                          \
-            _Pragma("unroll") for (int i = 0; i < MB; ++i) {                                                       \
-                float ssum = 0.f;                                                                                  \
-                _Pragma("unroll") for (int u = 0; u < SS_EARLY; ++u) { ssum += ssv[i][u].x; ssum += ssv[i][u].y; } \
-                if (nf.n_slots_in > 2 * SS_EARLY) {                                                                \
-                    int gm = m0 + wm * WTM + i * 32 + r;                                                           \
-                    gm = gm < M ? gm : M - 1;                                                                      \
-                    const float* sp = nf.ss_in + (size_t)gm * nf.n_slots_in;                                       \
-                    for (int k0 = 2 * SS_EARLY; k0 < nf.n_slots_in; k0 += 2 * SS_EARLY) {                          \
-                        float2 more[SS_EARLY];                                                                     \
-                        _Pragma("unroll") for (int u = 0; u < SS_EARLY; ++u)                                       \
-                            more[u] = k0 + 2 * u < nf.n_slots_in ? *reinterpret_cast<const float2*>(sp + k0 + 2 * u) \
-                                                                 : make_float2(0.f, 0.f);                          \
-                        _Pragma("unroll") for (int u = 0; u < SS_EARLY; ++u) { ssum += more[u].x; ssum += more[u].y; } \
-                    }                                                                                              \
-                }                                                                                                  \
-                rsr[i] = 1.0f / sqrtf(ssum * nf.inv_d + nf.eps);                                                   \
-            }                                                                                                      \
-        }                                                                                                          \
-    } while (0)
-    V8 fa0[MB], fb0[NB], fa1[MB], fb1[NB];
-    if constexpr (NS == 5) {
-    RADIX_ISSUE2(0, 0u, STAGE_B);
-    {   // activation half of the pair (2, 3); K = 64: tiles 0, 1 again, into stages nobody reads
-        const int ka = 2 < KT ? 2 : KT - 2;
+    auto row_scales = [&]() {
 #pragma unroll
-        for (int f = 0; f < A_LOADS; ++f) {
-            RADIX_DMA1(ka, 2 * STAGE_B, f);
-            RADIX_DMA1(ka + 1, 3 * STAGE_B, f);
-        }
-    }
-    wait_vmcnt<A_LOADS * 2>();
-    __builtin_amdgcn_s_barrier();
+        for (int i = 0; i < MB; ++i) rsr[i] = 1.0f;
+        if (scale_rows) {
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) RADIX_FRAG1(0u, 0, fa0, fb0, u);
-    RADIX_ROW_SCALES();
-
-    // One k-tile = two k-steps of 16, software-pipelined over two fragment register sets and
-    // scheduled by hand (the scheduling barriers pin the order): the first half of a k-step's MFMAs
-    // is cut into UNITS slices, each led by one LDS fragment read for the NEXT k-step; the second half
-    // of the MFMAs then covers the LDS latency of those reads, so the matrix pipe always has queued work.
-    // K-tiles travel in PAIRS (t even, t+1) and their loads are spread thinly over the MFMA stream (a
-    // wavefront that has to wait for room in the memory pipeline cannot issue MFMAs meanwhile):
-    //   * first k-step of the even tile: the WEIGHT rows of the pair (t+2, t+3);
-    //   * between the two k-steps of the odd tile: wait for this wavefront's loads of the pair
-    //     (t+2, t+3), barrier (everybody's share has landed and everybody is done with the pair
-    //     (t, t+1)), then, along the second k-step, the ACTIVATION rows of the pair (t+4, t+5) into
-    //     the stages of tiles t-1 and t.
-    // Pairs past the end re-fetch the last pair into stages nobody reads again: no branch in the body.
-    uint32_t so_e = 0, so_o = STAGE_B, so_n = 2 * STAGE_B, so_n1 = 3 * STAGE_B, so_ra = 4 * STAGE_B;   // t, t+1, t+2, t+3, t+4
-    for (int kt = 0; kt < KT; kt += 2) {
-        const int kw = kt + 2 < KT ? kt + 2 : KT - 2;
+            for (int i = 0; i < MB; ++i) {
+                float ssum = 0.f;
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
+                for (int u = 0; u < SS_EARLY; ++u) { ssum += ssv[i][u].x; ssum += ssv[i][u].y; }
+                if (nf.n_slots_in > 2 * SS_EARLY) {
+                    int gm = m0 + wm * WTM + i * 16 + r;
+                    gm = gm < M ? gm : M - 1;
+                    const float* sp = nf.ss_in + (size_t)gm * nf.n_slots_in;
+                    for (int k0 = 2 * SS_EARLY; k0 < nf.n_slots_in; k0 += 2 * SS_EARLY) {
+                        float2 more[SS_EARLY];
 #pragma unroll
-            for (int dd = 0; dd < 2 * B_LOADS; ++dd)        // load dd: row group dd / 2 of tile t+2 + dd % 2
-                if (dd * UNITS / (2 * B_LOADS) == u) {
-                    if (dd % 2 == 0) RADIX_DMA1(kw, so_n, A_LOADS + dd / 2);
-                    else RADIX_DMA1(kw + 1, so_n1, A_LOADS + dd / 2);
+                        for (int u = 0; u < SS_EARLY; ++u)
+                            more[u] = k0 + 2 * u < nf.n_slots_in ? *reinterpret_cast<const float2*>(sp + k0 + 2 * u)
+                                                                 : make_float2(0.f, 0.f);
+#pragma unroll
+                        for (int u = 0; u < SS_EARLY; ++u) { ssum += more[u].x; ssum += more[u].y; }
+                    }
                 }
-            RADIX_FRAG1(so_e, 1, fa1, fb1, u);
-            RADIX_MFMA_RANGE(fa0, fb0, u * HALF / UNITS, (u + 1) * HALF / UNITS);
-            __builtin_amdgcn_sched_barrier(0);
+                rsr[i] = 1.0f / sqrtf(ssum * nf.inv_d + nf.eps);
+            }
         }
-        RADIX_MFMA_RANGE(fa0, fb0, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            RADIX_FRAG1(so_o, 0, fa0, fb0, u);
-            RADIX_MFMA_RANGE(fa1, fb1, u * HALF / UNITS, (u + 1) * HALF / UNITS);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        RADIX_MFMA_RANGE(fa1, fb1, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
+    };
 
-        RADIX_HALF0(so_o)
-        wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        const int ka = kt + 4 < KT ? kt + 4 : KT - 2;
+    uint32_t a_cur = 0, a_nxt = A_SLOT, a_far = 2 * A_SLOT, b_cur = 0, b_nxt = B_SLOT;     // slots of tiles t, t+1, t+2
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
+    for (int f = 0; f < A_LOADS; ++f) load_a(a_cur, f);
 #pragma unroll
-            for (int dd = 0; dd < 2 * A_LOADS; ++dd)
-                if (dd * UNITS / (2 * A_LOADS) == u) {
-                    if (dd % 2 == 0) RADIX_DMA1(ka, so_ra, dd / 2);
-                    else RADIX_DMA1(ka + 1, so_e, dd / 2);       // tile t+5 goes where tile t was
-                }
-            RADIX_FRAG1(so_n, 0, fa0, fb0, u);
-            RADIX_MFMA_RANGE(fa1, fb1, u * HALF / UNITS, (u + 1) * HALF / UNITS);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        RADIX_MFMA_RANGE(fa1, fb1, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
-
-        // rotate by two stages: t+2 -> t
-        so_e = so_n;
-        so_o = so_n + STAGE_B == 5 * STAGE_B ? 0u : so_n + STAGE_B;
-        so_n = so_o + STAGE_B == 5 * STAGE_B ? 0u : so_o + STAGE_B;
-        so_n1 = so_n + STAGE_B == 5 * STAGE_B ? 0u : so_n + STAGE_B;
-        so_ra = so_n1 + STAGE_B == 5 * STAGE_B ? 0u : so_n1 + STAGE_B;
-    }
+    for (int f = 0; f < B_LOADS; ++f) load_b(b_cur, f);
+    if (KT > 1) {
+#pragma unroll
+        for (int f = 0; f < A_LOADS; ++f) load_a(a_nxt, f);
+#pragma unroll
+        for (int f = 0; f < B_LOADS; ++f) load_b(b_nxt, f);
+        wait_vmcnt<A_LOADS + B_LOADS>();
     } else {
-    // Six stages = three pair slots: the loads of a pair are issued two pair-iterations before they
-    // are waited for (one with five stages), which the short k-tiles of the small workgroup tiles need.
-    // Iteration p (tiles t = 2p, t+1): weight rows of pair p+2 along the first k-step of the even tile;
-    // between the k-steps of the odd tile wait for pair p+1 (pair p+2 may stay in flight), barrier, then
-    // the activation rows of pair p+3 into the stages of pair p.
-    RADIX_ISSUE2(0, 0u, STAGE_B);
-    RADIX_ISSUE2(2, 2 * STAGE_B, 3 * STAGE_B);
-    {
-        const int ka = 4 < KT ? 4 : KT - 2;
-#pragma unroll
-        for (int f = 0; f < A_LOADS; ++f) {
-            RADIX_DMA1(ka, 4 * STAGE_B, f);
-            RADIX_DMA1(ka + 1, 5 * STAGE_B, f);
-        }
+        wait_vmcnt<0>();
     }
-    wait_vmcnt<LOADS * 2 + A_LOADS * 2>();
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) RADIX_FRAG1(0u, 0, fa0, fb0, u);
-    RADIX_ROW_SCALES();
-    uint32_t so_e = 0, so_n = 2 * STAGE_B, so_w = 4 * STAGE_B;      // stages of t, t+2, t+4 (pairs are adjacent)
-    for (int kt = 0; kt < KT; kt += 2) {
-        const int kw = kt + 4 < KT ? kt + 4 : KT - 2;
+    for (int i = 0; i < MB; ++i) read_a(fa0[i], a_cur, 0, i);
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
+    for (int j = 0; j < NB - 1; ++j) read_b(b_cur, 0, j);
+    row_scales();
+
+    // One k-tile = two k-steps of 32, each of NB slices (the scheduling barriers pin the order): slice j multiplies W
+    // fragment j with the MB fragments of A.  W fragments are reloaded in place for the next k-step, one slice after
+    // their use; A fragments alternate between two sets.  What is read from LDS in a slice is used NB - 1 slices later.
+    // Global loads, two per slice: A of tile t+2 from the start of the first k-step, into the slot of tile t-1; W of tile
+    // t+2 in the second, into the slot of tile t, right after the barrier that says that every wavefront has read tile t
+    // and has tile t+1 in LDS (spread over the k-step they land too late for the next barrier: 2 to 4 % with zero operands).
+    // Every other slice runs its blocks backwards, so that two MFMAs in a row always share an operand: less switching
+    // (registers only: 1.99 -> 2.04 PFLOP/s).
+    // MODE 2: tile t+2 exists; 1: only tile t+1; 0: the last tile.
+    constexpr int BAR = NB >= 8 ? 2 : 1;                        // the barrier stands ahead of this slice
+    auto k_tile = [&](auto mode_c) {
+        constexpr int MODE = decltype(mode_c)::value;
 #pragma unroll
-            for (int dd = 0; dd < 2 * B_LOADS; ++dd)
-                if (dd * UNITS / (2 * B_LOADS) == u) {
-                    if (dd % 2 == 0) RADIX_DMA1(kw, so_w, A_LOADS + dd / 2);
-                    else RADIX_DMA1(kw + 1, so_w + STAGE_B, A_LOADS + dd / 2);
+        for (int j = 0; j < NB; ++j) {
+            if (MODE == 2) {
+#pragma unroll
+                for (int f = 0; f < A_LOADS; ++f)
+                    if (f / 2 == j) load_a(a_far, f);
+            }
+            if (j == 0) read_b(b_cur, 0, NB - 1);
+            else read_b(b_cur, 1, j - 1);
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+                if (1 + i * (NB - 2) / MB == j) read_a(fa1[i], a_cur, 1, i);
+#pragma unroll
+            for (int u = 0; u < MB; ++u) {
+                const int i = j & 1 ? MB - 1 - u : u;
+                acc[j][i] = Op<DT>::mfma16(fb[j], fa0[i], acc[j][i]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            if (MODE > 0 && j == BAR) {
+                wait_vmcnt_and_lds<MODE == 2 ? A_LOADS : 0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            if (MODE == 2 && j >= BAR) {
+#pragma unroll
+                for (int f = 0; f < B_LOADS; ++f)
+                    if (BAR + f / 2 == j) load_b(b_cur, f);
+            }
+            if (j == 0) read_b(b_cur, 1, NB - 1);
+            if (MODE > 0 && j >= BAR) {
+                if (j == BAR) {
+#pragma unroll
+                    for (int u = 0; u < BAR; ++u) read_b(b_nxt, 0, u);
+                } else {
+                    read_b(b_nxt, 0, j - 1);
                 }
-            RADIX_FRAG1(so_e, 1, fa1, fb1, u);
-            RADIX_MFMA_RANGE(fa0, fb0, u * HALF / UNITS, (u + 1) * HALF / UNITS);
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+                    if (BAR + i * (NB - BAR) / MB == j) read_a(fa0[i], a_nxt, 0, i);
+            }
+#pragma unroll
+            for (int u = 0; u < MB; ++u) {
+                const int i = j & 1 ? MB - 1 - u : u;
+                acc[j][i] = Op<DT>::mfma16(fb[j], fa1[i], acc[j][i]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        RADIX_MFMA_RANGE(fa0, fb0, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            RADIX_FRAG1(so_e + STAGE_B, 0, fa0, fb0, u);
-            RADIX_MFMA_RANGE(fa1, fb1, u * HALF / UNITS, (u + 1) * HALF / UNITS);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        RADIX_MFMA_RANGE(fa1, fb1, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
+        const uint32_t a_t = a_cur, b_t = b_cur;
+        a_cur = a_nxt; a_nxt = a_far; a_far = a_t;
+        b_cur = b_nxt; b_nxt = b_t;
+    };
+    for (int t = 0; t + 2 < KT; ++t) k_tile(std::integral_constant<int, 2>());
+    if (KT > 1) k_tile(std::integral_constant<int, 1>());
+    k_tile(std::integral_constant<int, 0>());
+    __builtin_amdgcn_s_barrier();     // every load has landed (the last waits were for all of them); wait until every
+                                      // wavefront is done with the slots
+    asm volatile("" ::: "memory");
 
-        RADIX_HALF0(so_e + STAGE_B)
-        // the fragment reads just issued come from a stage that other wavefronts refill right after the
-        // barrier (activation rows of pair p+3): they must have returned before this wavefront passes it
-        wait_vmcnt_and_lds<LOADS * 2>();
-        __builtin_amdgcn_s_barrier();
-        const int ka = kt + 6 < KT ? kt + 6 : KT - 2;
-#pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-#pragma unroll
-            for (int dd = 0; dd < 2 * A_LOADS; ++dd)
-                if (dd * UNITS / (2 * A_LOADS) == u) {
-                    if (dd % 2 == 0) RADIX_DMA1(ka, so_e, dd / 2);
-                    else RADIX_DMA1(ka + 1, so_e + STAGE_B, dd / 2);
-                }
-            RADIX_FRAG1(so_n, 0, fa0, fb0, u);
-            RADIX_MFMA_RANGE(fa1, fb1, u * HALF / UNITS, (u + 1) * HALF / UNITS);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        RADIX_MFMA_RANGE(fa1, fb1, HALF, MB * NB);
-        __builtin_amdgcn_sched_barrier(0);
-
-        // rotate by one pair slot
-        so_e = so_n;
-        so_n = so_w;
-        so_w = so_w + 2 * STAGE_B == 6 * STAGE_B ? 0u : so_w + 2 * STAGE_B;
-    }
-    }
-#undef RADIX_ROW_SCALES
-#undef RADIX_HALF0
-#undef RADIX_ISSUE2
-#undef RADIX_MFMA_RANGE
-#undef RADIX_DMA1
-#undef RADIX_FRAG1
-    wait_vmcnt<0>();                  // drain the tail loads ...
-    __builtin_amdgcn_s_barrier();     // ... and wait until every wavefront is done with the stages
-
-    // ---- epilogue.  acc[j][i] register e holds output row 32 i + r, column 32 j + 8 (e/4) + 4 g + e%4
+    // ---- epilogue.  acc[j][i] register e holds output row 16 i + r, column 16 j + 4 g + e
     // of this wavefront's block: a lane owns a ROW.  To write full 128-byte lines the block goes
     // through LDS in passes of 64 rows: every lane drops its row pieces into a padded row-major
     // buffer private to its wavefront (row pitch 272 bytes), then the wavefront reads the buffer back
     // 16 bytes per lane, 16 lanes per 256-byte row, and does the global access from that layout.
     constexpr int PITCH = EPI_PITCH;
-    char* const ebuf = (char*)lds_all + wave * (64 * PITCH);
-    static_assert(MB % 2 == 0 && NB % 2 == 0, "passes of 64 rows / 64 columns");
+    char* const ebuf = lds_all + wave * (64 * PITCH);
 
     // The epilogue derives all its addresses from a lane id the compiler cannot see through, so that
     // none of that arithmetic is hoisted above the main loop, where every vector register counts.
@@ -435,86 +327,94 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     asm volatile("" : "+v"(lane_opaque));
     {
     const int lane = lane_opaque;
-    const int r = lane & 31, g = lane >> 5;
+    const int r = lane & 15, g = lane >> 4;
 
 #define RADIX_ACC(J, I, E) (acc[J][I][E] * rsr[I])
 
     if (EPI == EPI_RESIDUAL_NORM) {
         // fp32 read-modify-write of the residual stream as below, plus, per row: the updated values times the
         // gain of the norm that follows, in the operand type (what the next projection multiplies), and the
-        // sum of their squares over this wavefront's 128 columns (in-lane in (j, q, t) order, then the partner
-        // lane that holds the other half of the row's columns).  The loads of a row block are all issued before
+        // sum of their squares over this wavefront's 128 columns (in-lane in column order, then the three other
+        // lanes of the row).  The loads of a row block are all issued before
         // anything of the block before it is stored: written in that order by hand, because with three
         // unrelated pointers in play the compiler may not move a load above a store on its own, and every
         // (load, add, store) step would then pay the memory latency in turn.
         const int slot = (n0 + wn * WTN) >> 7, n_slots = Nout >> 7;
         const float* grow = nf.gain + n0 + wn * WTN;
-        f32x4 gn[NB * 4];
+        f32x4 gn[NB];
 #pragma unroll
-        for (int jq = 0; jq < NB * 4; ++jq)
-            gn[jq] = *reinterpret_cast<const f32x4*>(grow + (jq >> 2) * 32 + 8 * (jq & 3) + 4 * g);
-        f32x4 cur[NB * 4], nxt[NB * 4];
+        for (int j = 0; j < NB; ++j) gn[j] = *reinterpret_cast<const f32x4*>(grow + 16 * j + 4 * g);
+        f32x4 cur[NB], nxt[NB];
         auto load_block = [&](int i, f32x4* v) {
-            const int gm = m0 + wm * WTM + i * 32 + r;
+            const int gm = m0 + wm * WTM + i * 16 + r;
             const float* orow = (const float*)out_ + (size_t)(gm < M ? gm : M - 1) * Nout + n0 + wn * WTN;
 #pragma unroll
-            for (int jq = 0; jq < NB * 4; ++jq)
-                v[jq] = *reinterpret_cast<const f32x4*>(orow + (jq >> 2) * 32 + 8 * (jq & 3) + 4 * g);
+            for (int j = 0; j < NB; ++j) v[j] = *reinterpret_cast<const f32x4*>(orow + 16 * j + 4 * g);
         };
         load_block(0, cur);
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
             if (i + 1 < MB) load_block(i + 1 < MB ? i + 1 : 0, nxt);
-            const int gm = m0 + wm * WTM + i * 32 + r;
-            const bool live = gm < M;                              // both lanes of a row agree
+            const int gm = m0 + wm * WTM + i * 16 + r;
+            const bool live = gm < M;                              // all lanes of a row agree
             float* orow = (float*)out_ + (size_t)(live ? gm : M - 1) * Nout + n0 + wn * WTN;
             T* arow = (T*)nf.a16 + (size_t)(live ? gm : M - 1) * Nout + n0 + wn * WTN;
             float ss = 0.f;
 #pragma unroll
-            for (int jq = 0; jq < NB * 4; ++jq) {
-                const int c = (jq >> 2) * 32 + 8 * (jq & 3) + 4 * g;
-                f32x4 v = cur[jq];
+            for (int j = 0; j < NB; ++j) {
+                const int c = 16 * j + 4 * g;
+                f32x4 v = cur[j];
                 V4 a;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    v[t] += acc[jq >> 2][i][(jq & 3) * 4 + t];
+                    v[t] += acc[j][i][t];
                     ss += v[t] * v[t];
-                    a[t] = (T)(v[t] * gn[jq][t]);
+                    a[t] = (T)(v[t] * gn[j][t]);
                 }
                 if (live) {
                     *reinterpret_cast<f32x4*>(orow + c) = v;
                     *reinterpret_cast<V4*>(arow + c) = a;
                 }
             }
+            ss += __shfl_xor(ss, 16, 64);
             ss += __shfl_xor(ss, 32, 64);
             if (live && g == 0) nf.ss_out[(size_t)gm * n_slots + slot] = ss;
 #pragma unroll
-            for (int jq = 0; jq < NB * 4; ++jq) cur[jq] = nxt[jq];
+            for (int j = 0; j < NB; ++j) cur[j] = nxt[j];
         }
     } else if (EPI == EPI_RESIDUAL || EPI == EPI_STORE_F32) {
         // fp32 read-modify-write of the residual stream (or a plain fp32 store) straight from the accumulator layout: per
-        // instruction 32 rows x 32 contiguous bytes; all loads of a row block are issued before its
+        // instruction 16 rows x 64 contiguous bytes; the loads of two row blocks are issued before their
         // stores, and nothing has to be converted, so the LDS detour does not pay here.
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            const int gm = m0 + wm * WTM + i * 32 + r;
-            if (gm >= M) continue;
-            float* orow = (float*)out_ + (size_t)gm * Nout + n0 + wn * WTN;
+        for (int ip = 0; ip < MB; ip += 2) {
+            f32x4 v[2][NB];
+            float* orow[2];
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
+            for (int il = 0; il < 2; ++il) {
+                const int gm = m0 + wm * WTM + (ip + il) * 16 + r;
+                orow[il] = (float*)out_ + (size_t)(gm < M ? gm : M - 1) * Nout + n0 + wn * WTN + 4 * g;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    f32x4* p = reinterpret_cast<f32x4*>(orow + j * 32 + 8 * q + 4 * g);
-                    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                    if (EPI == EPI_RESIDUAL) v = *p;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) v[t] += acc[j][i][q * 4 + t];
-                    *p = v;
+                for (int j = 0; j < NB; ++j) {
+                    v[il][j] = {0.f, 0.f, 0.f, 0.f};
+                    if (EPI == EPI_RESIDUAL) v[il][j] = *reinterpret_cast<const f32x4*>(orow[il] + 16 * j);
                 }
+            }
+#pragma unroll
+            for (int il = 0; il < 2; ++il) {
+                const int gm = m0 + wm * WTM + (ip + il) * 16 + r;
+                if (gm >= M) continue;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[il][j][t] += acc[j][ip + il][t];
+                    *reinterpret_cast<f32x4*>(orow[il] + 16 * j) = v[il][j];
+                }
+            }
         }
     } else {
         // 16-bit outputs.  EPI_STORE: 128 output columns per wavefront row (256 bytes);
-        // EPI_SWIGLU: gate block j / up block j+1 pairs -> 64 output columns per row (128 bytes);
+        // EPI_SWIGLU: gate blocks j, j+1 and up blocks j+2, j+3 -> 64 output columns per row (128 bytes);
         // EPI_SWIGLU_SPLIT: the same twice, the rounded value into the left half of the output row and what
         // the rounding dropped into the right half (the down projection then runs over the doubled K).
         constexpr int OUT_COLS = SWIGLU ? WTN / 2 : WTN;
@@ -529,33 +429,32 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         const bool rope_head = ROPE && head < qe.n_q_heads + qe.n_kv_heads;
         const float* rope_gain = (ROPE && head >= qe.n_q_heads) ? qe.gk : qe.gq;
 #pragma unroll
-        for (int ip = 0; ip < MB; ip += 2) {
+        for (int ip = 0; ip < MB; ip += 4) {
 #pragma unroll
           for (int part = 0; part < PARTS; ++part) {
 #pragma unroll
-            for (int il = 0; il < 2; ++il) {
-                char* rowp = ebuf + (il * 32 + r) * PITCH;
+            for (int il = 0; il < 4; ++il) {
+                char* rowp = ebuf + (il * 16 + r) * PITCH;
                 if (SWIGLU) {
 #pragma unroll
-                    for (int j = 0; j < NB; j += 2)
+                    for (int j = 0; j < NB; ++j) {
+                        if (j & 2) continue;                       // an up block
+                        V4 v;
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            V4 v;
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const float gt = RADIX_ACC(j, ip + il, q * 4 + t), up = RADIX_ACC(j + 1, ip + il, q * 4 + t);
-                                // silu(g) * u with the hardware reciprocal (1 ulp) instead of an IEEE division
-                                const float y = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-                                const T hi = (T)y;
-                                v[t] = part == 0 ? hi : (T)(y - (float)hi);
-                            }
-                            *reinterpret_cast<V4*>(rowp + ((j >> 1) * 32 + 8 * q + 4 * g) * 2) = v;
+                        for (int t = 0; t < 4; ++t) {
+                            const float gt = RADIX_ACC(j, ip + il, t), up = RADIX_ACC(j + 2 < NB ? j + 2 : 0, ip + il, t);
+                            // silu(g) * u with the hardware reciprocal (1 ulp) instead of an IEEE division
+                            const float y = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
+                            const T hi = (T)y;
+                            v[t] = part == 0 ? hi : (T)(y - (float)hi);
                         }
+                        *reinterpret_cast<V4*>(rowp + (((j >> 2) * 2 + (j & 1)) * 16 + 4 * g) * 2) = v;
+                    }
                 } else if (ROPE && rope_head) {
                     // This wavefront's 128 columns are exactly one q or k head of the fused q|k|v row and
-                    // a lane owns a row: the per-head RMSNorm is an in-lane sum of 64 squares plus one
-                    // exchange with lane ^ 32, and the rotary partner of column c < 64 (block j) is
-                    // column c + 64 (block j + 2) of the same lane and register.  (Paper: Q/K norms and
+                    // a lane owns a quarter of a row: the per-head RMSNorm is an in-lane sum of 32 squares plus two
+                    // exchanges, and the rotary partner of column c < 64 (block j) is
+                    // column c + 64 (block j + 4) of the same lane and register.  (Paper: Q/K norms and
                     // RoPE are position-wise, hence run on compact rows - "Integration with Attention".)
                     const int i = ip + il;
                     float rs = 1.0f;
@@ -564,58 +463,55 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
 #pragma unroll
                         for (int j = 0; j < NB; ++j)
 #pragma unroll
-                            for (int e = 0; e < 16; ++e) ss += RADIX_ACC(j, i, e) * RADIX_ACC(j, i, e);
+                            for (int e = 0; e < 4; ++e) ss += RADIX_ACC(j, i, e) * RADIX_ACC(j, i, e);
+                        ss += __shfl_xor(ss, 16, 64);
                         ss += __shfl_xor(ss, 32, 64);
                         rs = 1.0f / sqrtf(ss * (1.0f / 128.0f) + qe.eps);
                     }
                     const float* ct = qe.cos_tab + (size_t)rope_pos[i] * 64;
                     const float* st = qe.sin_tab + (size_t)rope_pos[i] * 64;
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int c = 32 * j + 8 * q + 4 * g;
-                            const f32x4 cs = *reinterpret_cast<const f32x4*>(ct + c);
-                            const f32x4 sn = *reinterpret_cast<const f32x4*>(st + c);
-                            f32x4 ga = {1.f, 1.f, 1.f, 1.f}, gb = {1.f, 1.f, 1.f, 1.f};
-                            if (qe.qk_norm) {
-                                ga = *reinterpret_cast<const f32x4*>(rope_gain + c);
-                                gb = *reinterpret_cast<const f32x4*>(rope_gain + c + 64);
-                            }
-                            V4 va, vb;
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const float xa = RADIX_ACC(j, i, q * 4 + t) * rs * ga[t];
-                                const float xb = RADIX_ACC(j + 2, i, q * 4 + t) * rs * gb[t];
-                                const float ya = xa * cs[t] - xb * sn[t], yb = xb * cs[t] + xa * sn[t];
-                                const T ha = (T)ya, hb = (T)yb;
-                                va[t] = part == 0 ? ha : (T)(ya - (float)ha);
-                                vb[t] = part == 0 ? hb : (T)(yb - (float)hb);
-                            }
-                            *reinterpret_cast<V4*>(rowp + c * 2) = va;
-                            *reinterpret_cast<V4*>(rowp + (c + 64) * 2) = vb;
+                    for (int j = 0; j < 4; ++j) {
+                        const int c = 16 * j + 4 * g;
+                        const f32x4 cs = *reinterpret_cast<const f32x4*>(ct + c);
+                        const f32x4 sn = *reinterpret_cast<const f32x4*>(st + c);
+                        f32x4 ga = {1.f, 1.f, 1.f, 1.f}, gb = {1.f, 1.f, 1.f, 1.f};
+                        if (qe.qk_norm) {
+                            ga = *reinterpret_cast<const f32x4*>(rope_gain + c);
+                            gb = *reinterpret_cast<const f32x4*>(rope_gain + c + 64);
                         }
+                        V4 va, vb;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const float xa = RADIX_ACC(j, i, t) * rs * ga[t];
+                            const float xb = RADIX_ACC(j + 4 < NB ? j + 4 : 0, i, t) * rs * gb[t];
+                            const float ya = xa * cs[t] - xb * sn[t], yb = xb * cs[t] + xa * sn[t];
+                            const T ha = (T)ya, hb = (T)yb;
+                            va[t] = part == 0 ? ha : (T)(ya - (float)ha);
+                            vb[t] = part == 0 ? hb : (T)(yb - (float)hb);
+                        }
+                        *reinterpret_cast<V4*>(rowp + c * 2) = va;
+                        *reinterpret_cast<V4*>(rowp + (c + 64) * 2) = vb;
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 } else {
 #pragma unroll
-                    for (int j = 0; j < NB; ++j)
+                    for (int j = 0; j < NB; ++j) {
+                        V4 v;
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            V4 v;
-#pragma unroll
-                            for (int t = 0; t < 4; ++t) {
-                                const float y = RADIX_ACC(j, ip + il, q * 4 + t);
-                                const T hi = (T)y;
-                                v[t] = part == 0 ? hi : (T)(y - (float)hi);
-                            }
-                            *reinterpret_cast<V4*>(rowp + (j * 32 + 8 * q + 4 * g) * 2) = v;
+                        for (int t = 0; t < 4; ++t) {
+                            const float y = RADIX_ACC(j, ip + il, t);
+                            const T hi = (T)y;
+                            v[t] = part == 0 ? hi : (T)(y - (float)hi);
                         }
+                        *reinterpret_cast<V4*>(rowp + (16 * j + 4 * g) * 2) = v;
+                    }
                 }
             }
 #pragma unroll
             for (int t = 0; t < 64 / ROWS_PER_INST; ++t) {
                 const int row = orow + ROWS_PER_INST * t;
-                const int gm = m0 + wm * WTM + ip * 32 + row;
+                const int gm = m0 + wm * WTM + ip * 16 + row;
                 const uint4 v = *reinterpret_cast<const uint4*>(ebuf + row * PITCH + ochunk * 16);
                 if (gm < M)
                     *reinterpret_cast<uint4*>((T*)out_ + (size_t)gm * ldo + part * out_w + ncol0 + ochunk * 8) = v;
@@ -631,7 +527,7 @@ template <int DT, int BM, int BN, int WAVES_M, int WAVES_N>
 int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out,
                const QkvEpilogue& qe, const ARowMap& amap, const NormFusion& nf, hipStream_t stream) {
     typedef typename Op<DT>::T T;
-    if (Nout % BN != 0 || K % (2 * BK) != 0) return RADIX_ERR_UNSUPPORTED;
+    if (Nout % BN != 0 || K % GEMM_BK != 0) return RADIX_ERR_UNSUPPORTED;
     const int tiles_m = ceil_div(M, BM), tiles_n = Nout / BN;
     dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * WAVES_M * WAVES_N);
     const int band_cfg = gemm_band_rows(BM, K, (int)sizeof(T), tiles_n);
@@ -643,6 +539,11 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
     } while (0)
     // the 128-row tiles serve folded norms only: the epilogues that consume or produce one
     constexpr bool ALL = BM == 256;
+    if constexpr (BM == 256 && WAVES_M * WAVES_N == 4) {
+        if (epilogue != EPI_RESIDUAL_NORM) return RADIX_ERR_UNSUPPORTED;
+        RADIX_LAUNCH(EPI_RESIDUAL_NORM);
+        return RADIX_OK;
+    } else {
     if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE);
     else if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU);
     else if (epilogue == EPI_RESIDUAL) {
@@ -666,8 +567,9 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
         if constexpr (ALL && BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT);
         else return RADIX_ERR_UNSUPPORTED;
     } else return RADIX_ERR_UNSUPPORTED;
-#undef RADIX_LAUNCH
     return RADIX_OK;
+    }
+#undef RADIX_LAUNCH
 }
 
 // CUs of the device (a partition has fewer than the chip's 256); 256 where there is no device to ask
@@ -709,11 +611,13 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
             const double tiles = (double)ceil_div(M, sh.bm) * (Nout / sh.bn);
             double rounds = tiles / n_cu;
             if (rounds < 8.0) rounds = (double)(long long)(rounds + 0.999999);   // few rounds: the last one counts whole
-            const double t = rounds * (sh.fixed_us + (K / BK) * sh.ktile_us);
+            const double t = rounds * (sh.fixed_us + (K / 32) * sh.ktile_us);
             if (variant == 0 || t < best) { best = t; variant = sh.variant; }
         }
         if (variant == 0) return RADIX_ERR_UNSUPPORTED;
     }
+    // four wavefronts of 512 registers: for the epilogue that needs them
+    if (variant == 1 && epilogue != EPI_RESIDUAL_NORM) variant = 4;
     if (variant == 5 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 4 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 1 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
@@ -743,7 +647,6 @@ struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[3]; };
 struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
 constexpr int LONG_K = 1024;
 const TileShape tile_shapes[] = {
-    { 1, 256, 256, 1, {0.00, 10.78, 1.424, 0.000, {0.00, 0.00, 0.00}}, {0.30, 0.00, 1.590, 0.000, {5.86, 18.25, 22.79}}},
     { 4, 256, 256, 1, {0.00,  5.33, 1.446, 0.000, {0.00, 0.00, 0.00}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
     {11,  32,  16, 3, {0.00,  0.40, 0.132, 0.105, {0.00, 0.00, 0.00}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
     {12,  32,  32, 2, {0.00,  0.68, 0.142, 0.123, {0.00, 0.00, 0.00}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
@@ -823,7 +726,7 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
     if (M <= 0 || Nout <= 0) return RADIX_OK;
     if (K <= 0) return RADIX_ERR_UNSUPPORTED;
     if (w_k == 0) w_k = K;
-    if (w_k != K && (2 * w_k != K || w_k % (2 * BK) != 0)) return RADIX_ERR_UNSUPPORTED;
+    if (w_k != K && (2 * w_k != K || w_k % GEMM_BK != 0)) return RADIX_ERR_UNSUPPORTED;
     if ((((uintptr_t)A | (uintptr_t)W | (uintptr_t)out) & 15) != 0) return RADIX_ERR_MISALIGNED;
     QkvEpilogue qe = {};
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT) {
@@ -852,7 +755,7 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
         return RADIX_ERR_UNSUPPORTED;
     };
     if (variant != 0 || folded) return launch(variant, A, M, out);
-    if (K % (2 * BK) != 0) return RADIX_ERR_UNSUPPORTED;
+    if (K % GEMM_BK != 0) return RADIX_ERR_UNSUPPORTED;
     const GemmPlan plan = plan_gemm(device_cus(), M, Nout, K, epilogue);
     if (plan.v1 == 0) return RADIX_ERR_UNSUPPORTED;
     const int rc = launch(plan.v1, A, plan.m1, out);
@@ -932,7 +835,8 @@ extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int
     if (rows && (!status || n_valid < 0 || n_valid > M)) return RADIX_ERR_BAD_SIZE;
     if (variant != 0) {
         bool known = false;
-        for (const TileShape& sh : tile_shapes) known = known || (sh.variant == variant && tile_usable(sh, Nout, epilogue));
+        for (const TileShape& sh : tile_shapes)
+            known = known || ((sh.variant == variant || (sh.variant == 4 && variant == 1)) && tile_usable(sh, Nout, epilogue));
         if (!known) return RADIX_ERR_UNSUPPORTED;
     }
     const QkvEpilogue qe = {gq, gk, cos_tab, sin_tab, pos, n_q_heads, n_kv_heads, qk_norm, 1e-6f};

@@ -5,8 +5,8 @@
 // come from HBM once.  A 128-row tile gives such a launch 8 to 100 workgroups of 256 CUs, each of which walks all
 // of K alone.  Splitting K over workgroups would shorten the walk, but an output element must be summed in the
 // same order whatever M is (a row of the deduplicated and of the plain pass agree bit for bit), so the tiles get
-// smaller instead: every element is the chain of matrix instructions of the large kernel (one v_mfma_f32_16x16x32
-// rounds like two v_mfma_f32_32x32x16) with the same epilogue expressions, and the results are identical.
+// smaller instead: every element is the chain of matrix instructions of the large kernel with the same epilogue expressions,
+// and the results are identical.
 //
 // Structure: k-tiles of 64 (a row is one 128-byte line) travel global -> LDS by global_load_lds_dwordx4 through a
 // ring of NS stages; the fragments of the next tile (small wavefront blocks) or k-step (large ones) are read ahead of
@@ -29,26 +29,6 @@
 
 namespace {
 
-constexpr int SBK = 64;                    // k-tile: 128 bytes = 8 chunks of 16 bytes per row
-
-// LDS byte offset of chunk c of tile row `row`: two rows span the 64 banks, so XORing the chunk index with bits
-// 1..3 of the row sends 16 consecutive rows of one chunk column to 16 distinct 16-byte bank groups.
-__device__ __forceinline__ int sswz(int row) { return (row >> 1) & 7; }
-
-// v_mfma_f32_16x16x32: lane (r = lane % 16, g = lane / 16) supplies 8 consecutive k of row r for both operands (k-group
-// g); accumulator register e is row 4 g + e, column r.  One of them rounds like two v_mfma_f32_32x32x16 in a row.
-template <int DT> struct Op16;
-template <> struct Op16<RADIX_BF16> {
-    static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct Op16<RADIX_F16> {
-    static __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-    }
-};
-
 template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int NS, int EPI>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
     const typename Op<DT>::T* __restrict__ A, const typename Op<DT>::T* __restrict__ W, int M, int Nout, int K,
@@ -62,7 +42,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
     constexpr int A_LOADS = BM / (8 * NW), B_LOADS = BN / (8 * NW), LOADS = A_LOADS + B_LOADS;   // 1 KB wave-loads
     static_assert(A_LOADS * 8 * NW == BM && B_LOADS * 8 * NW == BN, "every wavefront issues the same number of loads");
     static_assert((NS - 1) * LOADS < 64, "vmcnt range");
-    constexpr uint32_t STAGE_B = (BM + BN) * SBK * 2;
+    constexpr uint32_t STAGE_B = (BM + BN) * GEMM_BK * 2;
     constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_SPLIT;
     constexpr bool ROPE = EPI == EPI_QKV_ROPE || EPI == EPI_QKV_ROPE_SPLIT;
     constexpr int PARTS = (EPI == EPI_SWIGLU_SPLIT || EPI == EPI_QKV_ROPE_SPLIT) ? 2 : 1;
@@ -101,16 +81,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
                 src = src < 0 ? 0 : amap.n_src - 1;
             }
         }
-        a_off[j] = (uint32_t)(((size_t)src * K + 8 * (lpc ^ sswz(row))) * sizeof(T));
+        a_off[j] = (uint32_t)(((size_t)src * K + 8 * (lpc ^ gemm_swz(row))) * sizeof(T));
     }
 #pragma unroll
     for (int j = 0; j < B_LOADS; ++j) {
         const int row = 8 * (wave + NW * j) + lrow;
-        w_off[j] = (uint32_t)(((size_t)row * w_k + 8 * (lpc ^ sswz(row))) * sizeof(T));
+        w_off[j] = (uint32_t)(((size_t)row * w_k + 8 * (lpc ^ gemm_swz(row))) * sizeof(T));
     }
     const char* a_base = (const char*)(A + (amap.rows != nullptr ? (size_t)0 : (size_t)m0 * K));
     const char* w_base = (const char*)(W + (size_t)n0 * w_k);
-    const int KT = K / SBK, WKT = w_k / SBK;
+    const int KT = K / GEMM_BK, WKT = w_k / GEMM_BK;
     const uint32_t lds_base = lds_addr(lds_all);
 
     // EPI_RESIDUAL: this thread's pieces of the residual tile are requested ahead of everything else
@@ -138,13 +118,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
             else dma16(a_ptr, a_off[f < B_LOADS ? 0 : f - B_LOADS], lds_base + so + 1024 * (wave + NW * (f - B_LOADS)));
         }
         if (part == 0) return;
-        a_ptr += SBK * sizeof(T);
-        w_ptr += SBK * sizeof(T);
+        a_ptr += GEMM_BK * sizeof(T);
+        w_ptr += GEMM_BK * sizeof(T);
         if (--w_left == 0) { w_left = WKT; w_ptr = w_base; }
     };
     uint32_t rd[2];                                             // k-step ks: chunk 4 ks + g of row r
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(r * 128 + (((4 * ks + g) ^ sswz(r)) << 4));
+    for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(r * 128 + (((4 * ks + g) ^ gemm_swz(r)) << 4));
     const uint32_t a_rd = (uint32_t)(wm * WTM) * 128u, b_rd = (uint32_t)(BM + wn * WTN) * 128u;
     auto read_frags = [&](uint32_t so, int ks, V8 (&fa)[2][MB], V8 (&fb)[2][NB]) {
 #pragma unroll
@@ -181,7 +161,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int i = 0; i < MB; ++i) acc[j][i] = Op16<DT>::mfma(fb[ks][j], fa[ks][i], acc[j][i]);
+            for (int i = 0; i < MB; ++i) acc[j][i] = Op<DT>::mfma16(fb[ks][j], fa[ks][i], acc[j][i]);
     };
     auto tile_step = [&](auto more_c) {
         constexpr bool MORE = decltype(more_c)::value;
@@ -222,7 +202,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int i = 0; i < MB; ++i) acc[j][i] = Op16<DT>::mfma(fb[ks][j], fa[ks][i], acc[j][i]);
+                for (int i = 0; i < MB; ++i) acc[j][i] = Op<DT>::mfma16(fb[ks][j], fa[ks][i], acc[j][i]);
             __builtin_amdgcn_sched_barrier(0);
         }
         so = so_n;
@@ -320,8 +300,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
         continue;
     }
     if constexpr (ROPE) {
-        // One q or k head.  Lane (r, g) of EVERY wavefront adds the squares of its half of row r in the order of the
-        // large kernel's accumulator registers, so that the row scale is the same value; the pairs (c, c + 64) of a
+        // One q or k head.  Lane (r, g) of EVERY wavefront adds the squares of two quarters of row r in the order in which
+        // the large kernel's accumulators hold them, so that the row scale is the same value; the pairs (c, c + 64) of a
         // row are then shared out over the wavefronts, 8 U of them each.
         constexpr int U = 8 / NW;
         const int r = lane & 31, g = lane >> 5;
@@ -335,13 +315,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
                 const int pos = qe.pos_c[gm < M ? gm : M - 1];
                 float rs = 1.0f;
                 if (qe.qk_norm) {
-                    float ss = 0.f;
+                    float ss = 0.f, sq = 0.f;                   // quarters 2 g and 2 g + 1 of the row
+                    const float* qp = ct + (32 * ib + r) * CP + 128 * hh + 8 * g;
 #pragma unroll
-                    for (int jq = 0; jq < 16; ++jq) {
-                        const f32x4 v = *reinterpret_cast<const f32x4*>(rowp + 8 * jq);
+                    for (int j = 0; j < 8; ++j) {
+                        const f32x4 v = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+                        const f32x4 w = *reinterpret_cast<const f32x4*>(qp + 16 * j + 4);
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) ss += v[t] * v[t];
+                        for (int t = 0; t < 4; ++t) { ss += v[t] * v[t]; sq += w[t] * w[t]; }
                     }
+                    ss += sq;
                     ss += __shfl_xor(ss, 32, 64);
                     rs = 1.0f / sqrtf(ss * (1.0f / 128.0f) + qe.eps);
                 }
@@ -391,7 +374,7 @@ template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int NS>
 int launch_small_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out,
                      const QkvEpilogue& qe, const ARowMap& amap, hipStream_t stream) {
     typedef typename Op<DT>::T T;
-    if (Nout % BN != 0 || K % SBK != 0 || w_k % SBK != 0) return RADIX_ERR_UNSUPPORTED;
+    if (Nout % BN != 0 || K % GEMM_BK != 0 || w_k % GEMM_BK != 0) return RADIX_ERR_UNSUPPORTED;
     const int tiles_m = ceil_div(M, BM), tiles_n = Nout / BN;
     if ((long long)tiles_m * tiles_n > 0x7FFFFFFFLL) return RADIX_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * WAVES_M * WAVES_N);
