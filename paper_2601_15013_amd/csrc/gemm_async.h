@@ -1,6 +1,8 @@
-// Asynchronous global -> LDS copies and the waits that go with them, shared by the MFMA GEMM kernels.
+// What the MFMA GEMM kernels share: asynchronous global -> LDS copies and the waits that go with them, the k-tile's layout in
+// LDS, and the Q/K-norm + RoPE arithmetic of the q | k | v epilogue.
 #pragma once
 #include "common.h"
+#include "kernels.h"
 
 namespace {
 
@@ -39,5 +41,60 @@ constexpr int GEMM_BK = 64;
 // LDS chunk c of a tile row holds chunk c ^ gemm_swz(row): two rows span the 64 banks, so XORing the chunk index with bits
 // 1..3 of the row sends 16 consecutive rows of one chunk column to 16 distinct 16-byte bank groups.
 __device__ __forceinline__ int gemm_swz(int row) { return (row >> 1) & 7; }
+
+// One quarter of a q or k head's row, as the accumulators of a 16-row block hold it: lane (r, g) has columns 16 j + 4 g + e of
+// row r in v[j][e].  Paper: Q/K norms and RoPE are position-wise, hence run on compact rows ("Integration with Attention").
+// The tables' pieces of the row and the gains' (columns 16 j + 4 g + e, j < 4):
+struct RopeRow { f32x4 cs[4], sn[4]; };
+struct RopeGain { f32x4 a[4], b[4]; };
+__device__ __forceinline__ void rope_load(RopeRow& t, const QkvEpilogue& qe, int pos, int g) {
+    const float* ct = qe.cos_tab + (size_t)pos * 64 + 4 * g;
+    const float* st = qe.sin_tab + (size_t)pos * 64 + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        t.cs[j] = *reinterpret_cast<const f32x4*>(ct + 16 * j);
+        t.sn[j] = *reinterpret_cast<const f32x4*>(st + 16 * j);
+    }
+}
+__device__ __forceinline__ void rope_gain(RopeGain& t, const QkvEpilogue& qe, bool key_head, int g) {
+    const float* gain = (key_head ? qe.gk : qe.gq) + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        t.a[j] = t.b[j] = f32x4{1.f, 1.f, 1.f, 1.f};
+        if (qe.qk_norm) {
+            t.a[j] = *reinterpret_cast<const f32x4*>(gain + 16 * j);
+            t.b[j] = *reinterpret_cast<const f32x4*>(gain + 16 * j + 64);
+        }
+    }
+}
+// The per-head RMSNorm is an in-lane sum of 32 squares plus two exchanges; the rotary partner of column c < 64 (block j) is
+// column c + 64 (block j + 4) of the same lane and register.  out(j, y): the four results of block j.
+template <typename V, typename F>
+__device__ __forceinline__ void rope_apply(const V& v, const RopeRow& t, const RopeGain& gn, const QkvEpilogue& qe, F out) {
+    float rs = 1.0f;
+    if (qe.qk_norm) {
+        float ss = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ss = __builtin_fmaf(v(j, e), v(j, e), ss);
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        rs = 1.0f / sqrtf(ss * (1.0f / 128.0f) + qe.eps);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        f32x4 ya, yb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float xa = v(j, e) * rs * gn.a[j][e];
+            const float xb = v(j + 4, e) * rs * gn.b[j][e];
+            ya[e] = __builtin_fmaf(xa, t.cs[j][e], -(xb * t.sn[j][e]));
+            yb[e] = __builtin_fmaf(xb, t.cs[j][e], xa * t.sn[j][e]);
+        }
+        out(j, ya);
+        out(j + 4, yb);
+    }
+}
 
 }  // namespace

@@ -45,7 +45,7 @@
 
 namespace {
 
-template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
+template <int DT, int BM, int BN, int WAVES_M, int WAVES_N, int EPI, bool FOLD>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const typename Op<DT>::T* __restrict__ A,
                                                                  const typename Op<DT>::T* __restrict__ W, int M,
                                                                  int Nout, int K, void* __restrict__ out_,
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     // requested here, ahead of the first tile loads, and added up once those are under way; the row scales
     // then sit in MB registers through the main loop (the epilogue would otherwise start with a chain of
     // dependent loads per tile).
-    constexpr bool CONSUMES_NORM = EPI == EPI_STORE || EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE;
+    constexpr bool CONSUMES_NORM = FOLD && (EPI == EPI_STORE || EPI == EPI_SWIGLU || EPI == EPI_QKV_ROPE);
     constexpr int SS_EARLY = 16 / MB;                           // float2 loads per row requested early
     float2 ssv[MB][SS_EARLY];
     const bool scale_rows = CONSUMES_NORM && nf.ss_in != nullptr;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     const int lane = lane_opaque;
     const int r = lane & 15, g = lane >> 4;
 
-#define RADIX_ACC(J, I, E) (acc[J][I][E] * rsr[I])
+#define RADIX_ACC(J, I, E) (CONSUMES_NORM ? acc[J][I][E] * rsr[I] : acc[J][I][E])
 
     if (EPI == EPI_RESIDUAL_NORM) {
         // fp32 read-modify-write of the residual stream as below, plus, per row: the updated values times the
@@ -427,11 +427,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         // Q/K-norm + RoPE: which head this wavefront's columns are, and whether it is rotated (q, k) or not (v)
         const int head = (n0 + wn * WTN) >> 7;
         const bool rope_head = ROPE && head < qe.n_q_heads + qe.n_kv_heads;
-        const float* rope_gain = (ROPE && head >= qe.n_q_heads) ? qe.gk : qe.gq;
+        RopeGain gains;
+        constexpr int TABS = PARTS == 2 || FOLD ? 1 : 2;        // two do not fit the registers of those epilogues
+        RopeRow tab[TABS];
+        if (rope_head) rope_gain(gains, qe, head >= qe.n_q_heads, g);
 #pragma unroll
         for (int ip = 0; ip < MB; ip += 4) {
 #pragma unroll
           for (int part = 0; part < PARTS; ++part) {
+            if (TABS == 2 && rope_head) rope_load(tab[0], qe, rope_pos[ip], g);
 #pragma unroll
             for (int il = 0; il < 4; ++il) {
                 char* rowp = ebuf + (il * 16 + r) * PITCH;
@@ -451,48 +455,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                         *reinterpret_cast<V4*>(rowp + (((j >> 2) * 2 + (j & 1)) * 16 + 4 * g) * 2) = v;
                     }
                 } else if (ROPE && rope_head) {
-                    // This wavefront's 128 columns are exactly one q or k head of the fused q|k|v row and
-                    // a lane owns a quarter of a row: the per-head RMSNorm is an in-lane sum of 32 squares plus two
-                    // exchanges, and the rotary partner of column c < 64 (block j) is
-                    // column c + 64 (block j + 4) of the same lane and register.  (Paper: Q/K norms and
-                    // RoPE are position-wise, hence run on compact rows - "Integration with Attention".)
+                    // This wavefront's 128 columns are exactly one q or k head of the fused q|k|v row.  The table rows of the
+                    // next 16 rows are on their way while these are rotated: with the rows fetched as they are used, and the
+                    // gains with them, this epilogue cost as much as 6 k-tiles more (M 8192, N 4096, K 1024: 84 -> 75 us a
+                    // launch, 50432 rows 483 -> 444).
                     const int i = ip + il;
-                    float rs = 1.0f;
-                    if (qe.qk_norm) {
-                        float ss = 0.f;
-#pragma unroll
-                        for (int j = 0; j < NB; ++j)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) ss += RADIX_ACC(j, i, e) * RADIX_ACC(j, i, e);
-                        ss += __shfl_xor(ss, 16, 64);
-                        ss += __shfl_xor(ss, 32, 64);
-                        rs = 1.0f / sqrtf(ss * (1.0f / 128.0f) + qe.eps);
-                    }
-                    const float* ct = qe.cos_tab + (size_t)rope_pos[i] * 64;
-                    const float* st = qe.sin_tab + (size_t)rope_pos[i] * 64;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int c = 16 * j + 4 * g;
-                        const f32x4 cs = *reinterpret_cast<const f32x4*>(ct + c);
-                        const f32x4 sn = *reinterpret_cast<const f32x4*>(st + c);
-                        f32x4 ga = {1.f, 1.f, 1.f, 1.f}, gb = {1.f, 1.f, 1.f, 1.f};
-                        if (qe.qk_norm) {
-                            ga = *reinterpret_cast<const f32x4*>(rope_gain + c);
-                            gb = *reinterpret_cast<const f32x4*>(rope_gain + c + 64);
-                        }
-                        V4 va, vb;
+                    if (TABS == 1) rope_load(tab[0], qe, rope_pos[i], g);
+                    else if (il < 3) rope_load(tab[(il + 1) % TABS], qe, rope_pos[il < 3 ? i + 1 : 0], g);
+                    __builtin_amdgcn_sched_barrier(0);
+                    rope_apply([&](int j, int e) { return RADIX_ACC(j < NB ? j : 0, i, e); }, tab[il % TABS], gains, qe, [&](int j, f32x4 y) {
+                        V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const float xa = RADIX_ACC(j, i, t) * rs * ga[t];
-                            const float xb = RADIX_ACC(j + 4 < NB ? j + 4 : 0, i, t) * rs * gb[t];
-                            const float ya = xa * cs[t] - xb * sn[t], yb = xb * cs[t] + xa * sn[t];
-                            const T ha = (T)ya, hb = (T)yb;
-                            va[t] = part == 0 ? ha : (T)(ya - (float)ha);
-                            vb[t] = part == 0 ? hb : (T)(yb - (float)hb);
+                            const T hi = (T)y[t];
+                            v[t] = part == 0 ? hi : (T)(y[t] - (float)hi);
                         }
-                        *reinterpret_cast<V4*>(rowp + c * 2) = va;
-                        *reinterpret_cast<V4*>(rowp + (c + 64) * 2) = vb;
-                    }
+                        *reinterpret_cast<V4*>(rowp + (16 * j + 4 * g) * 2) = v;
+                    });
                     __builtin_amdgcn_sched_barrier(0);
                 } else {
 #pragma unroll
@@ -531,45 +510,41 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
     const int tiles_m = ceil_div(M, BM), tiles_n = Nout / BN;
     dim3 grid((unsigned)(tiles_m * tiles_n)), block(64 * WAVES_M * WAVES_N);
     const int band_cfg = gemm_band_rows(BM, K, (int)sizeof(T), tiles_n);
-#define RADIX_LAUNCH(E)                                                                                       \
+#define RADIX_LAUNCH(E, FOLD)                                                                                 \
     do {                                                                                                      \
-        auto kfn = gemm_mfma_kernel<DT, BM, BN, WAVES_M, WAVES_N, E>;                                         \
+        auto kfn = gemm_mfma_kernel<DT, BM, BN, WAVES_M, WAVES_N, E, FOLD>;                                   \
         hipLaunchKernelGGL(kfn, grid, block, 0, stream, (const T*)A, (const T*)W, M, Nout, K, out, tiles_m,   \
                            tiles_n, w_k, qe, amap, nf, band_cfg);                                             \
+        return RADIX_OK;                                                                                      \
     } while (0)
-    // the 128-row tiles serve folded norms only: the epilogues that consume or produce one
-    constexpr bool ALL = BM == 256;
-    if constexpr (BM == 256 && WAVES_M * WAVES_N == 4) {
-        if (epilogue != EPI_RESIDUAL_NORM) return RADIX_ERR_UNSUPPORTED;
-        RADIX_LAUNCH(EPI_RESIDUAL_NORM);
-        return RADIX_OK;
-    } else {
-    if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE);
-    else if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU);
-    else if (epilogue == EPI_RESIDUAL) {
-        if constexpr (ALL) RADIX_LAUNCH(EPI_RESIDUAL);
-        else return RADIX_ERR_UNSUPPORTED;
-    } else if (epilogue == EPI_SWIGLU_SPLIT) {
-        if constexpr (ALL) RADIX_LAUNCH(EPI_SWIGLU_SPLIT);
-        else return RADIX_ERR_UNSUPPORTED;
-    } else if (epilogue == EPI_STORE_F32) {
-        if constexpr (ALL) RADIX_LAUNCH(EPI_STORE_F32);
-        else return RADIX_ERR_UNSUPPORTED;
+    // PLAIN: products without a folded norm; the other shapes serve folded norms only
+    constexpr bool PLAIN = BM == 256 && WAVES_M * WAVES_N == 8, ROPE = BN / WAVES_N == 128;
+    if constexpr (!PLAIN || BN == 256) {
+        if (nf.ss_in != nullptr) {
+            if constexpr (BM != 256 || PLAIN) {
+                if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE, true);
+                if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU, true);
+                if constexpr (ROPE)
+                    if (epilogue == EPI_QKV_ROPE) RADIX_LAUNCH(EPI_QKV_ROPE, true);
+            }
+            return RADIX_ERR_UNSUPPORTED;
+        }
     }
-    else if (epilogue == EPI_RESIDUAL_NORM) {
-        if constexpr (BN / WAVES_N == 128 && WAVES_M * WAVES_N == 4) RADIX_LAUNCH(EPI_RESIDUAL_NORM);
-        else return RADIX_ERR_UNSUPPORTED;
+    if constexpr (PLAIN) {
+        if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE, false);
+        if (epilogue == EPI_RESIDUAL) RADIX_LAUNCH(EPI_RESIDUAL, false);
+        if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU, false);
+        if (epilogue == EPI_SWIGLU_SPLIT) RADIX_LAUNCH(EPI_SWIGLU_SPLIT, false);
+        if (epilogue == EPI_STORE_F32) RADIX_LAUNCH(EPI_STORE_F32, false);
+        if constexpr (ROPE) {
+            if (epilogue == EPI_QKV_ROPE) RADIX_LAUNCH(EPI_QKV_ROPE, false);
+            if (epilogue == EPI_QKV_ROPE_SPLIT) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT, false);
+        }
     }
-    else if (epilogue == EPI_QKV_ROPE) {
-        if constexpr (BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE);
-        else return RADIX_ERR_UNSUPPORTED;
-    } else if (epilogue == EPI_QKV_ROPE_SPLIT) {
-        if constexpr (ALL && BN / WAVES_N == 128) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT);
-        else return RADIX_ERR_UNSUPPORTED;
-    } else return RADIX_ERR_UNSUPPORTED;
-    return RADIX_OK;
-    }
+    if constexpr (ROPE && WAVES_M * WAVES_N == 4)
+        if (epilogue == EPI_RESIDUAL_NORM) RADIX_LAUNCH(EPI_RESIDUAL_NORM, false);
 #undef RADIX_LAUNCH
+    return RADIX_ERR_UNSUPPORTED;
 }
 
 // CUs of the device (a partition has fewer than the chip's 256); 256 where there is no device to ask

@@ -93,6 +93,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
     const int KT = K / GEMM_BK, WKT = w_k / GEMM_BK;
     const uint32_t lds_base = lds_addr(lds_all);
 
+    // EPI_QKV_ROPE: blocks of 16 rows of one head that a wavefront rotates at a time; where that is one in all, its rows'
+    // positions are fetched here and the table rows behind the loop, so that neither is waited for at the end
+    constexpr int RB = (EROWS / 16 + NW - 1) / NW;
+    constexpr bool ROPE_EARLY = ROPE && RB == 1 && EROWS == BM && BN == 128 && PARTS == 1;
+    int rope_pos = 0;
+    RopeRow tab;
+    RopeGain gains;
+    if (ROPE_EARLY) {
+        const int gm = m0 + 16 * wave + r;
+        rope_pos = qe.pos_c[gm < M ? gm : M - 1];
+    }
     // EPI_RESIDUAL: this thread's pieces of the residual tile are requested ahead of everything else
     constexpr int RES_IT = EROWS * BN / 4 / NT;
     constexpr bool RES_EARLY = EPI == EPI_RESIDUAL && EROWS == BM && RES_IT <= 8;
@@ -234,6 +245,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
     // time go to LDS, once the wavefronts are done with what was there: register e of acc[j][i] is row 16 i + r,
     // column 16 j + 4 g + e of this wavefront's block.
     float* const ct = reinterpret_cast<float*>(lds_all);
+    asm volatile("" : "+v"(rope_pos));                          // nothing that needs it is computed, and so waited for, above the loop
+    if (ROPE_EARLY && wave < EROWS / 16 && (n0 >> 7) < qe.n_q_heads + qe.n_kv_heads) {
+        rope_load(tab, qe, rope_pos, g);
+        rope_gain(gains, qe, (n0 >> 7) >= qe.n_q_heads, g);
+    }
     T* const outp = (T*)out_;
     const int out_w = SWIGLU ? (Nout >> 1) : Nout, ldo = out_w * PARTS;
     const int ncol0 = SWIGLU ? (n0 >> 1) : n0;
@@ -300,62 +316,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_small_kernel(
         continue;
     }
     if constexpr (ROPE) {
-        // One q or k head.  Lane (r, g) of EVERY wavefront adds the squares of two quarters of row r in the order in which
-        // the large kernel's accumulators hold them, so that the row scale is the same value; the pairs (c, c + 64) of a
-        // row are then shared out over the wavefronts, 8 U of them each.
-        constexpr int U = 8 / NW;
-        const int r = lane & 31, g = lane >> 5;
+        // One q or k head: blocks of 16 rows are shared out over the wavefronts, and a lane takes the piece of a row that the
+        // large kernel's accumulators would give it, so that the results are the same.
         T* const ht = reinterpret_cast<T*>(lds_all + EROWS * CP * 4);
-        const float* rope_gain = head >= qe.n_q_heads ? qe.gk : qe.gq;
         for (int part = 0; part < PARTS; ++part) {
             if (part || hh) __syncthreads();                    // the staging rows have been read
-            for (int ib = 0; ib < EROWS / 32; ++ib) {
-                const float* rowp = ct + (32 * ib + r) * CP + 128 * hh + 4 * g;
-                const int gm = e0 + 32 * ib + r;
-                const int pos = qe.pos_c[gm < M ? gm : M - 1];
-                float rs = 1.0f;
-                if (qe.qk_norm) {
-                    float ss = 0.f, sq = 0.f;                   // quarters 2 g and 2 g + 1 of the row
-                    const float* qp = ct + (32 * ib + r) * CP + 128 * hh + 8 * g;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const f32x4 v = *reinterpret_cast<const f32x4*>(qp + 16 * j);
-                        const f32x4 w = *reinterpret_cast<const f32x4*>(qp + 16 * j + 4);
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) { ss += v[t] * v[t]; sq += w[t] * w[t]; }
-                    }
-                    ss += sq;
-                    ss += __shfl_xor(ss, 32, 64);
-                    rs = 1.0f / sqrtf(ss * (1.0f / 128.0f) + qe.eps);
+            for (int q = 0; q < RB; ++q) {
+                const int ib = wave + NW * q;
+                if (ib >= EROWS / 16) continue;
+                if (!ROPE_EARLY) {
+                    const int gm = e0 + 16 * ib + r;
+                    rope_load(tab, qe, qe.pos_c[gm < M ? gm : M - 1], g);
+                    rope_gain(gains, qe, head >= qe.n_q_heads, g);
                 }
-                const float* ctab = qe.cos_tab + (size_t)pos * 64;
-                const float* stab = qe.sin_tab + (size_t)pos * 64;
+                const float* rowp = ct + (16 * ib + r) * CP + 128 * hh + 4 * g;
+                f32x4 v[8];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int c8 = 8 * (U * wave + u), c = c8 + 4 * g;
-                    const f32x4 cs = *reinterpret_cast<const f32x4*>(ctab + c);
-                    const f32x4 sn = *reinterpret_cast<const f32x4*>(stab + c);
-                    f32x4 ga = {1.f, 1.f, 1.f, 1.f}, gb = {1.f, 1.f, 1.f, 1.f};
-                    if (qe.qk_norm) {
-                        ga = *reinterpret_cast<const f32x4*>(rope_gain + c);
-                        gb = *reinterpret_cast<const f32x4*>(rope_gain + c + 64);
-                    }
-                    const f32x4 va = *reinterpret_cast<const f32x4*>(rowp + c8);
-                    const f32x4 vb = *reinterpret_cast<const f32x4*>(rowp + c8 + 64);
-                    T ya[4], yb[4];
+                for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4*>(rowp + 16 * j);
+                rope_apply([&](int j, int e) { return v[j][e]; }, tab, gains, qe, [&](int j, f32x4 y) {
+                    T o[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const float xa = va[t] * rs * ga[t];
-                        const float xb = vb[t] * rs * gb[t];
-                        const float a = xa * cs[t] - xb * sn[t], b = xb * cs[t] + xa * sn[t];
-                        ya[t] = (T)a;
-                        yb[t] = (T)b;
-                        if (part) { ya[t] = (T)(a - (float)ya[t]); yb[t] = (T)(b - (float)yb[t]); }
+                        o[t] = (T)y[t];
+                        if (part) o[t] = (T)(y[t] - (float)o[t]);
                     }
-                    T* hp = ht + (32 * ib + r) * HP + c;
-                    *reinterpret_cast<uint2*>(hp) = *reinterpret_cast<uint2*>(ya);
-                    *reinterpret_cast<uint2*>(hp + 64) = *reinterpret_cast<uint2*>(yb);
-                }
+                    *reinterpret_cast<uint2*>(ht + (16 * ib + r) * HP + 16 * j + 4 * g) = *reinterpret_cast<uint2*>(o);
+                });
             }
             __syncthreads();
             for (int idx = tid; idx < EROWS * 16; idx += NT) {
