@@ -22,6 +22,8 @@
 //           N 1024 K 3072 19.4 -> 6.8, N 4096 K 12288 96 -> 25
 //   M 1072: N 1024 K 2048 19.7 -> 13.8, N 1024 K 3072 27.3 -> 18.7, N 4096 K 12288 169 -> 141
 //   M 768:  N 24576 K 4096 183 -> 163, N 4096 K 12288 131 -> 112
+// The 128x128 tile has four stages: with three, two tiles of 0.44 us each were in flight, less than the latency of weights that
+// come from HBM (M 658: N 4096 K 12288 99.5 -> 89.6 us, N 4096 K 4096 35.9 -> 32.8, N 24576 K 4096 171 -> 166; five are no better).
 #include <type_traits>
 
 #include "gemm_async.h"
@@ -404,7 +406,7 @@ int launch_small_dt(int variant, const void* A, const void* W, int M, int Nout, 
         case 15: return launch_small_cfg<DT, 64, 32, 2, 2, 5>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
         case 16: return launch_small_cfg<DT, 64, 64, 2, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
         case 17: return launch_small_cfg<DT, 64, 128, 2, 4, 3>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
-        case 18: return launch_small_cfg<DT, 128, 128, 2, 4, 3>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
+        case 18: return launch_small_cfg<DT, 128, 128, 2, 4, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
         case 19: return launch_small_cfg<DT, 128, 256, 2, 4, 3>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
         case 20: return launch_small_cfg<DT, 256, 128, 4, 2, 3>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, s);
         default: return RADIX_ERR_UNSUPPORTED;
