@@ -58,7 +58,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     static_assert(NW == 4 || NW == 8, "4 or 8 wavefronts");
     constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;
     constexpr int MB = WTM / 16, NB = WTN / 16;
-    constexpr int A_LOADS = BM / (8 * NW), B_LOADS = BN / (8 * NW);     // 1 KB wave-loads per wavefront per k-tile
+    // 1 KB wave-loads per wavefront per k-tile; where the rows of A do not share out evenly the first wavefronts have one more
+    constexpr int A_LOADS = (BM / 8 + NW - 1) / NW, A_REM = BM / 8 % NW, B_LOADS = BN / (8 * NW);
+    static_assert(BM % 8 == 0 && BN % (8 * NW) == 0, "whole wave-loads");
     constexpr uint32_t A_SLOT = BM * GEMM_BK * 2, B_SLOT = BN * GEMM_BK * 2;
     constexpr bool SWIGLU = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_SPLIT;
     constexpr bool ROPE = EPI == EPI_QKV_ROPE || EPI == EPI_QKV_ROPE_SPLIT;
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     static_assert(!SWIGLU || (NB % 4 == 0), "SwiGLU needs gate/up block pairs of 32 columns in one wavefront");
     static_assert(!ROPE || WTN == 128, "Q/K-norm + RoPE epilogue: one wavefront = one 128-wide head");
     static_assert(EPI != EPI_RESIDUAL_NORM || WTN == 128, "sum-of-squares slots are 128 columns = one wavefront");
-    static_assert(MB % 4 == 0 && (NB == 4 || NB == 8), "passes of 64 rows, k-step slices");
+    static_assert(WTM % 16 == 0 && (NB == 4 || NB == 8), "whole blocks, k-step slices");
 
     constexpr int EPI_PITCH = 272;                             // epilogue row pitch in bytes (256 + 16 pad)
     constexpr uint32_t EPI_B = NW * 64 * EPI_PITCH;            // 64 rows per wavefront
@@ -107,6 +109,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         }
         a_off[j] = (uint32_t)(((size_t)src * K + 8 * (lpc ^ gemm_swz(row))) * sizeof(T));
     }
+    const bool a_extra = A_REM == 0 || wave < A_REM;            // this wavefront has A_LOADS of them, not one less
 #pragma unroll
     for (int j = 0; j < B_LOADS; ++j) {
         const int row = 8 * (wave + NW * j) + lrow;
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     const char* const a_rd = lds_all + (wm * WTM) * 128;
     const char* const b_rd = lds_all + 3 * A_SLOT + (wn * WTN) * 128;
     auto load_a = [&](uint32_t slot, int f) {
-        dma16(a_ptr, a_off[f], lds_base + slot + 1024 * (wave + NW * f));
+        if (A_REM == 0 || f < A_LOADS - 1 || a_extra) dma16(a_ptr, a_off[f], lds_base + slot + 1024 * (wave + NW * f));
         if (f == A_LOADS - 1) a_ptr += GEMM_BK * sizeof(T);
     };
     auto load_b = [&](uint32_t slot, int f) {
@@ -228,7 +231,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         for (int f = 0; f < A_LOADS; ++f) load_a(a_nxt, f);
 #pragma unroll
         for (int f = 0; f < B_LOADS; ++f) load_b(b_nxt, f);
-        wait_vmcnt<A_LOADS + B_LOADS>();
+        if (a_extra) wait_vmcnt<A_LOADS + B_LOADS>();
+        else wait_vmcnt<A_LOADS + B_LOADS - 1>();
     } else {
         wait_vmcnt<0>();
     }
@@ -274,7 +278,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             if (MODE > 0 && j == BAR) {
-                wait_vmcnt_and_lds<MODE == 2 ? A_LOADS : 0>();
+                if (MODE != 2) wait_vmcnt_and_lds<0>();
+                else if (a_extra) wait_vmcnt_and_lds<A_LOADS>();
+                else wait_vmcnt_and_lds<A_LOADS - 1>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
@@ -388,10 +394,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         // stores, and nothing has to be converted, so the LDS detour does not pay here.
 #pragma unroll
         for (int ip = 0; ip < MB; ip += 2) {
-            f32x4 v[2][NB];
-            float* orow[2];
+            constexpr int PAIR = 2;
+            f32x4 v[PAIR][NB];
+            float* orow[PAIR];
 #pragma unroll
-            for (int il = 0; il < 2; ++il) {
+            for (int il = 0; il < PAIR; ++il) {
+                if (ip + il >= MB) continue;
                 const int gm = m0 + wm * WTM + (ip + il) * 16 + r;
                 orow[il] = (float*)out_ + (size_t)(gm < M ? gm : M - 1) * Nout + n0 + wn * WTN + 4 * g;
 #pragma unroll
@@ -401,13 +409,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                 }
             }
 #pragma unroll
-            for (int il = 0; il < 2; ++il) {
+            for (int il = 0; il < PAIR; ++il) {
                 const int gm = m0 + wm * WTM + (ip + il) * 16 + r;
-                if (gm >= M) continue;
+                if (ip + il >= MB || gm >= M) continue;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) v[il][j][t] += acc[j][ip + il][t];
+                    for (int t = 0; t < 4; ++t) v[il][j][t] += acc[j][ip + il < MB ? ip + il : 0][t];
                     *reinterpret_cast<f32x4*>(orow[il] + 16 * j) = v[il][j];
                 }
             }
@@ -438,6 +446,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
             if (TABS == 2 && rope_head) rope_load(tab[0], qe, rope_pos[ip], g);
 #pragma unroll
             for (int il = 0; il < 4; ++il) {
+                if (ip + il >= MB) continue;
+                const int i = ip + il < MB ? ip + il : 0;
                 char* rowp = ebuf + (il * 16 + r) * PITCH;
                 if (SWIGLU) {
 #pragma unroll
@@ -446,7 +456,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                         V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const float gt = RADIX_ACC(j, ip + il, t), up = RADIX_ACC(j + 2 < NB ? j + 2 : 0, ip + il, t);
+                            const float gt = RADIX_ACC(j, i, t), up = RADIX_ACC(j + 2 < NB ? j + 2 : 0, i, t);
                             // silu(g) * u with the hardware reciprocal (1 ulp) instead of an IEEE division
                             const float y = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
                             const T hi = (T)y;
@@ -459,9 +469,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                     // next 16 rows are on their way while these are rotated: with the rows fetched as they are used, and the
                     // gains with them, this epilogue cost as much as 6 k-tiles more (M 8192, N 4096, K 1024: 84 -> 75 us a
                     // launch, 50432 rows 483 -> 444).
-                    const int i = ip + il;
                     if (TABS == 1) rope_load(tab[0], qe, rope_pos[i], g);
-                    else if (il < 3) rope_load(tab[(il + 1) % TABS], qe, rope_pos[il < 3 ? i + 1 : 0], g);
+                    else if (il < 3 && i + 1 < MB) rope_load(tab[(il + 1) % TABS], qe, rope_pos[i + 1 < MB ? i + 1 : 0], g);
                     __builtin_amdgcn_sched_barrier(0);
                     rope_apply([&](int j, int e) { return RADIX_ACC(j < NB ? j : 0, i, e); }, tab[il % TABS], gains, qe, [&](int j, f32x4 y) {
                         V4 v;
@@ -479,7 +488,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                         V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const float y = RADIX_ACC(j, ip + il, t);
+                            const float y = RADIX_ACC(j, i, t);
                             const T hi = (T)y;
                             v[t] = part == 0 ? hi : (T)(y - (float)hi);
                         }
@@ -488,7 +497,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                 }
             }
 #pragma unroll
-            for (int t = 0; t < 64 / ROWS_PER_INST; ++t) {
+            for (int t = 0; t < (MB - ip < 4 ? (MB - ip) * 16 : 64) / ROWS_PER_INST; ++t) {
                 const int row = orow + ROWS_PER_INST * t;
                 const int gm = m0 + wm * WTM + ip * 16 + row;
                 const uint4 v = *reinterpret_cast<const uint4*>(ebuf + row * PITCH + ochunk * 16);
@@ -517,11 +526,12 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
                            tiles_n, w_k, qe, amap, nf, band_cfg);                                             \
         return RADIX_OK;                                                                                      \
     } while (0)
-    // PLAIN: products without a folded norm; the other shapes serve folded norms only
-    constexpr bool PLAIN = BM == 256 && WAVES_M * WAVES_N == 8, ROPE = BN / WAVES_N == 128;
-    if constexpr (!PLAIN || BN == 256) {
+    // PLAIN: products without a folded norm; FOLDED: those with one, consumed or (four wavefronts) prepared
+    constexpr bool EIGHT = WAVES_M * WAVES_N == 8, ROPE = BN / WAVES_N == 128;
+    constexpr bool PLAIN = EIGHT && BM > 128, FOLDED = BM == 128 || (BM == 256 && BN == 256);
+    if constexpr (FOLDED) {
         if (nf.ss_in != nullptr) {
-            if constexpr (BM != 256 || PLAIN) {
+            if constexpr (EIGHT || BM == 128) {
                 if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE, true);
                 if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU, true);
                 if constexpr (ROPE)
@@ -531,17 +541,19 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
         }
     }
     if constexpr (PLAIN) {
+        if constexpr (!(ROPE && BM == 192)) {
         if (epilogue == EPI_STORE) RADIX_LAUNCH(EPI_STORE, false);
         if (epilogue == EPI_RESIDUAL) RADIX_LAUNCH(EPI_RESIDUAL, false);
         if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU, false);
         if (epilogue == EPI_SWIGLU_SPLIT) RADIX_LAUNCH(EPI_SWIGLU_SPLIT, false);
         if (epilogue == EPI_STORE_F32) RADIX_LAUNCH(EPI_STORE_F32, false);
+        }
         if constexpr (ROPE) {
             if (epilogue == EPI_QKV_ROPE) RADIX_LAUNCH(EPI_QKV_ROPE, false);
             if (epilogue == EPI_QKV_ROPE_SPLIT) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT, false);
         }
     }
-    if constexpr (ROPE && WAVES_M * WAVES_N == 4)
+    if constexpr (FOLDED && ROPE && !EIGHT)
         if (epilogue == EPI_RESIDUAL_NORM) RADIX_LAUNCH(EPI_RESIDUAL_NORM, false);
 #undef RADIX_LAUNCH
     return RADIX_ERR_UNSUPPORTED;
@@ -593,6 +605,12 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     }
     // four wavefronts of 512 registers: for the epilogue that needs them
     if (variant == 1 && epilogue != EPI_RESIDUAL_NORM) variant = 4;
+    const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
+    if (variant == 20) return launch_cfg<DT, 256, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 22) return launch_cfg<DT, 160, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 23 && rope) return launch_cfg<DT, 192, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 23) return launch_cfg<DT, 192, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 24) return launch_cfg<DT, 224, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 5 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 4 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 1 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
@@ -601,48 +619,60 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 }
 
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
-// in rounds.  A round of n workgroups per CU costs fixed_us (first loads, epilogue), n epi_us (what of the epilogue grows with
-// n, by what it writes: 16-bit rows, q|k|v heads, fp32 rows) and, per 64 columns of K, step_us (what a k-tile takes when
-// nothing else runs on the CU: a chain of latencies) or n share_us if that is more.  A launch that does not fill its last round
-// pays for it in full, until there are many rounds.
+// in rounds.  Where that is one, a round costs fixed_us + epi_us (first loads, epilogue, by what it writes: 16-bit rows, q|k|v
+// heads, fp32 rows) and, per 64 columns of K, step_us + share_us times the share of the CUs that it occupies (the clock and
+// the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
+// 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us if that is more.
+// A launch that does not fill its last round pays for it in full, until there are many rounds.
 // The constants are least-squares fits of the logarithm to timed launches on MI355X (fp16 operands), in two sets because rows
-// of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about (fits there even end
-// with zeros for some):
-//   long_k, K >= 1024: 240 launches of the four projections of the 0.6B, 4B and 8B shapes, M 8 .. 8240, weights from HBM.  Over
-//     30 products (N 384 .. 151936, K 1024 .. 17408) at 25 row counts from 1 to 130000 they are within 13 % of a launch (tiles
-//     within 2 of the best), and the tile they pick takes 0.8 % longer than the best one (a tenth of them more than 2 %, the
-//     worst 21 %).
-//   short_k: 23 products of K 64 .. 768 at the same row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
+// of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about:
+//   long_k, K >= 1024: 336 (product, row count) pairs of the four projections of the 0.6B, 4B and 8B shapes and four others
+//     (K 1024 .. 12288), M 8 .. 50000, weights from HBM: within 3 % (large tiles) to 13 % (the smallest) of a launch; the tile
+//     they pick takes 0.5 % longer than the best one (a tenth of them more than 1 %, the worst 23 %).
+//   short_k: 23 products of K 64 .. 768 at 25 row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
 //     takes 2.4 % (K 64 and 128), 1.3 % (256 to 384) and 0.7 % (512 to 768) longer than the best, where long_k's pick took 13,
 //     10 and 6 %; bf16 operands, not in the fit, 2.7, 1.2 and 0.7 %.
-// The four-wavefront 256x256 tile is entered in short_k by its ratio to the eight-wavefront one.  The 256x256 tiles of this
-// file win once they fill the chip, their k-loop being the better one (N 24576, K 4096, M 8240: 1480 us against 1640 for
-// 256x256 built like the small ones); below, the smaller ones.
+// The 256x256 tile wins where it fills the chip; the tiles of 160, 192 and 224 rows where that leaves less of the last round
+// empty: M 8300, N 1024: K 3072 70.1 / 57.3 us (256 / 160 rows), K 2048 54.4 / 43.0; M 5000, N 7168, K 5120: 338 / 294 (192 rows);
+// 129 of the 336 pairs have one of the three as their best.  Their constants are 2 % above the fit: among many estimates one that
+// is low by chance would win, and the older tiles are the safer choice.
 struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[3]; };
 struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
 constexpr int LONG_K = 1024;
+constexpr TileCost NOT_SHORT = {};                  // never chosen at short rows (tile_usable)
 const TileShape tile_shapes[] = {
-    { 4, 256, 256, 1, {0.00,  5.33, 1.446, 0.000, {0.00, 0.00, 0.00}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
-    {11,  32,  16, 3, {0.00,  0.40, 0.132, 0.105, {0.00, 0.00, 0.00}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
-    {12,  32,  32, 2, {0.00,  0.68, 0.142, 0.123, {0.00, 0.00, 0.00}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
-    {13,  32, 128, 2, {2.01,  0.00, 0.313, 0.274, {0.00, 0.00, 0.00}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
-    {14,  32,  64, 2, {2.40,  0.00, 0.000, 0.171, {0.00, 0.00, 0.00}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
-    {15,  64,  32, 2, {0.00,  0.00, 0.000, 0.208, {0.00, 0.00, 0.00}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
-    {16,  64,  64, 2, {0.52,  0.63, 0.257, 0.257, {0.00, 0.00, 0.00}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
-    {17,  64, 128, 2, {0.91,  1.48, 0.413, 0.362, {0.00, 0.00, 0.00}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
-    {18, 128, 128, 1, {0.00,  4.24, 0.512, 0.000, {0.00, 0.00, 0.00}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
-    {19, 128, 256, 1, {0.00,  7.75, 0.797, 0.000, {0.00, 0.00, 0.00}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
-    {20, 256, 128, 1, {0.00,  8.71, 0.748, 0.000, {0.00, 0.00, 0.00}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
+    { 4, 256, 256, 1, {1.95,  4.74, 0.776, 0.714, {0.37, 6.56, 12.93}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
+    {11,  32,  16, 3, {2.00,  0.00, 0.113, 0.079, {0.62, 0.50,  0.00}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
+    {12,  32,  32, 2, {1.74,  0.00, 0.130, 0.110, {0.51, 0.50,  0.00}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
+    {13,  32, 128, 2, {1.74,  0.00, 0.339, 0.244, {0.99, 0.46,  0.00}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
+    {14,  32,  64, 2, {1.61,  0.00, 0.191, 0.157, {1.89, 6.30,  0.00}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
+    {15,  64,  32, 2, {1.09,  0.00, 0.183, 0.151, {1.00, 1.00,  0.17}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
+    {16,  64,  64, 2, {3.13,  0.00, 0.084, 0.214, {0.17, 0.55,  0.00}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
+    {17,  64, 128, 2, {1.88,  0.00, 0.443, 0.334, {0.36, 0.79,  0.00}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
+    {18, 128, 128, 1, {1.75,  2.63, 0.367, 0.155, {0.48, 2.12,  1.46}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
+    {19, 128, 256, 1, {3.29,  3.58, 0.598, 0.306, {0.10, 5.33,  2.45}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
+    {20, 256, 128, 1, {2.40,  2.15, 0.551, 0.295, {0.34, 9.36,  6.02}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
+    {22, 160, 256, 1, {3.44,  2.44, 0.663, 0.411, {0.33, 0.51,  6.95}}, NOT_SHORT},
+    {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41}}, NOT_SHORT},
+    {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22}}, NOT_SHORT},
 };
+// 128 to 224 rows of 256 columns are one variant outside: 19
+int variant_outside(int variant) { return variant >= 22 && variant <= 24 ? 19 : variant; }
 
 double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
     const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
     const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 :
                                 epilogue == EPI_RESIDUAL || epilogue == EPI_STORE_F32 ? 2 : 0];
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
+    const double kt = K / 64;
+    if (sh.per_cu == 1) {
+        auto round_us = [&](double busy) { return c.fixed_us + epi + kt * (c.step_us + c.share_us * busy); };
+        if (tiles >= 8LL * cus) return c.launch_us + (double)tiles / cus * round_us(1.0);
+        const int rest = (int)(tiles % cus);
+        return c.launch_us + (double)(tiles / cus) * round_us(1.0) + (rest ? round_us((double)rest / cus) : 0.0);
+    }
     double per = (double)tiles / cus;
     if (per < 8.0) per = (double)((tiles + cus - 1) / cus);
-    const double kt = K / 64;
     const double full = (double)(long long)(per / sh.per_cu), rest = per - full * sh.per_cu;
     auto round_us = [&](double n) {
         return c.fixed_us + n * epi + kt * (n * c.share_us > c.step_us ? n * c.share_us : c.step_us);
@@ -650,9 +680,14 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
     return c.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
 }
 
-bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
+bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
     if (Nout % sh.bn != 0) return false;
-    if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT) return sh.bn % 128 == 0;      // whole heads
+    if (sh.variant >= 22) {                         // chosen where they were measured: long rows, fp32 rows of any width, 16-bit ones
+        const bool fp32 = epilogue == EPI_RESIDUAL || epilogue == EPI_STORE_F32;
+        if (K < LONG_K || (!fp32 && Nout < 2048)) return false;
+    }
+    if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
+        return sh.bn % 128 == 0 && sh.variant != 22 && sh.variant != 24;
     if (epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_SPLIT) return sh.bn % 64 == 0;           // gate/up pairs
     return true;
 }
@@ -661,7 +696,7 @@ bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
 int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double* us) {
     int v = 0;
     for (const TileShape& sh : tile_shapes) {
-        if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
+        if (!tile_usable(sh, Nout, K, epilogue) || (whole && M % sh.bm != 0)) continue;
         const double t = tile_time(sh, cus, M, Nout, K, epilogue);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
     }
@@ -679,7 +714,7 @@ GemmPlan plan_gemm(int cus, int M, int Nout, int K, int epilogue) {
     if (M <= 256) return p;
     double best = 0.97 * whole;             // what a split has to beat: a launch more, and the model's own error
     for (const TileShape& sh : tile_shapes) {
-        if (sh.bm < 128 || !tile_usable(sh, Nout, epilogue)) continue;
+        if (sh.bm < 128 || !tile_usable(sh, Nout, K, epilogue)) continue;
         const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
         const long long rounds = row_tiles * per_row / cus;
         if (rounds < 1 || rounds >= 8) continue;
@@ -723,8 +758,9 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
     if (nf.ss_in && (nf.n_slots_in <= 0 || nf.n_slots_in % 2 != 0 || ((uintptr_t)nf.ss_in & 7) != 0)) return RADIX_ERR_UNSUPPORTED;
     const bool folded = nf.ss_in != nullptr || epilogue == EPI_RESIDUAL_NORM;
     if (folded && variant >= 11) return RADIX_ERR_UNSUPPORTED;
+    const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
     auto launch = [&](int v, const void* a, int m, void* o) -> int {
-        if (v >= 11) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
+        if ((v >= 11 && v < 20) || (v == 20 && rope)) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
         if (op_dtype == RADIX_BF16) return launch_dt<RADIX_BF16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         return RADIX_ERR_UNSUPPORTED;
@@ -768,12 +804,14 @@ extern "C" int radix_debug_gemm_plan_cus(int32_t cus, int32_t M, int32_t Nout, i
     if (!v1 || !bm1 || !bn1 || !m1 || !v2 || !bm2 || !bn2) return RADIX_ERR_NULL_POINTER;
     if (cus <= 0 || M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0) return RADIX_ERR_BAD_SIZE;
     const GemmPlan p = plan_gemm(cus, M, Nout, K, epilogue);
-    *v1 = p.v1; *m1 = p.m1; *v2 = p.v2;
+    *m1 = p.m1;
     *bm1 = *bn1 = *bm2 = *bn2 = 0;
     for (const TileShape& sh : tile_shapes) {
         if (sh.variant == p.v1) { *bm1 = sh.bm; *bn1 = sh.bn; }
         if (sh.variant == p.v2) { *bm2 = sh.bm; *bn2 = sh.bn; }
     }
+    *v1 = variant_outside(p.v1);
+    *v2 = variant_outside(p.v2);
     return p.v1 ? RADIX_OK : RADIX_ERR_UNSUPPORTED;
 }
 extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
@@ -784,15 +822,20 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
                                         double* us) {
     if (!us) return RADIX_ERR_NULL_POINTER;
     if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0 || m1 <= 0 || m1 > M) return RADIX_ERR_BAD_SIZE;
-    double t = 0.0;
-    int parts = 0;
+    double t1 = -1.0, t2 = -1.0;                    // of a variant with several heights the fastest (in front: that divides the rows)
     for (const TileShape& sh : tile_shapes) {
-        if (!tile_usable(sh, Nout, epilogue)) continue;
-        if (sh.variant == v1) { t += tile_time(sh, device_cus(), m1, Nout, K, epilogue); ++parts; }
-        if (m1 < M && sh.variant == v2) { t += tile_time(sh, device_cus(), M - m1, Nout, K, epilogue); ++parts; }
+        if (!tile_usable(sh, Nout, K, epilogue)) continue;
+        if (variant_outside(sh.variant) == v1 && (m1 == M || m1 % sh.bm == 0)) {
+            const double t = tile_time(sh, device_cus(), m1, Nout, K, epilogue);
+            if (t1 < 0.0 || t < t1) t1 = t;
+        }
+        if (m1 < M && variant_outside(sh.variant) == v2) {
+            const double t = tile_time(sh, device_cus(), M - m1, Nout, K, epilogue);
+            if (t2 < 0.0 || t < t2) t2 = t;
+        }
     }
-    if (parts != (m1 < M ? 2 : 1)) return RADIX_ERR_UNSUPPORTED;
-    *us = t;
+    if (t1 < 0.0 || (m1 < M && t2 < 0.0)) return RADIX_ERR_UNSUPPORTED;
+    *us = m1 < M ? t1 + t2 : t1;
     return RADIX_OK;
 }
 // One product on the device with the tile named (0: what the plan picks), for tests that compare the tiles.
@@ -811,7 +854,8 @@ extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int
     if (variant != 0) {
         bool known = false;
         for (const TileShape& sh : tile_shapes)
-            known = known || ((sh.variant == variant || (sh.variant == 4 && variant == 1)) && tile_usable(sh, Nout, epilogue));
+            known = known || ((sh.variant == variant || (sh.variant == 4 && variant == 1)) && tile_usable(sh, Nout, LONG_K, epilogue));
+        if (variant >= 22 && variant <= 24) known = Nout % 256 == 0 && (!rope || variant == 23);
         if (!known) return RADIX_ERR_UNSUPPORTED;
     }
     const QkvEpilogue qe = {gq, gk, cos_tab, sin_tab, pos, n_q_heads, n_kv_heads, qk_norm, 1e-6f};
