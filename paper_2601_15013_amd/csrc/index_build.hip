@@ -25,6 +25,7 @@
 // sequences), but for the comparisons of its first round in large batches; the final map write-out is a chip-wide
 // kernel over tokens.
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -35,7 +36,8 @@ namespace {
 constexpr int IDX_THREADS = 1024;
 constexpr int IDX_WAVES = IDX_THREADS / RADIX_WAVE;
 constexpr int LCP_UNROLL = 4;
-constexpr int LDS_TABLE = 8192;       // slots of a grouping table kept in LDS (64 KB): batches of up to 4096 sequences
+// sequences whose state (22 bytes each) and grouping table (two slots of 8 bytes each) are kept in LDS: 19 and 152 KB
+constexpr int LDS_SEQ_FEW = 512, LDS_SEQ_MANY = 4096;
 
 __device__ __forceinline__ int ld_agent(const int* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -84,19 +86,38 @@ __device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, co
 
 // Validation of cu_seqlens (before anything is dereferenced through it) and the initial state, by one workgroup.
 // Returns the first non-empty sequence, which everybody else follows, or -1 on a malformed array.
+// first: null, or what index_first_round_kernel found: where a follower leaves the first sequence.
+template <int BATCH>
 __device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr, int32_t* ldr,
-                                          int32_t* dep, int32_t* bdep, int32_t* mis, int32_t* n_compact_dev) {
+                                          int32_t* dep, int32_t* bdep, int32_t* mis, const int32_t* first, int32_t* n_compact_dev) {
     __shared__ int sh_first;
-    const int tid = threadIdx.x;
-    // every call starts with a clean status word
-    if (tid == 0) hdr[0] = 0;
-    int bad = 0;
-    for (int i = tid; i <= B; i += IDX_THREADS) {
-        int c = cu[i];
-        if (c < 0 || c > N) bad = 1;
-        if (i == 0 && c != 0) bad = 1;
-        if (i == B && c != N) bad = 1;
-        if (i < B && cu[i + 1] < c) bad = 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) {
+        hdr[0] = 0;             // every call starts with a clean status word
+        sh_first = B;
+    }
+    // BATCH sequences per thread at a time, so that their loads are in flight together
+    int c0[BATCH], c1[BATCH], f[BATCH];
+    auto fetch = [&](int base) {
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = base + u * IDX_THREADS + tid;
+            c0[u] = s < B ? cu[s] : 0;
+            c1[u] = s < B ? cu[s + 1] : 0;
+            f[u] = first != nullptr && s < B ? first[s] : -1;
+        }
+    };
+    int bad = tid == 0 && (cu[0] != 0 || cu[B] != N);
+    __syncthreads();
+    for (int base = 0; base < B; base += BATCH * IDX_THREADS) {
+        fetch(base);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = base + u * IDX_THREADS + tid;
+            if (c0[u] < 0 || c0[u] > N || c1[u] < c0[u] || c1[u] > N) bad = 1;
+            const unsigned long long some = __ballot(c1[u] > c0[u]);
+            if (lane == 0 && some != 0ull) atomicMin(&sh_first, s + __ffsll((long long)some) - 1);
+        }
     }
     bad = __syncthreads_or(bad);
     if (bad) {
@@ -107,75 +128,88 @@ __device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B,
         }
         return -1;
     }
-    if (tid == 0) sh_first = B;
-    __syncthreads();
-    for (int s = tid; s < B; s += IDX_THREADS)
-        if (cu[s + 1] - cu[s] > 0) atomicMin(&sh_first, s);
-    __syncthreads();
     const int s0 = sh_first;
-    for (int s = tid; s < B; s += IDX_THREADS) {
-        int len = cu[s + 1] - cu[s];
-        mis[s] = -1;
-        if (len == 0 || s == s0) {
-            bdep[s] = 0;      // leader from depth 0 (or empty)
-            ldr[s] = -1;
-        } else {
-            bdep[s] = -1;     // -1 marks an active follower
-            ldr[s] = s0;
-            dep[s] = 0;
+    for (int base = 0; base < B; base += BATCH * IDX_THREADS) {
+        if (B > BATCH * IDX_THREADS) fetch(base);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int s = base + u * IDX_THREADS + tid, len = c1[u] - c0[u];
+            if (s >= B) continue;
+            if (len == 0 || s == s0) {
+                bdep[s] = 0;      // leader from depth 0 (or empty)
+                ldr[s] = -1;
+                mis[s] = -1;
+            } else {
+                bdep[s] = f[u] == len ? len : -1;       // -1 marks an active follower; else (as in step 1 below) it ran out of tokens
+                ldr[s] = f[u] == len ? -1 : s0;
+                mis[s] = f[u] == len ? -1 : f[u];
+                dep[s] = 0;
+            }
         }
     }
     __syncthreads();
     return s0;
 }
 
-__global__ __launch_bounds__(IDX_THREADS) void index_init_kernel(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr,
-                                                                 int32_t* ldr, int32_t* dep, int32_t* bdep, int32_t* mis,
-                                                                 int32_t* n_compact_dev) {
-    index_init(cu, B, N, hdr, ldr, dep, bdep, mis, n_compact_dev);
-}
-
 // The comparisons of the first round, one wavefront per sequence over the whole chip: all sequences start by following
-// the first one, so this is where the prefix that a batch shares is read, and most of what there is to compare.
+// the first non-empty one, so this is where the prefix that a batch shares is read, and most of what there is to compare.
+// first[s]: where sequence s leaves it (its length, if it does not).  The chain kernel checks cu_seqlens and reports; here a
+// malformed array must only do no harm, so every sequence's own ends are checked before anything is read through them.
 __global__ __launch_bounds__(256) void index_first_round_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos,
-                                                                const int32_t* __restrict__ cu, int B, int32_t* __restrict__ lead,
-                                                                const int32_t* hdr, int32_t* ldr, int32_t* bdep, int32_t* mis) {
+                                                                const int32_t* __restrict__ cu, int B, int N,
+                                                                int32_t* __restrict__ lead, int32_t* __restrict__ first) {
     const int lane = threadIdx.x & 63;
     const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (s >= B || hdr[0] != 0 || bdep[s] != -1) return;
-    const int l = ldr[s];
-    const int bs = cu[s], bl = cu[l];
-    const int len_s = cu[s + 1] - bs, len_l = cu[l + 1] - bl;
-    const int m = common_prefix<8>(tok, pos, bs, bl, 0, len_s < len_l ? len_s : len_l, l, lead, lane);
-    if (lane == 0) {
-        if (m == len_s) {           // as in the rounds of the chain kernel
-            bdep[s] = len_s;
-            ldr[s] = -1;
-        } else {
-            mis[s] = m;
+    if (s >= B) return;
+    int l = 0;                                      // the first sequence that ends behind 0
+    for (;; l += 64) {
+        if (l >= B) return;
+        const int i = l + lane;
+        const unsigned long long some = __ballot(i < B && cu[i < B ? i + 1 : B] > 0);
+        if (some != 0ull) {
+            l += __ffsll((long long)some) - 1;
+            break;
         }
     }
+    const int bs = cu[s], es = cu[s + 1], bl = cu[l], el = cu[l + 1];
+    if (s == l || bs < 0 || es <= bs || es > N || bl < 0 || el <= bl || el > N) return;
+    const int len_s = es - bs, len_l = el - bl;
+    const int m = common_prefix<8>(tok, pos, bs, bl, 0, len_s < len_l ? len_s : len_l, l, lead, lane);
+    if (lane == 0) first[s] = m;
 }
 
-// first_done: index_init_kernel and index_first_round_kernel ran before.
-// LDS: the grouping table (H slots, a power of two <= LDS_TABLE) lives in LDS instead of the workspace: a probe is an
-// LDS atomic instead of a round trip to L2.
-template <bool LDS>
+// first_done: index_first_round_kernel ran before.
+// SEQ: 0, or the largest B for which the grouping table (H slots, a power of two <= 2 SEQ) and the per-sequence state live in
+// LDS instead of the workspace: what one step leaves for the next is an LDS access away instead of a round trip to L2, and there are ten of those in a round.  (Two sizes: the larger one costs
+// small batches 1 us.)
+// 2048 sequences of 512 tokens, half of them shared: 29 us with the state in the workspace and a pass over all sequences for
+// every wavefront of step 1, 15.6 with both here and a list of the followers that are left.
+template <int SEQ>
 __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
-    int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr, int32_t* dep, int32_t* bdep,
-    int32_t* mis, int32_t* myslot, int32_t* cbase, int32_t* slot_owner_ws, int32_t* slot_min_ws, int H,
+    int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr_ws, int32_t* dep_ws, int32_t* bdep_ws,
+    int32_t* mis_ws, int32_t* myslot_ws, int32_t* cbase, int32_t* slot_owner_ws, int32_t* slot_min_ws, int H,
     int32_t* n_compact_dev, int first_done) {
+    constexpr bool LDS = SEQ > 0;
+    constexpr int LDS_TABLE = 2 * SEQ, LDS_SEQ = SEQ;
+    constexpr int BATCH = LDS && SEQ <= IDX_THREADS ? 1 : 4;           // sequences that a thread fetches the state of at a time
+    typedef typename std::conditional<LDS, uint16_t, int32_t>::type Index;
     __shared__ int sh_wave_tot[IDX_WAVES];
+    __shared__ int sh_left[2];
     __shared__ int32_t sh_table[LDS ? 2 * LDS_TABLE : 1];
+    __shared__ int32_t sh_state[LDS ? 5 * LDS_SEQ : 1];
+    __shared__ uint16_t sh_list[LDS ? LDS_SEQ : 1];
     int32_t* const slot_owner = LDS ? sh_table : slot_owner_ws;
     int32_t* const slot_min = LDS ? sh_table + LDS_TABLE : slot_min_ws;
+    int32_t* const ldr = LDS ? sh_state : ldr_ws;
+    int32_t* const dep = LDS ? sh_state + LDS_SEQ : dep_ws;
+    int32_t* const bdep = LDS ? sh_state + 2 * LDS_SEQ : bdep_ws;
+    int32_t* const mis = LDS ? sh_state + 3 * LDS_SEQ : mis_ws;
+    int32_t* const myslot = LDS ? sh_state + 4 * LDS_SEQ : myslot_ws;
+    Index* const list = LDS ? (Index*)sh_list : (Index*)cbase;         // the followers left; cbase is not needed before the end
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (first_done) {
-        if (hdr[0] != 0) return;
-    } else if (index_init(cu, B, N, hdr, ldr, dep, bdep, mis, n_compact_dev) < 0) {
-        return;
-    }
+    if (tid < 2) sh_left[tid] = 0;
+    if (index_init<BATCH>(cu, B, N, hdr, ldr, dep, bdep, mis, first_done ? mis_ws : nullptr, n_compact_dev) < 0) return;
     for (int h = tid; h < H; h += IDX_THREADS) {
         slot_owner[h] = -1;
         slot_min[h] = 0x7FFFFFFF;
@@ -185,39 +219,64 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     // ---- rounds.  Each active follower's matched depth grows by >= 1 per round, so the loop
     // ends after at most (longest sequence + 1) rounds; N + 2 is a hard upper bound.
     for (int round = 0; round < N + 2; ++round) {
+        for (int base = 0; base < B; base += IDX_THREADS) {
+            const int s = base + tid;
+            const unsigned long long mine = __ballot(s < B && bdep[s < B ? s : 0] == -1);
+            int at = 0;
+            if (lane == 0 && mine != 0ull) at = atomicAdd(&sh_left[round & 1], __popcll(mine));
+            at = __shfl(at, 0, 64) + __popcll(mine & ((1ull << lane) - 1));
+            if (mine >> lane & 1) list[at] = (Index)s;
+        }
+        __syncthreads();
+        const int left = sh_left[round & 1];
+        if (left == 0) break;
+        if (tid == 0) sh_left[(round + 1) & 1] = 0;
+
         // step 1: longest common prefix with the leader, one wavefront per follower
-        int any = 0;
-        if (round == 0 && first_done) {
-            for (int s = tid; s < B; s += IDX_THREADS) any |= bdep[s] == -1;
-        } else
-        for (int s = wave; s < B; s += IDX_WAVES) {
-            if (bdep[s] != -1) continue;
-            any = 1;
-            const int l = ldr[s], st = dep[s];
-            const int bs = cu[s], bl = cu[l];
-            const int len_s = cu[s + 1] - bs, len_l = cu[l + 1] - bl;
-            const int m = common_prefix<LCP_UNROLL>(tok, pos, bs, bl, st, len_s < len_l ? len_s : len_l, l, lead, lane);
-            if (lane == 0) {
-                if (m == len_s) {       // s ran out while still equal to its leader: no new node
-                    bdep[s] = len_s;
-                    ldr[s] = -1;
-                } else {
-                    mis[s] = m;         // s leaves its leader at depth m
+        if (round > 0 || !first_done) {
+            for (int i = wave; i < left; i += IDX_WAVES) {
+                const int s = list[i];
+                const int l = ldr[s], st = dep[s];
+                const int bs = cu[s], bl = cu[l];
+                const int len_s = cu[s + 1] - bs, len_l = cu[l + 1] - bl;
+                const int m = common_prefix<LCP_UNROLL>(tok, pos, bs, bl, st, len_s < len_l ? len_s : len_l, l, lead, lane);
+                if (lane == 0) {
+                    if (m == len_s) {       // s ran out while still equal to its leader: no new node
+                        bdep[s] = len_s;
+                        ldr[s] = -1;
+                    } else {
+                        mis[s] = m;         // s leaves its leader at depth m
+                    }
                 }
             }
+            __syncthreads();
         }
-        if (!__syncthreads_or(any)) break;
 
         // step 2: group the leavers by (leader, depth, token, position) - exact comparison, of full keys only where the
         // 32-bit hashes agree.  dep[] holds the hash meanwhile: the depth it keeps was used in step 1 and step 3 sets
         // the next one.
-        for (int s = tid; s < B; s += IDX_THREADS) {
-            if (bdep[s] != -1) continue;
-            const int m = mis[s], i = cu[s] + m;
-            dep[s] = (int)key_hash(ldr[s], m, tok[i], pos ? pos[i] : m);
+        for (int i0 = tid; i0 < left; i0 += BATCH * IDX_THREADS) {
+            int sq[BATCH], at[BATCH], t[BATCH], pp[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int i = i0 + u * IDX_THREADS;
+                sq[u] = i < left ? (int)list[i] : -1;
+                if (sq[u] >= 0 && bdep[sq[u]] != -1) sq[u] = -1;
+                at[u] = sq[u] >= 0 ? cu[sq[u]] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int m = sq[u] >= 0 ? mis[sq[u]] : 0;
+                t[u] = sq[u] >= 0 ? tok[at[u] + m] : 0;
+                pp[u] = sq[u] >= 0 && pos ? pos[at[u] + m] : m;
+            }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u)
+                if (sq[u] >= 0) dep[sq[u]] = (int)key_hash(ldr[sq[u]], mis[sq[u]], t[u], pp[u]);
         }
         __syncthreads();
-        for (int s = tid; s < B; s += IDX_THREADS) {
+        for (int i = tid; i < left; i += IDX_THREADS) {
+            const int s = list[i];
             if (bdep[s] != -1) continue;
             const int hash = dep[s];
             uint32_t h = (uint32_t)hash & (uint32_t)(H - 1);
@@ -230,8 +289,8 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
                 }
                 if (o == s) break;
                 if (dep[o] == hash) {
-                    const int l = ldr[s], m = mis[s], i = cu[s] + m, j = cu[o] + m;
-                    if (ldr[o] == l && mis[o] == m && tok[j] == tok[i] && (pos == nullptr || pos[j] == pos[i])) break;
+                    const int l = ldr[s], m = mis[s], at = cu[s] + m, ot = cu[o] + m;
+                    if (ldr[o] == l && mis[o] == m && tok[ot] == tok[at] && (pos == nullptr || pos[ot] == pos[at])) break;
                 }
                 h = (h + 1) & (uint32_t)(H - 1);
             }
@@ -241,7 +300,8 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
         __syncthreads();
 
         // step 3: lowest member leads the new node, the others follow it
-        for (int s = tid; s < B; s += IDX_THREADS) {
+        for (int i = tid; i < left; i += IDX_THREADS) {
+            const int s = list[i];
             if (bdep[s] != -1) continue;
             const int c = LDS ? slot_min[myslot[s]] : ld_agent(&slot_min[myslot[s]]);
             const int m = mis[s];
@@ -254,7 +314,8 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
             }
         }
         __syncthreads();
-        for (int s = tid; s < B; s += IDX_THREADS) {
+        for (int i = tid; i < left; i += IDX_THREADS) {
+            const int s = list[i];
             if (mis[s] < 0) continue;
             const int h = myslot[s];
             slot_owner[h] = -1;
@@ -277,6 +338,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
                 bdep[s] = len;
                 set_status(hdr, RADIX_ERR_BAD_SIZE);
             }
+            if (LDS) bdep_ws[s] = b;
             cnt = len - b;
         }
         int incl = cnt;
@@ -304,32 +366,87 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     }
 }
 
-// One thread per original position: turn (leader sequence, offset) into compact ids.
+// U original positions per thread, 64 U consecutive ones per wavefront: turn (leader sequence, offset) into compact ids.  What
+// bounds it is memory latency: the sequence of a position used to be searched by every thread on its own, eleven dependent loads
+// for 2048 sequences.  Now the wavefront searches the sequence of its first position, 64 candidates a step, and the few ends of
+// sequences behind it come with one more load; only where 64 sequences or more end within them every lane searches for
+// itself.  1 050 931 tokens in 2048 sequences: 12.7 -> 7.0 us.
+template <int U>
 __global__ __launch_bounds__(256) void index_finalize_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
     int B, int N, int32_t* __restrict__ I_scatter /* holds leader ids of duplicate positions */,
     int32_t* __restrict__ I_gather, int32_t* hdr, const int32_t* __restrict__ bdep,
     const int32_t* __restrict__ cbase) {
     if (ld_agent(&hdr[0]) == RADIX_ERR_BAD_CU_SEQLENS) return;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    // sequence of j: smallest s with cu[s+1] > j
+    const int lane = threadIdx.x & 63;
+    const int j0 = blockIdx.x * (256 * U) + (threadIdx.x >> 6) * (64 * U);
+    if (j0 >= N) return;
+    const int left = N - j0, j_last = left > 64 * U ? j0 + 64 * U - 1 : N - 1;
+    int t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = 64 * u + lane;
+        t[u] = i < left ? tok[j0 + i] : 0;
+        if (pos != nullptr && i < left) t[u] |= pos[j0 + i];     // negative if one of the two is
+    }
+    // smallest s with cu[s + 1] > j0; it exists, as cu[B] = N
     int lo = 0, hi = B - 1;
     while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (cu[mid + 1] > j) hi = mid; else lo = mid + 1;
+        const int step = (hi - lo) / 64 + 1;                // candidates lo + step (lane + 1) - 1, the last one at or behind hi
+        const int c = lo + step * (lane + 1) - 1;
+        const unsigned long long behind = __ballot(cu[(c < hi ? c : hi) + 1] > j0);
+        const int f = __ffsll((long long)behind) - 1;       // the first candidate whose sequence ends behind j0: hi's does
+        const int nh = lo + step * (f + 1) - 1;
+        lo = lo + step * f;
+        if (nh < hi) hi = nh;
     }
-    const int s = lo;
-    const int p = j - cu[s];
-    if (tok[j] < 0 || (pos != nullptr && pos[j] < 0)) set_status(hdr, RADIX_ERR_BAD_TOKEN);
-    const int b = bdep[s];
-    if (p >= b) {
-        const int c = cbase[s] + (p - b);
-        I_scatter[j] = c;
-        I_gather[c] = j;
+    const int s0 = lo;
+    const int i_end = s0 + 1 + lane;
+    const int end = i_end <= B ? cu[i_end] : 0x7FFFFFFF;    // ends of the sequences s0, s0 + 1, ...
+    const unsigned long long inside = __ballot(end <= j_last);
+    const int n_in = __popcll(inside);
+    int sq[U];
+    if (n_in < 64) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) sq[u] = s0;
+        for (int k = 0; k < n_in; ++k) {
+            const int e = __shfl(end, k, 64);
+#pragma unroll
+            for (int u = 0; u < U; ++u) sq[u] += e - j0 <= 64 * u + lane;
+        }
     } else {
-        const int l = I_scatter[j];
-        I_scatter[j] = cbase[l] + (p - bdep[l]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = 64 * u + lane < left ? j0 + 64 * u + lane : N - 1;
+            int a = s0, b = B - 1;
+            while (a < b) {
+                const int mid = (a + b) >> 1;
+                if (cu[mid + 1] > j) b = mid; else a = mid + 1;
+            }
+            sq[u] = a;
+        }
+    }
+    int p[U], bd[U], cb[U], ld[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = 64 * u + lane, s = sq[u];
+        p[u] = j0 - cu[s] + i;
+        bd[u] = bdep[s];
+        cb[u] = cbase[s];
+        ld[u] = i < left && p[u] < bd[u] ? I_scatter[j0 + i] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (64 * u + lane >= left) continue;
+        const int j = j0 + 64 * u + lane;
+        if (t[u] < 0) set_status(hdr, RADIX_ERR_BAD_TOKEN);
+        if (ld[u] < 0) {
+            const int c = cb[u] + (p[u] - bd[u]);
+            I_scatter[j] = c;
+            I_gather[c] = j;
+        } else {
+            I_scatter[j] = cbase[ld[u]] + (p[u] - bdep[ld[u]]);
+        }
     }
 }
 
@@ -355,13 +472,13 @@ extern "C" int radix_index_workspace_bytes(int32_t max_B, size_t* bytes_out) {
 
 namespace {
 
-// Whether the comparisons of the first round get a launch over the whole chip (two launches more, 3.5 us).  In the chain
+// Whether the comparisons of the first round get a launch over the whole chip (one launch more, 2 us).  In the chain
 // kernel IDX_WAVES followers are compared at a time; every further step of that loop costs 0.9 us and 4 ns per token
-// compared.  How many tokens that will be is not known before; half of the mean length is counted.  A line 1 us above
-// break-even keeps batches that share less from losing.  Measured (us, one kernel / over the chip): 24 sequences of a
-// shared prefix of 16 tokens 37.4 / 39.8, of 2048 tokens 51.8 / 47.4; 48 of 16 tokens 38.9 / 40.8, of 1024 50.5 / 44.3;
-// 64 of 16 tokens 41.0 / 41.6, of 512 48.5 / 43.2; 96 of 16 tokens 43.2 / 42.3; nothing shared, 48 of 300 to 600 tokens
-// 40.4 / 41.4.
+// compared.  How many tokens that will be is not known before; half of the mean length is counted.  The line lies above
+// break-even, which keeps batches that share less from losing.  Measured (us, one kernel / over the chip): 24 sequences of a
+// shared prefix of 16 tokens 30.4 / 32.7, of 512 tokens 34.6 / 33.9, of 2048 tokens 45.5 / 39.1; 48 of 16 tokens 33.0 / 34.2, of
+// 1024 43.9 / 35.7; 64 of 16 tokens 34.9 / 35.7, of 512 43.3 / 36.4; 96 of 16 tokens 36.0 / 34.8; nothing shared, 48 of 450
+// tokens 32.2 / 32.7.
 bool first_round_over_the_chip(int B, int N) {
     if (B <= IDX_WAVES) return false;
     const long long more_steps = (B - 2) / IDX_WAVES;           // B - 1 followers
@@ -385,21 +502,20 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     int32_t* slot_min = slot_owner + H;
 
     // The launches of one call together initialise every word of builder state that they read, so the buffer may hold
-    // anything when the call starts: index_init (in the launch of its own or inside the chain kernel) writes the status word
-    // and the per-sequence arrays, the chain kernel its slot table (in LDS up to LDS_TABLE slots; the tables in the
-    // workspace are for larger batches).
+    // anything when the call starts: index_first_round_kernel writes where the followers leave, the chain kernel the status word,
+    // the per-sequence state and its slot table (in LDS up to LDS_SEQ_MANY sequences; the arrays in the workspace are for larger
+    // batches).
     const int first_done = N > 0 && first_round_over_the_chip(B, N);
-    if (first_done) {
-        hipLaunchKernelGGL(index_init_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr, ldr, dep, bdep,
-                           mis, n_compact_dev);
-        hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B,
-                           I_scatter, hdr, ldr, bdep, mis);
-    }
-    auto chain = H <= LDS_TABLE ? index_chain_kernel<true> : index_chain_kernel<false>;
+    if (first_done)
+        hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B, N,
+                           I_scatter, mis);
+    auto chain = B <= LDS_SEQ_FEW ? index_chain_kernel<LDS_SEQ_FEW> : B <= LDS_SEQ_MANY ? index_chain_kernel<LDS_SEQ_MANY> : index_chain_kernel<0>;
     hipLaunchKernelGGL(chain, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N, I_scatter,
                        hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done);
     if (N > 0) {
-        hipLaunchKernelGGL(index_finalize_kernel, dim3(ceil_div(N, 256)), dim3(256), 0, stream, tok, pos,
+        const bool few = N < 1 << 18;           // workgroups for every CU come first
+        auto finalize = few ? index_finalize_kernel<1> : index_finalize_kernel<4>;
+        hipLaunchKernelGGL(finalize, dim3(ceil_div(N, few ? 256 : 1024)), dim3(256), 0, stream, tok, pos,
                            cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase);
     }
     HIP_TRY(hipGetLastError());

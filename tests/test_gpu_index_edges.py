@@ -1,0 +1,85 @@
+"""The index builder where its launches change: sequences kept in LDS (512, 4096) or in the workspace, positions per thread of the
+map write-out (2^18 tokens), more ends of sequences in a wavefront's positions than it has lanes, empty sequences in front of the
+first one, and malformed cu_seqlens in a batch whose first round runs over the chip."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import radix_index
+from paper_2601_15013_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def check(seqs, positions=None):
+    lens = [len(s) for s in seqs]
+    tok = np.concatenate([np.asarray(s, dtype=np.int32) for s in seqs])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    s_ref, g_ref = radix_index.build_index_trie(tok, cu)
+    pos = None
+    if positions:
+        pos = torch.from_numpy(np.concatenate([np.arange(n) for n in lens]).astype(np.int32) + positions).cuda()
+    ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(len(seqs)))
+    ws.fill_(0x5A)
+    S, G, _, n = binding.radix_build_index(torch.from_numpy(tok).cuda(), pos, torch.from_numpy(cu).cuda(), ws)
+    assert n == len(g_ref)
+    assert np.array_equal(S.cpu().numpy(), s_ref) and np.array_equal(G[:n].cpu().numpy(), g_ref)
+
+
+def batch(rng, B, lo, hi, alphabet=3, empty=0.0):
+    """Sequences over a tiny alphabet: they branch at every level, and many are equal."""
+    return [rng.integers(0, alphabet, 0 if rng.random() < empty else rng.integers(lo, hi + 1)) for _ in range(B)]
+
+
+@pytest.mark.parametrize("B", [511, 512, 513, 1024, 1025, 4095, 4096, 4097])
+@pytest.mark.parametrize("positions", [0, 7])
+def test_around_the_state_kept_in_lds(B, positions):
+    check(batch(np.random.default_rng(B), B, 1, 9, empty=0.1), positions)
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1, 255, 1025])
+def test_around_the_positions_of_a_thread(extra):
+    rng = np.random.default_rng(extra + 5)
+    n = (1 << 18) + extra
+    prefix = rng.integers(0, 50, 300)
+    seqs, left = [], n
+    while left > 0:
+        k = min(left, int(rng.integers(301, 700)))
+        seqs.append(np.concatenate([prefix, rng.integers(0, 50, 400)])[:k])
+        left -= k
+    check(seqs)
+
+
+def test_many_ends_within_a_wavefronts_positions():
+    rng = np.random.default_rng(9)
+    short = batch(rng, 3000, 1, 2, alphabet=40)                       # 64 ends and more within 64 positions and within 256
+    check(short[:150])
+    long = [rng.integers(0, 40, 1 << 17) for _ in range(2)]
+    check(long[:1] + short + long[1:] + short[::-1])
+
+
+@pytest.mark.parametrize("lead", [1, 63, 64, 65, 130])
+def test_empty_sequences_in_front(lead):
+    rng = np.random.default_rng(lead)
+    check([rng.integers(0, 3, 0)] * lead + batch(rng, 200, 40, 90, alphabet=2, empty=0.2))
+
+
+@pytest.mark.parametrize("fault", ["falls", "past the end", "negative", "starts late", "ends early"])
+def test_malformed_ends_in_a_batch_over_the_chip(fault):
+    B, n = 300, 100
+    cu = np.arange(B + 1, dtype=np.int32) * n
+    if fault == "falls":
+        cu[150] = cu[149] - 40
+    elif fault == "past the end":
+        cu[150:299] = B * n + 1000
+    elif fault == "negative":
+        cu[1] = -5
+    elif fault == "starts late":
+        cu[0] = 3
+    else:
+        cu[B] = B * n - 1
+    tok = torch.zeros(B * n, dtype=torch.int32, device="cuda")
+    ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(B))
+    with pytest.raises(binding.RadixError) as e:
+        binding.radix_build_index(tok, None, torch.from_numpy(cu).cuda(), ws)
+    assert e.value.code == -6
