@@ -195,7 +195,9 @@ int radix_workspace_bytes(const radix_model* model, int32_t max_N, int32_t max_B
  *   I_gather     int32[N]    out; only the first N' entries are written
  *   n_compact_dev int32[1]   out (device), N'
  *   n_compact_host           HOST pointer or NULL.  If given, the call waits for the stream,
- *                            stores N' there and returns any device-data error.
+ *                            stores N' there and returns any device-data error.  (The kernels
+ *                            answer through a page of pinned host memory that the first such
+ *                            call of the process makes; without one the two words are copied.)
  *   ws, ws_bytes             workspace of at least radix_index_workspace_bytes(B)
  * B = 0 or N = 0 is valid and yields N' = 0.
  */

@@ -43,6 +43,13 @@ __device__ __forceinline__ int ld_agent(const int* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// status word and N' for the host that waits for them (host: two words of its memory, or null)
+__device__ __forceinline__ void tell_host(int32_t* host, int status, int n_compact) {
+    if (!host) return;
+    __hip_atomic_store(host, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(host + 1, n_compact, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ uint32_t key_hash(int l, int m, int t, int pp) {
     uint64_t x = (((uint64_t)(uint32_t)l << 32) | (uint32_t)m) * 0x9E3779B97F4A7C15ull;
     x ^= ((uint64_t)(uint32_t)pp << 32) | (uint32_t)t;
@@ -189,7 +196,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
     int B, int N, int32_t* __restrict__ lead, int32_t* hdr, int32_t* ldr_ws, int32_t* dep_ws, int32_t* bdep_ws,
     int32_t* mis_ws, int32_t* myslot_ws, int32_t* cbase, int32_t* slot_owner_ws, int32_t* slot_min_ws, int H,
-    int32_t* n_compact_dev, int first_done) {
+    int32_t* n_compact_dev, int first_done, int32_t* host) {
     constexpr bool LDS = SEQ > 0;
     constexpr int LDS_TABLE = 2 * SEQ, LDS_SEQ = SEQ;
     constexpr int BATCH = LDS && SEQ <= IDX_THREADS ? 1 : 4;           // sequences that a thread fetches the state of at a time
@@ -209,7 +216,10 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     Index* const list = LDS ? (Index*)sh_list : (Index*)cbase;         // the followers left; cbase is not needed before the end
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < 2) sh_left[tid] = 0;
-    if (index_init<BATCH>(cu, B, N, hdr, ldr, dep, bdep, mis, first_done ? mis_ws : nullptr, n_compact_dev) < 0) return;
+    if (index_init<BATCH>(cu, B, N, hdr, ldr, dep, bdep, mis, first_done ? mis_ws : nullptr, n_compact_dev) < 0) {
+        if (tid == 0) tell_host(host, RADIX_ERR_BAD_CU_SEQLENS, 0);
+        return;
+    }
     for (int h = tid; h < H; h += IDX_THREADS) {
         slot_owner[h] = -1;
         slot_min[h] = 0x7FFFFFFF;
@@ -337,6 +347,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
                 b = len;
                 bdep[s] = len;
                 set_status(hdr, RADIX_ERR_BAD_SIZE);
+                sh_left[0] = RADIX_ERR_BAD_SIZE;
             }
             if (LDS) bdep_ws[s] = b;
             cnt = len - b;
@@ -363,6 +374,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     if (tid == 0) {
         *n_compact_dev = running;
         hdr[1] = running;
+        tell_host(host, sh_left[0] < 0 ? sh_left[0] : 0, running);
     }
 }
 
@@ -376,7 +388,7 @@ __global__ __launch_bounds__(256) void index_finalize_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
     int B, int N, int32_t* __restrict__ I_scatter /* holds leader ids of duplicate positions */,
     int32_t* __restrict__ I_gather, int32_t* hdr, const int32_t* __restrict__ bdep,
-    const int32_t* __restrict__ cbase) {
+    const int32_t* __restrict__ cbase, int32_t* host) {
     if (ld_agent(&hdr[0]) == RADIX_ERR_BAD_CU_SEQLENS) return;
     const int lane = threadIdx.x & 63;
     const int j0 = blockIdx.x * (256 * U) + (threadIdx.x >> 6) * (64 * U);
@@ -439,7 +451,8 @@ __global__ __launch_bounds__(256) void index_finalize_kernel(
     for (int u = 0; u < U; ++u) {
         if (64 * u + lane >= left) continue;
         const int j = j0 + 64 * u + lane;
-        if (t[u] < 0) set_status(hdr, RADIX_ERR_BAD_TOKEN);
+        if (t[u] < 0 && atomicCAS(hdr, 0, RADIX_ERR_BAD_TOKEN) == 0 && host)
+            __hip_atomic_store(host, RADIX_ERR_BAD_TOKEN, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         if (ld[u] < 0) {
             const int c = cb[u] + (p[u] - bd[u]);
             I_scatter[j] = c;
@@ -485,9 +498,50 @@ bool first_round_over_the_chip(int B, int N) {
     return more_steps * (900 + 4 * (long long)(N / B) / 2) >= 4500;
 }
 
+// Words of pinned host memory that the kernels write a call's status and N' to, so that the host that waits for them needs no copy
+// behind the kernels (2048 x 512 tokens 56 -> 47 us a call, 8 x 48 about 8 us less).  One page for the process, made on the first such
+// call and kept; a call borrows
+// one of its 64 slots, and copies as before if there is none.
+struct HostSlots {
+    static constexpr int SLOT_WORDS = 16;                       // one cache line each
+    std::mutex m;
+    int32_t* page = nullptr;
+    bool made = false;
+    uint64_t taken = 0;
+    int borrow(int32_t** words) {
+        std::lock_guard<std::mutex> lock(m);
+        if (!made) {
+            made = true;
+            // the allocation must not end a capture that some other thread has under way
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+                if (hipHostMalloc((void**)&page, 64 * SLOT_WORDS * sizeof(int32_t), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+                    page = nullptr;
+                    (void)hipGetLastError();
+                }
+                (void)hipThreadExchangeStreamCaptureMode(&mode);
+            }
+        }
+        if (!page || taken == ~0ull) return -1;
+        const int i = __builtin_ctzll(~taken);
+        taken |= 1ull << i;
+        *words = page + i * SLOT_WORDS;
+        return i;
+    }
+    void give_back(int i) {
+        std::lock_guard<std::mutex> lock(m);
+        taken &= ~(1ull << i);
+    }
+};
+HostSlots& host_slots() {
+    static HostSlots* const s = new HostSlots;                  // never destroyed: the runtime may be gone before static objects are
+    return *s;
+}
+
+// may_allocate: false for the entry point that promises not to
 int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_seqlens, int32_t B, int32_t N,
                      int32_t* I_scatter, int32_t* I_gather, int32_t* n_compact_dev, int32_t* n_compact_host,
-                     void* ws, hipStream_t stream) {
+                     void* ws, hipStream_t stream, bool may_allocate) {
     int32_t* hdr = (int32_t*)ws;
     int32_t* base = (int32_t*)((char*)ws + RADIX_WS_HEADER_BYTES);
     const size_t Bn = (size_t)(B > 0 ? B : 1);
@@ -506,27 +560,42 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     // the per-sequence state and its slot table (in LDS up to LDS_SEQ_MANY sequences; the arrays in the workspace are for larger
     // batches).
     const int first_done = N > 0 && first_round_over_the_chip(B, N);
+    int32_t* host = nullptr;
+    const int slot = n_compact_host && may_allocate ? host_slots().borrow(&host) : -1;
     if (first_done)
         hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B, N,
                            I_scatter, mis);
     auto chain = B <= LDS_SEQ_FEW ? index_chain_kernel<LDS_SEQ_FEW> : B <= LDS_SEQ_MANY ? index_chain_kernel<LDS_SEQ_MANY> : index_chain_kernel<0>;
     hipLaunchKernelGGL(chain, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N, I_scatter,
-                       hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done);
+                       hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done, host);
     if (N > 0) {
         const bool few = N < 1 << 18;           // workgroups for every CU come first
         auto finalize = few ? index_finalize_kernel<1> : index_finalize_kernel<4>;
         hipLaunchKernelGGL(finalize, dim3(ceil_div(N, few ? 256 : 1024)), dim3(256), 0, stream, tok, pos,
-                           cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase);
+                           cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase, host);
     }
-    HIP_TRY(hipGetLastError());
+    const hipError_t launched = hipGetLastError();
     if (n_compact_host) {
         int32_t h2[2] = {0, 0};
-        HIP_TRY(hipMemcpyAsync(h2, hdr, sizeof(h2), hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipStreamSynchronize(stream));
+        if (slot >= 0) {
+            // whatever went wrong, the words go back only when nothing on the stream can write them any more
+            const hipError_t waited = hipStreamSynchronize(stream);
+            if (launched == hipSuccess && waited == hipSuccess) {
+                h2[0] = __atomic_load_n(host, __ATOMIC_ACQUIRE);
+                h2[1] = __atomic_load_n(host + 1, __ATOMIC_ACQUIRE);
+            }
+            if (waited == hipSuccess) host_slots().give_back(slot);
+            if (launched != hipSuccess || waited != hipSuccess) return RADIX_ERR_HIP;
+        } else {
+            if (launched != hipSuccess) return RADIX_ERR_HIP;
+            HIP_TRY(hipMemcpyAsync(h2, hdr, sizeof(h2), hipMemcpyDeviceToHost, stream));
+            HIP_TRY(hipStreamSynchronize(stream));
+        }
         *n_compact_host = h2[1];
         if (h2[0] != 0) return h2[0];
+        return RADIX_OK;
     }
-    return RADIX_OK;
+    return launched == hipSuccess ? RADIX_OK : RADIX_ERR_HIP;
 }
 
 int check_index_args(const int32_t* tok, const int32_t* cu_seqlens, int32_t B, int32_t N, const int32_t* I_scatter,
@@ -556,7 +625,7 @@ extern "C" int radix_build_index(const int32_t* tok, const int32_t* pos, const i
     if (((uintptr_t)ws & 255) != 0) return RADIX_ERR_MISALIGNED;
     if (ws_bytes < radix_index_ws_bytes(B)) return RADIX_ERR_WORKSPACE_TOO_SMALL;
     return build_index_impl(tok, pos, cu_seqlens, B, N, I_scatter, I_gather, n_compact_dev, n_compact_host, ws,
-                            (hipStream_t)stream);
+                            (hipStream_t)stream, true);
 }
 
 // ---- the same builder for callers that cannot allocate: its state lives in a static device array
@@ -602,5 +671,5 @@ extern "C" int radix_build_index_static(const int32_t* tok, const int32_t* pos, 
     void* ws = nullptr;
     if ((rc = static_scratch(&ws)) != RADIX_OK) return rc;
     return build_index_impl(tok, pos, cu_seqlens, B, N, I_scatter, I_gather, n_compact_dev, n_compact_host, ws,
-                            (hipStream_t)stream);
+                            (hipStream_t)stream, false);
 }

@@ -1,6 +1,8 @@
 """The index builder where its launches change: sequences kept in LDS (512, 4096) or in the workspace, positions per thread of the
 map write-out (2^18 tokens), more ends of sequences in a wavefront's positions than it has lanes, empty sequences in front of the
 first one, and malformed cu_seqlens in a batch whose first round runs over the chip."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -83,3 +85,34 @@ def test_malformed_ends_in_a_batch_over_the_chip(fault):
     with pytest.raises(binding.RadixError) as e:
         binding.radix_build_index(tok, None, torch.from_numpy(cu).cuda(), ws)
     assert e.value.code == -6
+
+
+def test_threads_and_streams_get_their_own_answers():
+    # N' and the status come back through pinned host memory that calls share
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            n = 50 + 13 * i
+            tok = torch.arange(2 * n, dtype=torch.int32, device="cuda") % n                 # two equal sequences of n tokens
+            cu = torch.tensor([0, n, 2 * n], dtype=torch.int32, device="cuda")
+            bad = tok.clone()
+            bad[n + 3] = -1
+            ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(2))
+            for _ in range(50):
+                if binding.radix_build_index(tok, None, cu, ws, stream=stream)[3] != n:
+                    wrong.append(i)
+                try:
+                    binding.radix_build_index(bad, None, cu, ws, stream=stream)
+                    wrong.append(-i)
+                except binding.RadixError as e:
+                    if e.code != -7:
+                        wrong.append(e.code)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
