@@ -60,7 +60,7 @@ __device__ __forceinline__ uint32_t key_hash(int l, int m, int t, int pp) {
 }
 
 // Comparison of follower s with its leader l from position st on, by one wavefront: the first position where they
-// differ (or the shorter length); lead[] of the equal positions is written on the way.
+// differ (or the shorter length); lead[] of the equal positions is written on the way, if given.
 template <int UNROLL>
 __device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, int bs,
                                              int bl, int st, int lim, int l, int32_t* __restrict__ lead, int lane) {
@@ -82,10 +82,10 @@ __device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, co
             unsigned long long mask = __ballot(neq[u]);
             if (mask != 0ull) {
                 int first = __ffsll((long long)mask) - 1;
-                if (lane < first) lead[bs + p] = l;
+                if (lead && lane < first) lead[bs + p] = l;
                 return p0 + u * 64 + first;
             }
-            lead[bs + p] = l;
+            if (lead) lead[bs + p] = l;
         }
     }
     return lim;
@@ -158,13 +158,28 @@ __device__ __forceinline__ int index_init(const int32_t* __restrict__ cu, int B,
     return s0;
 }
 
+// Validation of cu_seqlens alone, in front of a first round that writes into I_scatter.
+__global__ __launch_bounds__(IDX_THREADS) void index_check_kernel(const int32_t* __restrict__ cu, int B, int N, int32_t* hdr) {
+    int bad = threadIdx.x == 0 && (cu[0] != 0 || cu[B] != N);
+    for (int s = threadIdx.x; s < B; s += IDX_THREADS) {
+        const int c0 = cu[s], c1 = cu[s + 1];
+        if (c0 < 0 || c0 > N || c1 < c0 || c1 > N) bad = 1;
+    }
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) hdr[0] = bad ? RADIX_ERR_BAD_CU_SEQLENS : 0;
+}
+
 // The comparisons of the first round, one wavefront per sequence over the whole chip: all sequences start by following
 // the first non-empty one, so this is where the prefix that a batch shares is read, and most of what there is to compare.
 // first[s]: where sequence s leaves it (its length, if it does not).  The chain kernel checks cu_seqlens and reports; here a
-// malformed array must only do no harm, so every sequence's own ends are checked before anything is read through them.
+// malformed array must only do no harm: every sequence's own ends are checked before anything is read through them, and the maps
+// are not written (lead null: the write-out takes the leader of the positions below first[s] from there).  With lead, the
+// leaders are written and index_check_kernel ran before (checked: its verdict).
 __global__ __launch_bounds__(256) void index_first_round_kernel(const int32_t* __restrict__ tok, const int32_t* __restrict__ pos,
                                                                 const int32_t* __restrict__ cu, int B, int N,
-                                                                int32_t* __restrict__ lead, int32_t* __restrict__ first) {
+                                                                int32_t* __restrict__ lead, int32_t* __restrict__ first,
+                                                                const int32_t* checked) {
+    if (checked && checked[0] != 0) return;
     const int lane = threadIdx.x & 63;
     const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (s >= B) return;
@@ -216,7 +231,8 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     Index* const list = LDS ? (Index*)sh_list : (Index*)cbase;         // the followers left; cbase is not needed before the end
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < 2) sh_left[tid] = 0;
-    if (index_init<BATCH>(cu, B, N, hdr, ldr, dep, bdep, mis, first_done ? mis_ws : nullptr, n_compact_dev) < 0) {
+    const int s0 = index_init<BATCH>(cu, B, N, hdr, ldr, dep, bdep, mis, first_done ? mis_ws : nullptr, n_compact_dev);
+    if (s0 < 0) {
         if (tid == 0) tell_host(host, RADIX_ERR_BAD_CU_SEQLENS, 0);
         return;
     }
@@ -374,6 +390,7 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
     if (tid == 0) {
         *n_compact_dev = running;
         hdr[1] = running;
+        hdr[2] = s0;
         tell_host(host, sh_left[0] < 0 ? sh_left[0] : 0, running);
     }
 }
@@ -386,9 +403,9 @@ __global__ __launch_bounds__(IDX_THREADS) void index_chain_kernel(
 template <int U>
 __global__ __launch_bounds__(256) void index_finalize_kernel(
     const int32_t* __restrict__ tok, const int32_t* __restrict__ pos, const int32_t* __restrict__ cu,
-    int B, int N, int32_t* __restrict__ I_scatter /* holds leader ids of duplicate positions */,
+    int B, int N, int32_t* __restrict__ I_scatter /* holds leader ids of duplicate positions, those below first[s] apart */,
     int32_t* __restrict__ I_gather, int32_t* hdr, const int32_t* __restrict__ bdep,
-    const int32_t* __restrict__ cbase, int32_t* host) {
+    const int32_t* __restrict__ cbase, const int32_t* __restrict__ first, int32_t* host) {
     if (ld_agent(&hdr[0]) == RADIX_ERR_BAD_CU_SEQLENS) return;
     const int lane = threadIdx.x & 63;
     const int j0 = blockIdx.x * (256 * U) + (threadIdx.x >> 6) * (64 * U);
@@ -445,7 +462,8 @@ __global__ __launch_bounds__(256) void index_finalize_kernel(
         p[u] = j0 - cu[s] + i;
         bd[u] = bdep[s];
         cb[u] = cbase[s];
-        ld[u] = i < left && p[u] < bd[u] ? I_scatter[j0 + i] : -1;
+        ld[u] = -1;
+        if (i < left && p[u] < bd[u]) ld[u] = first && p[u] < first[s] ? hdr[2] : I_scatter[j0 + i];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -562,9 +580,12 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     const int first_done = N > 0 && first_round_over_the_chip(B, N);
     int32_t* host = nullptr;
     const int slot = n_compact_host && may_allocate ? host_slots().borrow(&host) : -1;
-    if (first_done)
+    const bool in_lds = B <= LDS_SEQ_MANY;              // then the chain kernel leaves mis[] as the first round wrote it
+    if (first_done) {
+        if (!in_lds) hipLaunchKernelGGL(index_check_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr);
         hipLaunchKernelGGL(index_first_round_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, stream, tok, pos, cu_seqlens, B, N,
-                           I_scatter, mis);
+                           in_lds ? nullptr : I_scatter, mis, in_lds ? nullptr : hdr);
+    }
     auto chain = B <= LDS_SEQ_FEW ? index_chain_kernel<LDS_SEQ_FEW> : B <= LDS_SEQ_MANY ? index_chain_kernel<LDS_SEQ_MANY> : index_chain_kernel<0>;
     hipLaunchKernelGGL(chain, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N, I_scatter,
                        hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done, host);
@@ -572,7 +593,7 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
         const bool few = N < 1 << 18;           // workgroups for every CU come first
         auto finalize = few ? index_finalize_kernel<1> : index_finalize_kernel<4>;
         hipLaunchKernelGGL(finalize, dim3(ceil_div(N, few ? 256 : 1024)), dim3(256), 0, stream, tok, pos,
-                           cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase, host);
+                           cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase, first_done && in_lds ? mis : nullptr, host);
     }
     const hipError_t launched = hipGetLastError();
     if (n_compact_host) {

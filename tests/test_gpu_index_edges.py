@@ -66,9 +66,10 @@ def test_empty_sequences_in_front(lead):
     check([rng.integers(0, 3, 0)] * lead + batch(rng, 200, 40, 90, alphabet=2, empty=0.2))
 
 
+@pytest.mark.parametrize("B", [300, 5000])
 @pytest.mark.parametrize("fault", ["falls", "past the end", "negative", "starts late", "ends early"])
-def test_malformed_ends_in_a_batch_over_the_chip(fault):
-    B, n = 300, 100
+def test_malformed_ends_in_a_batch_over_the_chip(fault, B):
+    n = 100
     cu = np.arange(B + 1, dtype=np.int32) * n
     if fault == "falls":
         cu[150] = cu[149] - 40
@@ -82,9 +83,11 @@ def test_malformed_ends_in_a_batch_over_the_chip(fault):
         cu[B] = B * n - 1
     tok = torch.zeros(B * n, dtype=torch.int32, device="cuda")
     ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(B))
+    S, G = (torch.full((B * n,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
     with pytest.raises(binding.RadixError) as e:
-        binding.radix_build_index(tok, None, torch.from_numpy(cu).cuda(), ws)
+        binding.radix_build_index(tok, None, torch.from_numpy(cu).cuda(), ws, S, G)
     assert e.value.code == -6
+    assert bool((S == -7).all()) and bool((G == -7).all()), "the maps were written"
 
 
 def test_threads_and_streams_get_their_own_answers():
