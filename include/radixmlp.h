@@ -139,7 +139,8 @@ typedef struct radix_fwd_opts {
     int32_t force_dedup;  /* 1: always take the deduplicated path, whatever the threshold says */
     int32_t attention_mode;  /* How scatter -> attention -> gather (Algorithm 1) is executed on the deduplicated path.
                               *  RADIX_ATTN_AUTO (0): the fused kernel where it applies (16-bit operand configurations,
-                              *    compact q|k|v buffer below 4 GB), else the three kernels.
+                              *    compact q|k|v buffer below 4 GB), else the three kernels; with fp32 weights the
+                              *    attention kernel reads through the maps itself (same values bit for bit).
                               *  RADIX_ATTN_THREE_KERNELS (1): scatter of q|k|v to all N rows, attention on the full
                               *    ragged layout, gather of its output: the sequence as Algorithm 1 writes it.
                               *  RADIX_ATTN_FUSED (2): one attention kernel that reads q, k, v of the compact buffer

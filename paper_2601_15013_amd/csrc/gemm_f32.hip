@@ -6,7 +6,8 @@
 // times what one costs.  So the outputs of a tile are TM x TM with TM = 16 R, the smaller the fewer workgroups there
 // are, the k-tile of the small ones is 64 wide, the next one is fetched into registers (16 bytes per lane) while the
 // present one is multiplied, and LDS is read 16 bytes along k.  M 300, K 768, N 256: 27.9 us with R = 2, against 88.5 us
-// with a 64 x 64 tile of scalar LDS reads, k-tiles of 16 and no prefetch.
+// with a 64 x 64 tile of scalar LDS reads, k-tiles of 16 and no prefetch.  SwiGLU needs gate and up columns in one tile: the
+// smallest one is 16 rows of 16 + 16 columns (M 160, N 1536, K 256: 14.1 us with 32 x 32, 7.4 with it).
 // With many rows every CU has several workgroups that hide each other's latency, and what counts is how many fit: the
 // 64 x 64 tile (R = 4) takes k-tiles of 16 (10 KB of LDS and 88 registers against 35 KB and 116 with k-tiles of 64).
 // us with k-tiles of 64 / 32 / 16 / the kernel of scalar reads: M 24000 N 1536 K 256 (gate/up) 410 / 377 / 270 / 345;
@@ -16,55 +17,68 @@
 
 namespace {
 
-// 256 threads = 16 x 16; thread (tx, ty) owns rows ty + 16 i and columns tx + 16 j, i, j < R.
-template <int R, int EPI>
+// 256 threads = 16 x 16; thread (tx, ty) owns rows ty + 16 i, i < RM, and columns tx + 16 j, j < R.
+template <int RM, int R, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        int M, int Nout, int K, float* __restrict__ out) {
     static_assert(EPI != EPI_SWIGLU || R == 4 || R == 2, "gate and up blocks of 32 columns meet in one tile");
     // SwiGLU with a 32-wide tile takes 16 gate columns and the 16 matching up columns, else 64 = 32 gate + 32 up
     constexpr bool PAIR16 = EPI == EPI_SWIGLU && R == 2;
-    constexpr int TK = R == 4 ? 16 : 64, PK = TK + 4;      // k-tile and its pitch in LDS: 16 rows start in 16 different 16-byte bank groups
-    constexpr int TM = 16 * R, LD = TM * TK / 4 / 256;
-    static_assert(LD >= 1 && LD * 256 * 4 == TM * TK, "every thread fetches whole pieces of 16 bytes");
+    constexpr int TK = RM == 4 ? 16 : 64, PK = TK + 4;      // k-tile and its pitch in LDS: 16 rows start in 16 different 16-byte bank groups
+    constexpr int TM = 16 * RM, TN = 16 * R, LA = TM * TK / 4 / 256, LW = TN * TK / 4 / 256;
+    static_assert(LA >= 1 && LA * 256 * 4 == TM * TK && LW * 256 * 4 == TN * TK, "every thread fetches whole pieces of 16 bytes");
     __shared__ float As[TM * PK];
-    __shared__ float Ws[TM * PK];
+    __shared__ float Ws[TN * PK];
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
     const int m0 = blockIdx.y * TM;
     // weight row of tile column c
-    const int n0 = PAIR16 ? ((int)blockIdx.x >> 1) * 64 + ((int)blockIdx.x & 1) * 16 : (int)blockIdx.x * TM;
+    const int n0 = PAIR16 ? ((int)blockIdx.x >> 1) * 64 + ((int)blockIdx.x & 1) * 16 : (int)blockIdx.x * TN;
     auto w_row = [&](int c) { return PAIR16 ? n0 + (c & 15) + (c >> 4) * 32 : n0 + c; };
-    float4 av[LD], wv[LD];
-    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 av[LA], wv[LW];
+    auto piece = [](const float* p, bool inside) {
+        // by value: `inside ? *p : zero` with a named zero selects between two addresses, which puts zero into scratch memory and
+        // makes the load a flat one
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (inside) v = *reinterpret_cast<const float4*>(p);
+        return v;
+    };
     auto fetch = [&](int k0) {                                   // K is a multiple of 4, rows are 16-byte aligned
 #pragma unroll
-        for (int u = 0; u < LD; ++u) {
-            const int e = tid + 256 * u, r = e / (TK / 4), gk = k0 + 4 * (e % (TK / 4));
-            const int gm = m0 + r, gn = w_row(r);
-            av[u] = gm < M && gk < K ? *reinterpret_cast<const float4*>(A + (size_t)gm * K + gk) : zero;
-            wv[u] = gn < Nout && gk < K ? *reinterpret_cast<const float4*>(W + (size_t)gn * K + gk) : zero;
+        for (int u = 0; u < LA; ++u) {
+            const int e = tid + 256 * u, gm = m0 + e / (TK / 4), gk = k0 + 4 * (e % (TK / 4));
+            av[u] = piece(A + (size_t)gm * K + gk, gm < M && gk < K);
+        }
+#pragma unroll
+        for (int u = 0; u < LW; ++u) {
+            const int e = tid + 256 * u, gn = w_row(e / (TK / 4)), gk = k0 + 4 * (e % (TK / 4));
+            wv[u] = piece(W + (size_t)gn * K + gk, gn < Nout && gk < K);
         }
     };
-    float acc[R][R] = {};
+    float acc[RM][R] = {};
     fetch(0);
     for (int k0 = 0; k0 < K; k0 += TK) {
 #pragma unroll
-        for (int u = 0; u < LD; ++u) {
-            const int e = tid + 256 * u, r = e / (TK / 4), k = 4 * (e % (TK / 4));
-            *reinterpret_cast<float4*>(As + r * PK + k) = av[u];
-            *reinterpret_cast<float4*>(Ws + r * PK + k) = wv[u];
+        for (int u = 0; u < LA; ++u) {
+            const int e = tid + 256 * u;
+            *reinterpret_cast<float4*>(As + e / (TK / 4) * PK + 4 * (e % (TK / 4))) = av[u];
+        }
+#pragma unroll
+        for (int u = 0; u < LW; ++u) {
+            const int e = tid + 256 * u;
+            *reinterpret_cast<float4*>(Ws + e / (TK / 4) * PK + 4 * (e % (TK / 4))) = wv[u];
         }
         __syncthreads();
         if (k0 + TK < K) fetch(k0 + TK);
 #pragma unroll
         for (int k = 0; k < TK; k += 4) {
-            float4 a[R], b[R];
+            float4 a[RM], b[R];
 #pragma unroll
-            for (int i = 0; i < R; ++i) a[i] = *reinterpret_cast<const float4*>(As + (ty + 16 * i) * PK + k);
+            for (int i = 0; i < RM; ++i) a[i] = *reinterpret_cast<const float4*>(As + (ty + 16 * i) * PK + k);
 #pragma unroll
             for (int j = 0; j < R; ++j) b[j] = *reinterpret_cast<const float4*>(Ws + (tx + 16 * j) * PK + k);
 #pragma unroll
-            for (int i = 0; i < R; ++i)
+            for (int i = 0; i < RM; ++i)
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
                     acc[i][j] = fmaf(a[i].x, b[j].x, acc[i][j]);
@@ -76,11 +90,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
         __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
+    for (int i = 0; i < RM; ++i) {
         const int gm = m0 + ty + 16 * i;
         if (gm >= M) continue;
         if (EPI == EPI_SWIGLU) {
-            // tile columns [0, TM / 2) are gate, the others the matching up columns
+            // tile columns [0, TN / 2) are gate, the others the matching up columns
 #pragma unroll
             for (int j = 0; j < R / 2; ++j) {
                 const int gn = w_row(tx + 16 * j);              // gate row of W; its up row is gn + 32
@@ -101,15 +115,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     }
 }
 
-template <int R, int EPI>
+template <int RM, int R, int EPI>
 void launch_r(const float* A, const float* W, int M, int Nout, int K, float* out, hipStream_t stream) {
-    const int tiles_m = ceil_div(M, 16 * R);
+    const int tiles_m = ceil_div(M, 16 * RM);
     // SwiGLU columns come in blocks of 64 (32 gate + 32 up)
     const int tiles_n = EPI == EPI_SWIGLU ? ceil_div(Nout, 64) * (4 / R) : ceil_div(Nout, 16 * R);
     // the grid's y extent is 16 bits: taller outputs go in several launches
     for (int t0 = 0; t0 < tiles_m; t0 += 65535) {
-        const int rows0 = t0 * 16 * R, n = tiles_m - t0 < 65535 ? tiles_m - t0 : 65535;
-        hipLaunchKernelGGL((gemm_f32_kernel<R, EPI>), dim3(tiles_n, n), dim3(256), 0, stream, A + (size_t)rows0 * K, W,
+        const int rows0 = t0 * 16 * RM, n = tiles_m - t0 < 65535 ? tiles_m - t0 : 65535;
+        hipLaunchKernelGGL((gemm_f32_kernel<RM, R, EPI>), dim3(tiles_n, n), dim3(256), 0, stream, A + (size_t)rows0 * K, W,
                            M - rows0, Nout, K, out + (size_t)rows0 * (EPI == EPI_SWIGLU ? Nout / 2 : Nout));
     }
 }
@@ -121,9 +135,9 @@ void launch_r(const float* A, const float* W, int M, int Nout, int K, float* out
 template <int EPI>
 void launch_epi(const float* A, const float* W, int M, int Nout, int K, float* out, hipStream_t stream) {
     const long long t64 = (long long)ceil_div(M, 64) * ceil_div(Nout, 64), t32 = (long long)ceil_div(M, 32) * ceil_div(Nout, 32);
-    if (t64 >= 192) launch_r<4, EPI>(A, W, M, Nout, K, out, stream);
-    else if (EPI == EPI_SWIGLU || t32 >= 256) launch_r<2, EPI>(A, W, M, Nout, K, out, stream);
-    else launch_r<EPI == EPI_SWIGLU ? 2 : 1, EPI>(A, W, M, Nout, K, out, stream);
+    if (t64 >= 192) launch_r<4, 4, EPI>(A, W, M, Nout, K, out, stream);
+    else if (t32 >= 256) launch_r<2, 2, EPI>(A, W, M, Nout, K, out, stream);
+    else launch_r<1, EPI == EPI_SWIGLU ? 2 : 1, EPI>(A, W, M, Nout, K, out, stream);      // SwiGLU: gate and up columns in one tile
 }
 
 }  // namespace

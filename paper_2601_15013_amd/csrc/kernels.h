@@ -160,8 +160,15 @@ int launch_gemm_small(const void* A, const void* W, int M, int Nout, int K, int 
 
 // ---- causal varlen GQA attention on the full ragged layout.
 // qkv[N, dq + 2 dkv] rows hold q | k | v of one token; out[N, dq].
-void launch_attention_f32(const float* qkv, const int32_t* cu, int B, int N, int max_seqlen, int n_q_heads,
-                          int n_kv_heads, int hd, float* out, hipStream_t stream);
+// maps.gather != nullptr: qkv holds the compact rows (maps.n_compact of them), read through maps.scatter, and output row r is that
+// of token maps.gather[r] (rows from n_compact on, the padding of a bucketed compact space: of token 0); n_rows output rows.
+struct AttnF32Maps {
+    const int32_t *scatter, *gather;
+    int n_compact;
+    int32_t* status;
+};
+void launch_attention_f32(const float* qkv, const int32_t* cu, int B, int N, int n_rows, int n_q_heads, int n_kv_heads, int hd,
+                          float* out, const AttnF32Maps& maps, hipStream_t stream);
 // 16-bit operands (op_dtype RADIX_BF16 or RADIX_F16), head_dim 128.
 // split_out != 0: out is [N, 2 dq] and a row holds T(o) in columns [0, dq) and T(o - T(o)) in columns [dq, 2 dq).
 // split_in != 0: qkv is [N, 2 (dq + 2 dkv)], a row holds q | k | v (hi parts) and then q | k | v (lo parts).

@@ -313,7 +313,8 @@ int forward_impl(const radix_model* model, const int32_t* tok, const int32_t* po
                  int max_seqlen, const int32_t* Is, const int32_t* Ig, int M, bool dedup, bool fused, int pad_to,
                  float* out, void* ws, size_t ws_bytes, hipStream_t stream) {
     const radix_model_config& c = model->cfg;
-    fused = fused && dedup && c.compute_dtype != RADIX_F32;   // the fused kernel is the MFMA one
+    const bool direct = fused && dedup && c.compute_dtype == RADIX_F32;      // fp32: the attention kernel reads through the maps
+    fused = fused && dedup && !direct;
     // the fused kernel addresses the compact q|k|v buffer with 32-bit byte offsets; beyond 4 GB the three-kernel
     // path (same results) takes over
     if (fused && (long long)M * (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * (long long)esize(c.compute_dtype) *
@@ -426,7 +427,7 @@ int forward_impl(const radix_model* model, const int32_t* tok, const int32_t* po
                 launch_index_select_rows(attn_c, M_valid, nullptr, M - M_valid, attn_row_bytes,
                                          (char*)attn_c + (size_t)M_valid * attn_row_bytes, hdr, stream, 0);
         }
-        if (dedup && !fused) {   // Scatter(q), Scatter(k), Scatter(v): one row copy of the fused q|k|v row
+        if (dedup && !fused && !direct) {   // Scatter(q), Scatter(k), Scatter(v): one row copy of the fused q|k|v row
             TimedScope t(RADIX_TIME_SCATTER, stream);
             launch_index_select_rows(qkv, M_valid, Is, N, (size_t)q2 * row * es, qkv_full, hdr, stream);
         }
@@ -437,14 +438,16 @@ int forward_impl(const radix_model* model, const int32_t* tok, const int32_t* po
                                            dt, stream, hl, qkv_split);
                 if (rc != RADIX_OK) return rc;
             } else {
-                launch_attention_f32((const float*)qkv_full, cu, B, N, max_seqlen, c.n_q_heads, c.n_kv_heads, hd,
-                                     (float*)attn_full, stream);
+                if (direct) launch_attention_f32((const float*)qkv, cu, B, N, M, c.n_q_heads, c.n_kv_heads, hd, (float*)attn_c,
+                                                 {Is, Ig, M_valid, hdr}, stream);
+                else launch_attention_f32((const float*)qkv_full, cu, B, N, N, c.n_q_heads, c.n_kv_heads, hd, (float*)attn_full, {},
+                                          stream);
             }
         }
         // Gather(a): with 16-bit operands the output projection reads its rows through I_gather itself (no copy);
         // the fp32 GEMM, and a full-layout buffer too large for 32-bit row offsets, take the row copy
         const bool gather_in_gemm = dedup && !fused && dt != RADIX_F32 && (long long)N * (long long)attn_row_bytes < (1LL << 32);
-        if (dedup && !fused && !gather_in_gemm) {
+        if (dedup && !fused && !direct && !gather_in_gemm) {
             TimedScope t(RADIX_TIME_GATHER, stream);
             launch_index_select_rows(attn_full, N, Ig, M, attn_row_bytes, attn_c, hdr, stream, M_valid);
         }
@@ -573,7 +576,8 @@ extern "C" int radix_prefill_forward(const radix_model* model, const int32_t* to
     if (opts && opts->pad_compact_to < 0) return RADIX_ERR_BAD_CONFIG;
     const int pad_to = opts ? opts->pad_compact_to : 0;
     if (!dedup) n_compact = N;
-    return forward_impl(model, tok, pos, cu_seqlens, B, N, max_seqlen, I_scatter, I_gather, n_compact, dedup, fused,
+    const bool fused_f32 = model->cfg.compute_dtype == RADIX_F32 && (!opts || opts->attention_mode == RADIX_ATTN_AUTO);
+    return forward_impl(model, tok, pos, cu_seqlens, B, N, max_seqlen, I_scatter, I_gather, n_compact, dedup, fused || fused_f32,
                         pad_to, out, ws, ws_bytes, (hipStream_t)stream);
 }
 
