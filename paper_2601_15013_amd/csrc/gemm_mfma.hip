@@ -30,7 +30,7 @@
 //     wait-count pass makes every later LDS read wait for ALL loads in flight (it cannot prove
 //     that the reads of one slot do not alias the fills of the others), which serialises the
 //     pipeline.  The only vector-memory waits are the explicit ones in front of the barriers.
-//   * LDS holds three k-tiles of A and two of W (all 160 KB for 256x256), one barrier per k-tile; details at the loop.
+//   * LDS holds D + 1 k-tiles of A and D of W (256x256: 3 and 2 in all 160 KB), one barrier per k-tile; details at the loop.
 //   * K is consumed in order and there is no split-K, so an output element is reduced in the
 //     same order wherever its row sits in the matrix: the deduplicated and the no-dedup pass
 //     give bit-identical rows.
@@ -72,7 +72,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
 
     constexpr int EPI_PITCH = 272;                             // epilogue row pitch in bytes (256 + 16 pad)
     constexpr uint32_t EPI_B = NW * 64 * EPI_PITCH;            // 64 rows per wavefront
-    constexpr uint32_t RING_B = 3 * A_SLOT + 2 * B_SLOT;       // 256x256: all 160 KB of a CU
+    // k-tiles from one's first load to its use: as many as LDS holds.  256x256: two, in all 160 KB of a CU
+    constexpr int D = 5 * A_SLOT + 4 * B_SLOT <= 160 * 1024 ? 4 : 4 * A_SLOT + 3 * B_SLOT <= 160 * 1024 ? 3 : 2;
+    constexpr uint32_t RING_B = (D + 1) * A_SLOT + D * B_SLOT;
     __shared__ __attribute__((aligned(16))) char lds_all[RING_B > EPI_B ? RING_B : EPI_B];
 
     // ---- tile assignment (gemm_tile_of: XCD-aware bands of row tiles sweeping the column tiles)
@@ -161,20 +163,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         }
     }
 
-    // ---- LDS: three slots for k-tiles of A, then two for k-tiles of W; tile t lives in A slot t % 3, W slot t % 2
+    // ---- LDS: D + 1 slots for k-tiles of A, then D for k-tiles of W; tile t lives in A slot t % (D + 1), W slot t % D
     // (wave-uniform offsets that rotate as the loop advances).
     const uint32_t lds_base = lds_addr(lds_all);
     uint32_t rd[2];                                             // k-step ks: chunk 4 ks + g of row r
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) rd[ks] = (uint32_t)(r * 128 + (((4 * ks + g) ^ gemm_swz(r)) << 4));
     const char* const a_rd = lds_all + (wm * WTM) * 128;
-    const char* const b_rd = lds_all + 3 * A_SLOT + (wn * WTN) * 128;
+    const char* const b_rd = lds_all + (D + 1) * A_SLOT + (wn * WTN) * 128;
     auto load_a = [&](uint32_t slot, int f) {
         if (A_REM == 0 || f < A_LOADS - 1 || a_extra) dma16(a_ptr, a_off[f], lds_base + slot + 1024 * (wave + NW * f));
         if (f == A_LOADS - 1) a_ptr += GEMM_BK * sizeof(T);
     };
     auto load_b = [&](uint32_t slot, int f) {
-        dma16(w_ptr, w_off[f], lds_base + 3 * A_SLOT + slot + 1024 * (wave + NW * f));
+        dma16(w_ptr, w_off[f], lds_base + (D + 1) * A_SLOT + slot + 1024 * (wave + NW * f));
         if (f == B_LOADS - 1) {
             w_ptr += GEMM_BK * sizeof(T);
             if (--w_left == 0) { w_left = WKT; w_ptr = w_base; }
@@ -221,21 +223,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         }
     };
 
-    uint32_t a_cur = 0, a_nxt = A_SLOT, a_far = 2 * A_SLOT, b_cur = 0, b_nxt = B_SLOT;     // slots of tiles t, t+1, t+2
+    uint32_t a_cur = 0, a_nxt = A_SLOT, a_far = D * A_SLOT, b_cur = 0, b_nxt = B_SLOT;     // slots of tiles t, t+1 and (A) t+D
 #pragma unroll
-    for (int f = 0; f < A_LOADS; ++f) load_a(a_cur, f);
+    for (int t = 0; t < D; ++t) {
+        if (t >= KT) break;
 #pragma unroll
-    for (int f = 0; f < B_LOADS; ++f) load_b(b_cur, f);
-    if (KT > 1) {
+        for (int f = 0; f < A_LOADS; ++f) load_a(t * A_SLOT, f);
 #pragma unroll
-        for (int f = 0; f < A_LOADS; ++f) load_a(a_nxt, f);
-#pragma unroll
-        for (int f = 0; f < B_LOADS; ++f) load_b(b_nxt, f);
-        if (a_extra) wait_vmcnt<A_LOADS + B_LOADS>();
-        else wait_vmcnt<A_LOADS + B_LOADS - 1>();
-    } else {
-        wait_vmcnt<0>();
+        for (int f = 0; f < B_LOADS; ++f) load_b(t * B_SLOT, f);
     }
+    if (KT < D) wait_vmcnt<0>();
+    else if (a_extra) wait_vmcnt<(D - 1) * (A_LOADS + B_LOADS)>();
+    else wait_vmcnt<(D - 1) * (A_LOADS + B_LOADS - 1)>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
@@ -247,12 +246,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     // One k-tile = two k-steps of 32, each of NB slices (the scheduling barriers pin the order): slice j multiplies W
     // fragment j with the MB fragments of A.  W fragments are reloaded in place for the next k-step, one slice after
     // their use; A fragments alternate between two sets.  What is read from LDS in a slice is used NB - 1 slices later.
-    // Global loads, two per slice: A of tile t+2 from the start of the first k-step, into the slot of tile t-1; W of tile
-    // t+2 in the second, into the slot of tile t, right after the barrier that says that every wavefront has read tile t
+    // Global loads, two per slice: A of tile t+D from the start of the first k-step, into the slot of tile t-1; W of tile
+    // t+D in the second, into the slot of tile t, right after the barrier that says that every wavefront has read tile t
     // and has tile t+1 in LDS (spread over the k-step they land too late for the next barrier: 2 to 4 % with zero operands).
     // Every other slice runs its blocks backwards, so that two MFMAs in a row always share an operand: less switching
     // (registers only: 1.99 -> 2.04 PFLOP/s).
-    // MODE 2: tile t+2 exists; 1: only tile t+1; 0: the last tile.
+    // MODE 2: tile t+D exists; 1: tile t+1 does; 0: the last tile.
     constexpr int BAR = NB >= 8 ? 2 : 1;                        // the barrier stands ahead of this slice
     auto k_tile = [&](auto mode_c) {
         constexpr int MODE = decltype(mode_c)::value;
@@ -279,8 +278,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         for (int j = 0; j < NB; ++j) {
             if (MODE > 0 && j == BAR) {
                 if (MODE != 2) wait_vmcnt_and_lds<0>();
-                else if (a_extra) wait_vmcnt_and_lds<A_LOADS>();
-                else wait_vmcnt_and_lds<A_LOADS - 1>();
+                else if (a_extra) wait_vmcnt_and_lds<(D - 1) * A_LOADS + (D - 2) * B_LOADS>();
+                else wait_vmcnt_and_lds<(D - 1) * (A_LOADS - 1) + (D - 2) * B_LOADS>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             }
@@ -308,12 +307,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        const uint32_t a_t = a_cur, b_t = b_cur;
-        a_cur = a_nxt; a_nxt = a_far; a_far = a_t;
-        b_cur = b_nxt; b_nxt = b_t;
+        if constexpr (D == 2) {
+            const uint32_t a_t = a_cur, b_t = b_cur;
+            a_cur = a_nxt; a_nxt = a_far; a_far = a_t;
+            b_cur = b_nxt; b_nxt = b_t;
+        } else {
+            a_far = a_cur;
+            a_cur = a_nxt; a_nxt = a_nxt == D * A_SLOT ? 0u : a_nxt + A_SLOT;
+            b_cur = b_nxt; b_nxt = b_nxt == (D - 1) * B_SLOT ? 0u : b_nxt + B_SLOT;
+        }
     };
-    for (int t = 0; t + 2 < KT; ++t) k_tile(std::integral_constant<int, 2>());
-    if (KT > 1) k_tile(std::integral_constant<int, 1>());
+    int t = 0;
+    for (; t + D < KT; ++t) k_tile(std::integral_constant<int, 2>());
+    if (D == 2) {
+        if (KT > 1) k_tile(std::integral_constant<int, 1>());
+    } else {
+        for (; t + 1 < KT; ++t) k_tile(std::integral_constant<int, 1>());
+    }
     k_tile(std::integral_constant<int, 0>());
     __builtin_amdgcn_s_barrier();     // every load has landed (the last waits were for all of them); wait until every
                                       // wavefront is done with the slots
@@ -546,14 +556,15 @@ int launch_cfg(const void* A, const void* W, int M, int Nout, int K, int w_k, in
         if (epilogue == EPI_RESIDUAL) RADIX_LAUNCH(EPI_RESIDUAL, false);
         if (epilogue == EPI_SWIGLU) RADIX_LAUNCH(EPI_SWIGLU, false);
         if (epilogue == EPI_SWIGLU_SPLIT) RADIX_LAUNCH(EPI_SWIGLU_SPLIT, false);
-        if (epilogue == EPI_STORE_F32) RADIX_LAUNCH(EPI_STORE_F32, false);
+        if constexpr (BN == 256)            // 256x128: gemm_small.hip
+            if (epilogue == EPI_STORE_F32) RADIX_LAUNCH(EPI_STORE_F32, false);
         }
         if constexpr (ROPE) {
             if (epilogue == EPI_QKV_ROPE) RADIX_LAUNCH(EPI_QKV_ROPE, false);
             if (epilogue == EPI_QKV_ROPE_SPLIT) RADIX_LAUNCH(EPI_QKV_ROPE_SPLIT, false);
         }
     }
-    if constexpr (FOLDED && ROPE && !EIGHT)
+    if constexpr (FOLDED && ROPE && !PLAIN)
         if (epilogue == EPI_RESIDUAL_NORM) RADIX_LAUNCH(EPI_RESIDUAL_NORM, false);
 #undef RADIX_LAUNCH
     return RADIX_ERR_UNSUPPORTED;
@@ -585,9 +596,8 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     if (variant == 0) {
         const int n_cu = device_cus();
         struct Shape { int variant, bm, bn, wave_cols; double fixed_us, ktile_us; };
-        static const Shape shapes[5] = {{4, 256, 256, 128, 8.0, 0.832}, {1, 256, 256, 128, 9.0, 0.83},
-                                        {5, 128, 256, 64, 6.5, 0.54},   {3, 128, 256, 128, 7.0, 0.57},
-                                        {2, 128, 128, 64, 5.0, 0.29}};
+        static const Shape shapes[4] = {{4, 256, 256, 128, 8.0, 0.832}, {1, 256, 256, 128, 9.0, 0.83},
+                                        {3, 128, 256, 128, 6.5, 0.54}, {2, 128, 128, 64, 5.0, 0.29}};
         double best = 0.0;
         for (const Shape& sh : shapes) {
             if (Nout % sh.bn != 0) continue;
@@ -611,16 +621,15 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     if (variant == 23 && rope) return launch_cfg<DT, 192, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 23) return launch_cfg<DT, 192, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 24) return launch_cfg<DT, 224, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
-    if (variant == 5 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 4 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 1 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
-    if (variant == 3 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
-    return launch_cfg<DT, 128, 128, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 3 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    return launch_cfg<DT, 128, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
 }
 
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
 // in rounds.  Where that is one, a round costs fixed_us + epi_us (first loads, epilogue, by what it writes: 16-bit rows, q|k|v
-// heads, fp32 rows) and, per 64 columns of K, step_us + share_us times the share of the CUs that it occupies (the clock and
+// heads, fp32 rows added to, fp32 rows written, which short_k does not tell apart) and, per 64 columns of K, step_us + share_us times the share of the CUs that it occupies (the clock and
 // the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
 // 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us if that is more.
 // A launch that does not fill its last round pays for it in full, until there are many rounds.
@@ -628,7 +637,9 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 // of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about:
 //   long_k, K >= 1024: 336 (product, row count) pairs of the four projections of the 0.6B, 4B and 8B shapes and four others
 //     (K 1024 .. 12288), M 8 .. 50000, weights from HBM: within 3 % (large tiles) to 13 % (the smallest) of a launch; the tile
-//     they pick takes 0.5 % longer than the best one (a tenth of them more than 1 %, the worst 23 %).
+//     they pick takes 0.5 % longer than the best one (a tenth of them more than 1 %, the worst 23 %).  Written fp32 rows from
+//     60 more (heads of 151936 columns, K 1024 .. 4096, and N 8192, M 8 .. 4500): 0.4 %, the worst 10 %.  They leave 256x128 tiles
+//     through LDS (gemm_small.hip): 151936 columns, K 1024, M 1000: 421 us, straight from the accumulators 592.
 //   short_k: 23 products of K 64 .. 768 at 25 row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
 //     takes 2.4 % (K 64 and 128), 1.3 % (256 to 384) and 0.7 % (512 to 768) longer than the best, where long_k's pick took 13,
 //     10 and 6 %; bf16 operands, not in the fit, 2.7, 1.2 and 0.7 %.
@@ -636,33 +647,33 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 // empty: M 8300, N 1024: K 3072 70.1 / 57.3 us (256 / 160 rows), K 2048 54.4 / 43.0; M 5000, N 7168, K 5120: 338 / 294 (192 rows);
 // 129 of the 336 pairs have one of the three as their best.  Their constants are 2 % above the fit: among many estimates one that
 // is low by chance would win, and the older tiles are the safer choice.
-struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[3]; };
+struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[4]; };
 struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
 constexpr int LONG_K = 1024;
 constexpr TileCost NOT_SHORT = {};                  // never chosen at short rows (tile_usable)
 const TileShape tile_shapes[] = {
-    { 4, 256, 256, 1, {1.95,  4.74, 0.776, 0.714, {0.37, 6.56, 12.93}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
-    {11,  32,  16, 3, {2.00,  0.00, 0.113, 0.079, {0.62, 0.50,  0.00}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
-    {12,  32,  32, 2, {1.74,  0.00, 0.130, 0.110, {0.51, 0.50,  0.00}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
-    {13,  32, 128, 2, {1.74,  0.00, 0.339, 0.244, {0.99, 0.46,  0.00}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
-    {14,  32,  64, 2, {1.61,  0.00, 0.191, 0.157, {1.89, 6.30,  0.00}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
-    {15,  64,  32, 2, {1.09,  0.00, 0.183, 0.151, {1.00, 1.00,  0.17}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
-    {16,  64,  64, 2, {3.13,  0.00, 0.084, 0.214, {0.17, 0.55,  0.00}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
-    {17,  64, 128, 2, {1.88,  0.00, 0.443, 0.334, {0.36, 0.79,  0.00}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
-    {18, 128, 128, 1, {1.75,  2.63, 0.367, 0.155, {0.48, 2.12,  1.46}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
-    {19, 128, 256, 1, {3.29,  3.58, 0.598, 0.306, {0.10, 5.33,  2.45}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
-    {20, 256, 128, 1, {2.40,  2.15, 0.551, 0.295, {0.34, 9.36,  6.02}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
-    {22, 160, 256, 1, {3.44,  2.44, 0.663, 0.411, {0.33, 0.51,  6.95}}, NOT_SHORT},
-    {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41}}, NOT_SHORT},
-    {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22}}, NOT_SHORT},
+    { 4, 256, 256, 1, {1.95,  4.74, 0.776, 0.714, {0.37, 6.56, 12.93,  4.25}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
+    {11,  32,  16, 3, {2.00,  0.00, 0.113, 0.079, {0.62, 0.50,  0.00,  0.70}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
+    {12,  32,  32, 2, {1.74,  0.00, 0.130, 0.110, {0.51, 0.50,  0.00,  1.50}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
+    {13,  32, 128, 2, {1.74,  0.00, 0.339, 0.244, {0.99, 0.46,  0.00,  2.20}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
+    {14,  32,  64, 2, {1.61,  0.00, 0.191, 0.157, {1.89, 6.30,  0.00,  1.80}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
+    {15,  64,  32, 2, {1.09,  0.00, 0.183, 0.151, {1.00, 1.00,  0.17,  1.15}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
+    {16,  64,  64, 2, {3.13,  0.00, 0.084, 0.214, {0.17, 0.55,  0.00,  1.10}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
+    {17,  64, 128, 2, {1.88,  0.00, 0.443, 0.334, {0.36, 0.79,  0.00,  2.50}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
+    {18, 128, 128, 1, {1.75,  2.63, 0.367, 0.155, {0.48, 2.12,  1.46,  3.40}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
+    {19, 128, 256, 1, {3.29,  3.58, 0.598, 0.306, {0.10, 5.33,  2.45,  0.85}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
+    {20, 256, 128, 1, {2.40,  2.15, 0.551, 0.295, {0.34, 9.36,  6.02,  6.80}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
+    {22, 160, 256, 1, {3.44,  2.44, 0.663, 0.411, {0.33, 0.51,  6.95,  3.60}}, NOT_SHORT},
+    {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41,  3.35}}, NOT_SHORT},
+    {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22,  3.90}}, NOT_SHORT},
 };
 // 128 to 224 rows of 256 columns are one variant outside: 19
 int variant_outside(int variant) { return variant >= 22 && variant <= 24 ? 19 : variant; }
 
 double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
     const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
-    const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 :
-                                epilogue == EPI_RESIDUAL || epilogue == EPI_STORE_F32 ? 2 : 0];
+    const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 : epilogue == EPI_RESIDUAL ? 2 :
+                                epilogue == EPI_STORE_F32 ? (K >= LONG_K ? 3 : 2) : 0];
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
     const double kt = K / 64;
     if (sh.per_cu == 1) {
@@ -682,10 +693,8 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
 
 bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
     if (Nout % sh.bn != 0) return false;
-    if (sh.variant >= 22) {                         // chosen where they were measured: long rows, fp32 rows of any width, 16-bit ones
-        const bool fp32 = epilogue == EPI_RESIDUAL || epilogue == EPI_STORE_F32;
-        if (K < LONG_K || (!fp32 && Nout < 2048)) return false;
-    }
+    // chosen where they were measured: long rows of A; results added to fp32 rows of any width, others from 4096 columns on
+    if (sh.variant >= 22 && (K < LONG_K || (epilogue != EPI_RESIDUAL && Nout < 2048))) return false;
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
         return sh.bn % 128 == 0 && sh.variant != 22 && sh.variant != 24;
     if (epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_SPLIT) return sh.bn % 64 == 0;           // gate/up pairs
@@ -760,7 +769,7 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
     if (folded && variant >= 11) return RADIX_ERR_UNSUPPORTED;
     const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
     auto launch = [&](int v, const void* a, int m, void* o) -> int {
-        if ((v >= 11 && v < 20) || (v == 20 && rope)) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
+        if ((v >= 11 && v < 20) || (v == 20 && (rope || epilogue == EPI_STORE_F32))) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
         if (op_dtype == RADIX_BF16) return launch_dt<RADIX_BF16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         return RADIX_ERR_UNSUPPORTED;
