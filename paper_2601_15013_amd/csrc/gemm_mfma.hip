@@ -693,7 +693,8 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
 
 bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
     if (Nout % sh.bn != 0) return false;
-    // chosen where they were measured: long rows of A; results added to fp32 rows of any width, others from 4096 columns on
+    // chosen where they were measured: long rows of A; results added to fp32 rows of any width, others of 2048 columns and more
+    // (measured from 4096 on)
     if (sh.variant >= 22 && (K < LONG_K || (epilogue != EPI_RESIDUAL && Nout < 2048))) return false;
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
         return sh.bn % 128 == 0 && sh.variant != 22 && sh.variant != 24;
