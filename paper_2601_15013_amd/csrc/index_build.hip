@@ -91,6 +91,22 @@ __device__ __forceinline__ int common_prefix(const int32_t* __restrict__ tok, co
     return lim;
 }
 
+// Smallest s in [lo, hi] with cu[s + 1] > x, which holds at hi, by a wavefront: 64 candidates a step.  (A malformed cu gives
+// some s of the range.)
+__device__ __forceinline__ int first_end_behind(const int32_t* __restrict__ cu, int lo, int hi, int x, int lane) {
+    while (lo < hi) {
+        const int step = (hi - lo) / 64 + 1;                // candidates lo + step (lane + 1) - 1, the last one at or behind hi
+        const int c = lo + step * (lane + 1) - 1;
+        const unsigned long long behind = __ballot(cu[(c < hi ? c : hi) + 1] > x);
+        if (behind == 0ull) break;
+        const int f = __ffsll((long long)behind) - 1;       // the first candidate whose sequence ends behind x
+        const int nh = lo + step * (f + 1) - 1;
+        lo = lo + step * f;
+        if (nh < hi) hi = nh;
+    }
+    return lo;
+}
+
 // Validation of cu_seqlens (before anything is dereferenced through it) and the initial state, by one workgroup.
 // Returns the first non-empty sequence, which everybody else follows, or -1 on a malformed array.
 // first: null, or what index_first_round_kernel found: where a follower leaves the first sequence.
@@ -183,16 +199,10 @@ __global__ __launch_bounds__(256) void index_first_round_kernel(const int32_t* _
     const int lane = threadIdx.x & 63;
     const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (s >= B) return;
-    int l = 0;                                      // the first sequence that ends behind 0
-    for (;; l += 64) {
-        if (l >= B) return;
-        const int i = l + lane;
-        const unsigned long long some = __ballot(i < B && cu[i < B ? i + 1 : B] > 0);
-        if (some != 0ull) {
-            l += __ffsll((long long)some) - 1;
-            break;
-        }
-    }
+    // the first sequence that ends behind 0: one of the first 64, or searched (walked to by every wavefront, a run of empty
+    // sequences in front made the launch quadratic: 999 800 of them 425 ms)
+    const unsigned long long some = __ballot(cu[lane < B ? lane + 1 : B] > 0);
+    const int l = some != 0ull ? __ffsll((long long)some) - 1 : first_end_behind(cu, 0, B - 1, 0, lane);
     const int bs = cu[s], es = cu[s + 1], bl = cu[l], el = cu[l + 1];
     if (s == l || bs < 0 || es <= bs || es > N || bl < 0 || el <= bl || el > N) return;
     const int len_s = es - bs, len_l = el - bl;
@@ -418,18 +428,7 @@ __global__ __launch_bounds__(256) void index_finalize_kernel(
         t[u] = i < left ? tok[j0 + i] : 0;
         if (pos != nullptr && i < left) t[u] |= pos[j0 + i];     // negative if one of the two is
     }
-    // smallest s with cu[s + 1] > j0; it exists, as cu[B] = N
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        const int step = (hi - lo) / 64 + 1;                // candidates lo + step (lane + 1) - 1, the last one at or behind hi
-        const int c = lo + step * (lane + 1) - 1;
-        const unsigned long long behind = __ballot(cu[(c < hi ? c : hi) + 1] > j0);
-        const int f = __ffsll((long long)behind) - 1;       // the first candidate whose sequence ends behind j0: hi's does
-        const int nh = lo + step * (f + 1) - 1;
-        lo = lo + step * f;
-        if (nh < hi) hi = nh;
-    }
-    const int s0 = lo;
+    const int s0 = first_end_behind(cu, 0, B - 1, j0, lane);       // it exists, as cu[B] = N
     const int i_end = s0 + 1 + lane;
     const int end = i_end <= B ? cu[i_end] : 0x7FFFFFFF;    // ends of the sequences s0, s0 + 1, ...
     const unsigned long long inside = __ballot(end <= j_last);

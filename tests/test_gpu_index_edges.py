@@ -66,6 +66,35 @@ def test_empty_sequences_in_front(lead):
     check([rng.integers(0, 3, 0)] * lead + batch(rng, 200, 40, 90, alphabet=2, empty=0.2))
 
 
+@pytest.mark.parametrize("lead", [63, 64, 4000, 4200, 70000])
+def test_long_runs_of_empty_sequences(lead):
+    rng = np.random.default_rng(lead)
+    own = batch(rng, 130, 40, 90, alphabet=2)
+    none = [rng.integers(0, 3, 0)]
+    check(none * lead + own[:70] + none * 65 + own[70:])
+
+
+def test_empty_sequences_in_front_cost_no_more_than_behind():
+    # every wavefront of the first round looks for the first sequence with tokens
+    k, B = 200, 400000
+    seqs = [np.concatenate([np.arange(20), [i], np.arange(10)]) for i in range(k)]
+    tok = torch.from_numpy(np.concatenate(seqs).astype(np.int32)).cuda()
+    ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(B))
+    took = {}
+    for kind, lens in (("front", [0] * (B - k) + [31] * k), ("behind", [31] * k + [0] * (B - k))):
+        cu = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)).cuda()
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            binding.radix_build_index(tok, None, cu, ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[kind] = min(times)
+    assert took["front"] < 3 * took["behind"], took        # walked to, 999 800 of them took 145 times as long
+
+
 @pytest.mark.parametrize("B", [300, 5000])
 @pytest.mark.parametrize("fault", ["falls", "past the end", "negative", "starts late", "ends early"])
 def test_malformed_ends_in_a_batch_over_the_chip(fault, B):
