@@ -48,6 +48,8 @@ int radix_timing_collect(float* total_ms_host, int32_t* launches_host);
  * radix_debug_gemm_plan_us: the time that the cost model behind that choice gives such a split (v2 is not read if m1 == M).
  * radix_debug_index_first_round: 1 if the index builder spreads its first round over the whole chip for B sequences of N
  * tokens together, 0 if one workgroup runs it, or a negative status.
+ * radix_debug_index_host_slots: how many of the words of pinned memory through which radix_build_index answers are free (64 when
+ * no call is running), 0 before the first call made them.
  */
 int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1, int32_t* bn1,
                           int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2);
@@ -57,6 +59,7 @@ int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int32_t epilogu
 int radix_debug_gemm_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n, int32_t band, int32_t* tm, int32_t* tn);
 int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles_n);
 int radix_debug_index_first_round(int32_t B, int32_t N);
+int radix_debug_index_host_slots(void);
 
 /*
  * One 16-bit product out = epilogue(A[M, K] W[Nout, w_k]^T) on the device in tiles of shape `variant` (as reported by

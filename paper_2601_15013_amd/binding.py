@@ -26,7 +26,7 @@ EXPORTS = (
     "radix_index_select_rows", "radix_device_status", "radix_status_string",
     "radix_timing_enable", "radix_timing_collect", "radix_debug_gemm_tile", "radix_debug_gemm_band", "radix_debug_gemm_plan", "radix_debug_gemm_plan_cus",
     "radix_debug_gemm_plan_us",
-    "radix_debug_index_first_round", "radix_debug_gemm_run",
+    "radix_debug_index_first_round", "radix_debug_index_host_slots", "radix_debug_gemm_run",
 )
 
 TIMING_CATEGORIES = ("gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "attention", "scatter", "gather", "rowops",

@@ -549,10 +549,22 @@ struct HostSlots {
         std::lock_guard<std::mutex> lock(m);
         taken &= ~(1ull << i);
     }
+    int available() {
+        std::lock_guard<std::mutex> lock(m);
+        return page ? 64 - __builtin_popcountll(taken) : 0;
+    }
 };
 HostSlots& host_slots() {
     static HostSlots* const s = new HostSlots;                  // never destroyed: the runtime may be gone before static objects are
     return *s;
+}
+
+// A call inside a capture cannot wait (it fails where it tries to): no slot for it, or that one could never be given back.
+bool waiting_is_possible(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
 
 // may_allocate: false for the entry point that promises not to
@@ -578,7 +590,7 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     // batches).
     const int first_done = N > 0 && first_round_over_the_chip(B, N);
     int32_t* host = nullptr;
-    const int slot = n_compact_host && may_allocate ? host_slots().borrow(&host) : -1;
+    const int slot = n_compact_host && may_allocate && waiting_is_possible(stream) ? host_slots().borrow(&host) : -1;
     const bool in_lds = B <= LDS_SEQ_MANY;              // then the chain kernel leaves mis[] as the first round wrote it
     if (first_done) {
         if (!in_lds) hipLaunchKernelGGL(index_check_kernel, dim3(1), dim3(IDX_THREADS), 0, stream, cu_seqlens, B, N, hdr);
@@ -634,6 +646,8 @@ extern "C" int radix_debug_index_first_round(int32_t B, int32_t N) {
     if (B <= 0 || N <= 0) return RADIX_ERR_BAD_SIZE;
     return first_round_over_the_chip(B, N) ? 1 : 0;
 }
+
+extern "C" int radix_debug_index_host_slots(void) { return host_slots().available(); }
 
 extern "C" int radix_build_index(const int32_t* tok, const int32_t* pos, const int32_t* cu_seqlens,
                                  int32_t B, int32_t N, int32_t* I_scatter, int32_t* I_gather,

@@ -1,6 +1,7 @@
 """The index builder where its launches change: sequences kept in LDS (512, 4096) or in the workspace, positions per thread of the
 map write-out (2^18 tokens), more ends of sequences in a wavefront's positions than it has lanes, empty sequences in front of the
 first one, and malformed cu_seqlens in a batch whose first round runs over the chip."""
+import ctypes as C
 import threading
 
 import numpy as np
@@ -148,3 +149,26 @@ def test_threads_and_streams_get_their_own_answers():
     for t in threads:
         t.join()
     assert not wrong
+
+
+def test_calls_that_fail_inside_a_capture_keep_no_words():
+    lib = binding.load_library()
+    n = 300
+    tok = torch.arange(2 * n, dtype=torch.int32, device="cuda") % n
+    cu = torch.tensor([0, n, 2 * n], dtype=torch.int32, device="cuda")
+    ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(2))
+    S, G, n_dev, _ = binding.radix_build_index(tok, None, cu, ws)
+    torch.cuda.synchronize()
+    assert lib.radix_debug_index_host_slots() == 64
+    n_host = C.c_int32(-1)
+    p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    for _ in range(3):
+        stream, graph = C.c_void_p(), C.c_void_p()
+        assert lib.hipStreamCreate(C.byref(stream)) == 0
+        assert lib.hipStreamBeginCapture(stream, 2) == 0                # relaxed
+        rc = lib.radix_build_index(p(tok), None, p(cu), 2, 2 * n, p(S), p(G), p(n_dev), C.byref(n_host), p(ws), ws.numel(), stream)
+        lib.hipStreamEndCapture(stream, C.byref(graph))                 # the wait has ended it: no graph
+        lib.hipGetLastError()
+        assert rc < 0 and n_host.value == -1
+    assert lib.radix_debug_index_host_slots() == 64
+    assert binding.radix_build_index(tok, None, cu, ws)[3] == n
