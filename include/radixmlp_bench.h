@@ -44,6 +44,7 @@ int radix_timing_collect(float* total_ms_host, int32_t* launches_host);
  * rows of K elements (>= 1), or a negative status.
  * radix_debug_gemm_plan: the tiles a 16-bit product C[M, Nout] = A[M, K] W^T with epilogue code `epilogue` runs in: rows
  * [0, *m1) in tiles of shape *v1 (*bm1 x *bn1), the rest, if *m1 < M, in tiles of shape *v2 (*bm2 x *bn2).
+ * Shapes: 4 is 256x256, 22 to 24 are 160, 192 and 224 rows of 256 columns, 20 is 256x128, 11 to 19 are the smaller ones.
  * radix_debug_gemm_plan_cus: the same for a device (a partition) of `cus` CUs instead of the present one.
  * radix_debug_gemm_plan_us: the time that the cost model behind that choice gives such a split (v2 is not read if m1 == M).
  * radix_debug_index_first_round: 1 if the index builder spreads its first round over the whole chip for B sequences of N

@@ -667,9 +667,6 @@ const TileShape tile_shapes[] = {
     {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41,  3.35}}, NOT_SHORT},
     {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22,  3.90}}, NOT_SHORT},
 };
-// 128 to 224 rows of 256 columns are one variant outside: 19
-int variant_outside(int variant) { return variant >= 22 && variant <= 24 ? 19 : variant; }
-
 double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
     const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
     const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 : epilogue == EPI_RESIDUAL ? 2 :
@@ -820,8 +817,8 @@ extern "C" int radix_debug_gemm_plan_cus(int32_t cus, int32_t M, int32_t Nout, i
         if (sh.variant == p.v1) { *bm1 = sh.bm; *bn1 = sh.bn; }
         if (sh.variant == p.v2) { *bm2 = sh.bm; *bn2 = sh.bn; }
     }
-    *v1 = variant_outside(p.v1);
-    *v2 = variant_outside(p.v2);
+    *v1 = p.v1;
+    *v2 = p.v2;
     return p.v1 ? RADIX_OK : RADIX_ERR_UNSUPPORTED;
 }
 extern "C" int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
@@ -832,17 +829,11 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
                                         double* us) {
     if (!us) return RADIX_ERR_NULL_POINTER;
     if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0 || m1 <= 0 || m1 > M) return RADIX_ERR_BAD_SIZE;
-    double t1 = -1.0, t2 = -1.0;                    // of a variant with several heights the fastest (in front: that divides the rows)
+    double t1 = -1.0, t2 = -1.0;
     for (const TileShape& sh : tile_shapes) {
         if (!tile_usable(sh, Nout, K, epilogue)) continue;
-        if (variant_outside(sh.variant) == v1 && (m1 == M || m1 % sh.bm == 0)) {
-            const double t = tile_time(sh, device_cus(), m1, Nout, K, epilogue);
-            if (t1 < 0.0 || t < t1) t1 = t;
-        }
-        if (m1 < M && variant_outside(sh.variant) == v2) {
-            const double t = tile_time(sh, device_cus(), M - m1, Nout, K, epilogue);
-            if (t2 < 0.0 || t < t2) t2 = t;
-        }
+        if (sh.variant == v1) t1 = tile_time(sh, device_cus(), m1, Nout, K, epilogue);
+        if (m1 < M && sh.variant == v2) t2 = tile_time(sh, device_cus(), M - m1, Nout, K, epilogue);
     }
     if (t1 < 0.0 || (m1 < M && t2 < 0.0)) return RADIX_ERR_UNSUPPORTED;
     *us = m1 < M ? t1 + t2 : t1;

@@ -55,7 +55,8 @@ def test_plan_rejects_bad_sizes(plan):
 PROJECTIONS = [(1024, 2048, RESIDUAL), (1024, 3072, RESIDUAL), (6144, 1024, SWIGLU), (4096, 1024, QKV_ROPE),
                (2560, 4096, RESIDUAL), (2560, 9728, RESIDUAL), (19456, 2560, SWIGLU), (6144, 2560, QKV_ROPE),
                (4096, 4096, RESIDUAL), (4096, 12288, RESIDUAL), (24576, 4096, SWIGLU), (6144, 4096, QKV_ROPE)]
-VARIANTS = {1: 256, 4: 256, 11: 32, 12: 32, 13: 32, 14: 32, 15: 64, 16: 64, 17: 64, 18: 128, 19: 128, 20: 256}      # rows of a tile
+# rows of a tile
+VARIANTS = {1: 256, 4: 256, 11: 32, 12: 32, 13: 32, 14: 32, 15: 64, 16: 64, 17: 64, 18: 128, 19: 128, 20: 256, 22: 160, 23: 192, 24: 224}
 
 
 def test_plan_is_the_fastest_that_the_cost_model_knows(plan):
@@ -68,8 +69,9 @@ def test_plan_is_the_fastest_that_the_cost_model_knows(plan):
 
     for nout, k, epi in PROJECTIONS:
         for m in list(range(257, 20000, 223)) + [7916, 9216, 8672, 939, 658, 33792, 50645]:
-            rc, (v1, bm1, _, m1, v2, _, _) = plan(m, nout, k, epi)
+            rc, (v1, bm1, _, m1, v2, bm2, _) = plan(m, nout, k, epi)
             assert rc == 0
+            assert bm1 == VARIANTS[v1] and (m1 == m or bm2 == VARIANTS[v2]), (m, nout, k)      # the tile named is the tile meant
             t = us(m, nout, k, epi, v1, m1, v2)
             whole = min(us(m, nout, k, epi, v, m, 0) for v in VARIANTS)
             assert t == whole if m1 == m else t < 0.97 * whole, (m, nout, k)
