@@ -590,21 +590,19 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     // costs a fixed part
     // (launch, first loads, epilogue) plus the k-tiles at the rate measured for that shape (microseconds per
     // 32-wide k-tile on MI355X, random fp16 operands): a launch that does not fill its last round pays for it
-    // in full, which is what decides between the shapes for small M * Nout.  Eight wavefronts (two per SIMD,
-    // 256 registers each) lose nothing in the main loop and overlap each other's epilogue and first loads:
-    // 1 to 4 us less per round; the four-wavefront tile is only chosen at K > 16000.
+    // in full, which is what decides between the shapes for small M * Nout.  Consumers run in eight wavefronts (two per SIMD,
+    // 256 registers each).  The epilogue that prepares a norm holds a row block twice and needs a wavefront block 128 columns wide:
+    // four wavefronts of 512 registers, or 128 rows.
     if (variant == 0) {
         const int n_cu = device_cus();
-        struct Shape { int variant, bm, bn, wave_cols; double fixed_us, ktile_us; };
-        static const Shape shapes[4] = {{4, 256, 256, 128, 8.0, 0.832}, {1, 256, 256, 128, 9.0, 0.83},
-                                        {3, 128, 256, 128, 6.5, 0.54}, {2, 128, 128, 64, 5.0, 0.29}};
+        const bool produces = epilogue == EPI_RESIDUAL_NORM, heads = epilogue == EPI_QKV_ROPE;
+        struct Shape { int variant, bm, bn, wave_cols; bool consumer, producer; double fixed_us, ktile_us; };
+        static const Shape shapes[4] = {{4, 256, 256, 128, true, false, 8.0, 0.832}, {1, 256, 256, 128, false, true, 9.0, 0.83},
+                                        {3, 128, 256, 128, true, true, 6.5, 0.54}, {2, 128, 128, 64, true, false, 5.0, 0.29}};
         double best = 0.0;
         for (const Shape& sh : shapes) {
-            if (Nout % sh.bn != 0) continue;
-            if ((epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT || epilogue == EPI_RESIDUAL_NORM) &&
-                sh.wave_cols != 128)
-                continue;                                            // need 128-wide wavefront blocks
-            if (epilogue == EPI_RESIDUAL_NORM && sh.variant == 4) continue;   // that epilogue needs 512 registers
+            if (Nout % sh.bn != 0 || !(produces ? sh.producer : sh.consumer)) continue;
+            if ((heads || produces) && sh.wave_cols != 128) continue;                // need 128-wide wavefront blocks
             const double tiles = (double)ceil_div(M, sh.bm) * (Nout / sh.bn);
             double rounds = tiles / n_cu;
             if (rounds < 8.0) rounds = (double)(long long)(rounds + 0.999999);   // few rounds: the last one counts whole
@@ -613,8 +611,6 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
         }
         if (variant == 0) return RADIX_ERR_UNSUPPORTED;
     }
-    // four wavefronts of 512 registers: for the epilogue that needs them
-    if (variant == 1 && epilogue != EPI_RESIDUAL_NORM) variant = 4;
     const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
     if (variant == 20) return launch_cfg<DT, 256, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 22) return launch_cfg<DT, 160, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
@@ -624,7 +620,8 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
     if (variant == 4 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 1 && Nout % 256 == 0) return launch_cfg<DT, 256, 256, 2, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 3 && Nout % 256 == 0) return launch_cfg<DT, 128, 256, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
-    return launch_cfg<DT, 128, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    if (variant == 2) return launch_cfg<DT, 128, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
+    return RADIX_ERR_UNSUPPORTED;
 }
 
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
@@ -855,7 +852,7 @@ extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int
     if (variant != 0) {
         bool known = false;
         for (const TileShape& sh : tile_shapes)
-            known = known || ((sh.variant == variant || (sh.variant == 4 && variant == 1)) && tile_usable(sh, Nout, LONG_K, epilogue));
+            known = known || (sh.variant == variant && tile_usable(sh, Nout, LONG_K, epilogue));
         if (variant >= 22 && variant <= 24) known = Nout % 256 == 0 && (!rope || variant == 23);
         if (!known) return RADIX_ERR_UNSUPPORTED;
     }

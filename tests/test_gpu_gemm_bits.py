@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 STORE, RESIDUAL, SWIGLU, QKV_ROPE, STORE_F32, SWIGLU_SPLIT, QKV_ROPE_SPLIT = 0, 1, 2, 3, 4, 5, 7
 EPILOGUES = [STORE, RESIDUAL, SWIGLU, QKV_ROPE, STORE_F32, SWIGLU_SPLIT, QKV_ROPE_SPLIT]
 ROPE = (QKV_ROPE, QKV_ROPE_SPLIT)
-TILES = {1: (256, 256), 4: (256, 256), 11: (32, 16), 12: (32, 32), 13: (32, 128), 14: (32, 64), 15: (64, 32), 16: (64, 64),
+TILES = {4: (256, 256), 11: (32, 16), 12: (32, 32), 13: (32, 128), 14: (32, 64), 15: (64, 32), 16: (64, 64),
          17: (64, 128), 18: (128, 128), 19: (128, 256), 20: (256, 128)}
 DTYPES = {"f16": (torch.float16, 2), "bf16": (torch.bfloat16, 1)}
 REFERENCE = 4
@@ -76,7 +76,7 @@ def same_bits(a, b):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("tile,epilogue", [(t, e) for t in sorted(TILES) for e in EPILOGUES if usable(t, e)])
+@pytest.mark.parametrize("tile,epilogue", [(t, e) for t in sorted(TILES) if t != REFERENCE for e in EPILOGUES if usable(t, e)])
 def test_every_tile_gives_the_same_bits(tile, epilogue, dtype):
     bm = TILES[tile][0]
     # K in k-tiles of 64: one, two, an odd number below, at and above the depth of every ring of stages (3 to 8), and many
@@ -203,7 +203,7 @@ def test_a_split_product_equals_the_unsplit_one(epilogue):
 
 def test_the_hook_refuses_what_the_tiles_cannot_run():
     p = Product("f16", 8, 256, 64, 64, STORE)
-    for tile, epilogue in ((2, STORE), (99, STORE), (16, QKV_ROPE), (15, SWIGLU)):
+    for tile, epilogue in ((1, STORE), (1, RESIDUAL), (2, STORE), (3, SWIGLU), (99, STORE), (16, QKV_ROPE), (15, SWIGLU)):
         p.epi = epilogue
         out = torch.zeros(8, 512, dtype=torch.float32, device="cuda")
         q = (lambda t: t.data_ptr())
