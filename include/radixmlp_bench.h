@@ -75,6 +75,18 @@ int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int32_t Nout, 
                          const float* sin_tab, const int32_t* pos, int32_t n_q_heads, int32_t n_kv_heads, int32_t qk_norm,
                          const int32_t* rows, int32_t n_valid, int32_t n_src, int32_t* status, void* stream);
 
+/*
+ * The same with a folded RMSNorm (radix_model_config.fold_norms).  Epilogues 0, 2 and 3 consume one: rows are scaled by
+ * 1 / sqrt(sum of the n_slots_in (even) values ss_in[m, :] * inv_d + eps) before the epilogue proper.  Epilogue 6 adds to the
+ * fp32 rows of out and prepares one: a16[M, Nout] = rows * gain[Nout] in the operand type, ss_out[M, Nout / 128] = sums of squares of
+ * 128 columns.  variant: 4 (256x256) and 2 (128x128, not for heads) consume, 1 (256x256) prepares, 3 (128x256) does both;
+ * 0: the tile the launcher picks.
+ */
+int radix_debug_gemm_run_folded(const void* A, const void* W, int32_t M, int32_t Nout, int32_t K, int32_t epilogue, void* out,
+                                int32_t op_dtype, int32_t variant, const float* gq, const float* gk, const float* cos_tab,
+                                const float* sin_tab, const int32_t* pos, int32_t n_q_heads, int32_t n_kv_heads, const float* ss_in,
+                                int32_t n_slots_in, float inv_d, float eps, void* a16, const float* gain, float* ss_out, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -26,7 +26,7 @@ EXPORTS = (
     "radix_index_select_rows", "radix_device_status", "radix_status_string",
     "radix_timing_enable", "radix_timing_collect", "radix_debug_gemm_tile", "radix_debug_gemm_band", "radix_debug_gemm_plan", "radix_debug_gemm_plan_cus",
     "radix_debug_gemm_plan_us",
-    "radix_debug_index_first_round", "radix_debug_index_host_slots", "radix_debug_gemm_run",
+    "radix_debug_index_first_round", "radix_debug_index_host_slots", "radix_debug_gemm_run", "radix_debug_gemm_run_folded",
 )
 
 TIMING_CATEGORIES = ("gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "attention", "scatter", "gather", "rowops",
@@ -95,6 +95,8 @@ def _lib() -> C.CDLL:
         lib.radix_debug_gemm_plan_cus.argtypes = [i32] * 5 + [C.POINTER(i32)] * 7
         lib.radix_debug_gemm_run.argtypes = ([C.c_void_p] * 2 + [i32] * 5 + [C.c_void_p] + [i32] * 2 + [C.c_void_p] * 5 + [i32] * 3 +
                                              [C.c_void_p] + [i32] * 2 + [C.c_void_p] * 2)
+        lib.radix_debug_gemm_run_folded.argtypes = ([vp] * 2 + [i32] * 4 + [vp] + [i32] * 2 + [vp] * 5 + [i32] * 2 + [vp, i32] +
+                                                    [C.c_float] * 2 + [vp] * 4)
         lib.radix_debug_gemm_plan_us.argtypes = [i32] * 7 + [C.POINTER(C.c_double)]
         lib.radix_debug_index_first_round.argtypes = [i32] * 2
         lib.radix_status_string.argtypes = [C.c_int]

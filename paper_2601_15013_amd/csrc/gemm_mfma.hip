@@ -345,7 +345,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
     const int lane = lane_opaque;
     const int r = lane & 15, g = lane >> 4;
 
-#define RADIX_ACC(J, I, E) (CONSUMES_NORM ? acc[J][I][E] * rsr[I] : acc[J][I][E])
+    if (CONSUMES_NORM) {            // in place: scaled as they are used, they would be held twice
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[j][i][e] *= rsr[i];
+    }
 
     if (EPI == EPI_RESIDUAL_NORM) {
         // fp32 read-modify-write of the residual stream as below, plus, per row: the updated values times the
@@ -448,7 +455,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
         RopeGain gains;
         constexpr int TABS = PARTS == 2 || FOLD ? 1 : 2;        // two do not fit the registers of those epilogues
         RopeRow tab[TABS];
-        if (rope_head) rope_gain(gains, qe, head >= qe.n_q_heads, g);
+        // 256x256 with a folded norm: fetched once, the gains were more registers than there are (four accumulators spilled)
+        constexpr bool GAINS_LATE = FOLD && MB * NB >= 32;
+        if (rope_head && !GAINS_LATE) rope_gain(gains, qe, head >= qe.n_q_heads, g);
 #pragma unroll
         for (int ip = 0; ip < MB; ip += 4) {
 #pragma unroll
@@ -466,7 +475,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                         V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const float gt = RADIX_ACC(j, i, t), up = RADIX_ACC(j + 2 < NB ? j + 2 : 0, i, t);
+                            const float gt = acc[j][i][t], up = acc[j + 2 < NB ? j + 2 : 0][i][t];
                             // silu(g) * u with the hardware reciprocal (1 ulp) instead of an IEEE division
                             const float y = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
                             const T hi = (T)y;
@@ -479,10 +488,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                     // next 16 rows are on their way while these are rotated: with the rows fetched as they are used, and the
                     // gains with them, this epilogue cost as much as 6 k-tiles more (M 8192, N 4096, K 1024: 84 -> 75 us a
                     // launch, 50432 rows 483 -> 444).
+                    if (GAINS_LATE) rope_gain(gains, qe, head >= qe.n_q_heads, g);
                     if (TABS == 1) rope_load(tab[0], qe, rope_pos[i], g);
                     else if (il < 3 && i + 1 < MB) rope_load(tab[(il + 1) % TABS], qe, rope_pos[i + 1 < MB ? i + 1 : 0], g);
                     __builtin_amdgcn_sched_barrier(0);
-                    rope_apply([&](int j, int e) { return RADIX_ACC(j < NB ? j : 0, i, e); }, tab[il % TABS], gains, qe, [&](int j, f32x4 y) {
+                    rope_apply([&](int j, int e) { return acc[j < NB ? j : 0][i][e]; }, tab[il % TABS], gains, qe, [&](int j, f32x4 y) {
                         V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
@@ -498,7 +508,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
                         V4 v;
 #pragma unroll
                         for (int t = 0; t < 4; ++t) {
-                            const float y = RADIX_ACC(j, i, t);
+                            const float y = acc[j][i][t];
                             const T hi = (T)y;
                             v[t] = part == 0 ? hi : (T)(y - (float)hi);
                         }
@@ -517,7 +527,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(const
           }
         }
     }
-#undef RADIX_ACC
     }
 }
 
@@ -860,6 +869,27 @@ extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int
     const ARowMap amap = {rows, n_valid, n_src, status};
     const int rc = launch_gemm_mfma(A, W, M, Nout, K, epilogue, out, op_dtype, variant, (hipStream_t)stream, rope ? &qe : nullptr,
                                     w_k, rows ? &amap : nullptr);
+    if (rc != RADIX_OK) return rc;
+    HIP_TRY(hipGetLastError());
+    return RADIX_OK;
+}
+extern "C" int radix_debug_gemm_run_folded(const void* A, const void* W, int32_t M, int32_t Nout, int32_t K, int32_t epilogue,
+                                           void* out, int32_t op_dtype, int32_t variant, const float* gq, const float* gk,
+                                           const float* cos_tab, const float* sin_tab, const int32_t* pos, int32_t n_q_heads,
+                                           int32_t n_kv_heads, const float* ss_in, int32_t n_slots_in, float inv_d, float eps,
+                                           void* a16, const float* gain, float* ss_out, void* stream) {
+    if (!A || !W || !out) return RADIX_ERR_NULL_POINTER;
+    if (M <= 0 || Nout <= 0 || K <= 0) return RADIX_ERR_BAD_SIZE;
+    if (variant < 0 || variant > 4) return RADIX_ERR_UNSUPPORTED;
+    const bool rope = epilogue == EPI_QKV_ROPE, produces = epilogue == EPI_RESIDUAL_NORM;
+    if (!rope && !produces && epilogue != EPI_STORE && epilogue != EPI_SWIGLU) return RADIX_ERR_UNSUPPORTED;
+    if (produces ? !a16 || !gain || !ss_out : !ss_in) return RADIX_ERR_NULL_POINTER;
+    if (rope && (!gq || !gk || !cos_tab || !sin_tab || !pos)) return RADIX_ERR_NULL_POINTER;
+    if (rope && (n_q_heads < 0 || n_kv_heads < 0 || Nout != (n_q_heads + 2 * n_kv_heads) * 128)) return RADIX_ERR_BAD_SIZE;
+    const QkvEpilogue qe = {gq, gk, cos_tab, sin_tab, pos, n_q_heads, n_kv_heads, 1, 1e-6f};
+    const NormFusion nf = {a16, gain, ss_out, produces ? nullptr : ss_in, n_slots_in, inv_d, eps};
+    const int rc = launch_gemm_mfma(A, W, M, Nout, K, epilogue, out, op_dtype, variant, (hipStream_t)stream, rope ? &qe : nullptr, K,
+                                    nullptr, &nf);
     if (rc != RADIX_OK) return rc;
     HIP_TRY(hipGetLastError());
     return RADIX_OK;
