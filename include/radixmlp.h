@@ -131,7 +131,8 @@ typedef struct radix_fwd_opts {
                            * (the paper's radix_mlp_threshold).  Negative (RADIX_THRESHOLD_AUTO): the library decides, per
                            * batch: the position-wise work saved per layer, (N - N') * F / 1.1e15 s (F = projection + MLP flops of
                            * one row), against what deduplication adds - with the fused attention kernel about 15 % of
-                           * the attention time, 0.15 * 2 * dq * N * (N / B) / 5e14 s; with the three-kernel attention the
+                           * the attention time, 0.15 * 2 * dq * N * (N / B) / 5e14 s (fp32 weights, whose rate above is 2e13:
+                           * 4.5e-6 s per forward); with the three-kernel attention the
                            * scatter of (N' + N) q|k|v rows at 5e12 bytes/s.  (Rates: what the kernels reach on an
                            * MI355X.)  E.g. 32 sequences of 1056 tokens: the 0.6B shape deduplicates below N'/N = 0.955 (fused
                            * attention) or 0.89 (three kernels), the 8B shape below 0.992 or 0.986.

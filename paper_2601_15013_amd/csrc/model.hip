@@ -526,7 +526,12 @@ static bool decide_dedup(const radix_model_config& c, int32_t B, int32_t N, int3
     const double gemm_rate = c.compute_dtype == RADIX_F32 ? 2.0e13 : 1.1e15;
     const double saved = ((double)N - n_compact) * flops_row / gemm_rate;
     double added;
-    if (fused) {
+    if (fused && c.compute_dtype == RADIX_F32) {
+        // attention reads through the maps and skips the duplicate rows: what is added is the scatter at the end of the
+        // forward, 4 to 6 us where nothing is saved (models of 128 to 1024 columns, 248 to 8004 rows).  4096 rows of
+        // 128 columns and 16 heads, 126 of them duplicates: 809 us, plain 947, with row copies 1038
+        added = 4.5e-6 / c.n_layers;
+    } else if (fused) {
         // the fused kernel starts every workgroup with two more dependent loads (work list, index map) and
         // cuts query blocks where the representatives start, not at multiples of the key tile: about 15 % on
         // top of the attention time when nothing is shared
@@ -543,7 +548,7 @@ static int fused_mode(const radix_model_config& c, const radix_fwd_opts* opts, b
     const int mode = opts ? opts->attention_mode : RADIX_ATTN_AUTO;
     if (mode != RADIX_ATTN_AUTO && mode != RADIX_ATTN_THREE_KERNELS && mode != RADIX_ATTN_FUSED) return RADIX_ERR_BAD_CONFIG;
     if (mode == RADIX_ATTN_FUSED && c.compute_dtype == RADIX_F32) return RADIX_ERR_UNSUPPORTED;
-    *fused = mode == RADIX_ATTN_FUSED || (mode == RADIX_ATTN_AUTO && c.compute_dtype != RADIX_F32);
+    *fused = mode != RADIX_ATTN_THREE_KERNELS;         // with fp32 weights: the attention kernel that reads through the maps
     return RADIX_OK;
 }
 
@@ -576,9 +581,8 @@ extern "C" int radix_prefill_forward(const radix_model* model, const int32_t* to
     if (opts && opts->pad_compact_to < 0) return RADIX_ERR_BAD_CONFIG;
     const int pad_to = opts ? opts->pad_compact_to : 0;
     if (!dedup) n_compact = N;
-    const bool fused_f32 = model->cfg.compute_dtype == RADIX_F32 && (!opts || opts->attention_mode == RADIX_ATTN_AUTO);
-    return forward_impl(model, tok, pos, cu_seqlens, B, N, max_seqlen, I_scatter, I_gather, n_compact, dedup, fused || fused_f32,
-                        pad_to, out, ws, ws_bytes, (hipStream_t)stream);
+    return forward_impl(model, tok, pos, cu_seqlens, B, N, max_seqlen, I_scatter, I_gather, n_compact, dedup, fused, pad_to,
+                        out, ws, ws_bytes, (hipStream_t)stream);
 }
 
 extern "C" int radix_prefill_forward_nodedup(const radix_model* model, const int32_t* tok, const int32_t* pos,

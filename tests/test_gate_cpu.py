@@ -78,6 +78,32 @@ def test_automatic_gate_weighs_the_model_size(lib):
         assert 0.5 < small <= mid <= big < 1.0, (fused, small, mid, big)
 
 
+THIN = synth.ModelConfig("thin", 2, 128, 16, 16, 128, 128, 4096, "f32")
+WIDE = synth.ModelConfig("wide", 2, 1024, 16, 8, 128, 3072, 4096, "f32")
+
+
+# (model, B, prefix, suffix) -> us of the deduplicated forward, of the plain one and of the one with row copies, on one MI355X
+@pytest.mark.parametrize("model_cfg,B,prefix,suffix,us", [
+    (synth.TINY, 8, 1, 30, (95.3, 91.7, 103.4)), (synth.TINY, 32, 1, 255, (816.7, 831.5, 855.2)),
+    (THIN, 8, 1, 30, (139.1, 132.8, 148.6)), (THIN, 32, 1, 63, (484.7, 545.6, 590.6)), (THIN, 64, 2, 62, (809.1, 946.5, 1038.4)),
+    (THIN, 32, 1, 1023, (46025.0, 49067.0, 49981.0)), (THIN, 256, 8, 24, (1128.6, 1522.6, 1680.2)),
+    (WIDE, 32, 1, 255, (9682.0, 10040.0, 10212.0)), (WIDE, 256, 1, 31, (7472.0, 7761.0, 7846.0))])
+def test_fp32_attention_through_the_maps_pays_no_row_copies(lib, model_cfg, B, prefix, suffix, us):
+    c = cfg_of(model_cfg, compute="f32")
+    N, n = sweep_counts(prefix, suffix, B)
+    through_maps, plain, _ = us
+    assert binding.radix_dedup_decision(c, B, N, n) == (through_maps < plain)
+    assert not binding.radix_dedup_decision(c, B, N, N)
+    decisions = [binding.radix_dedup_decision(c, B, N, m) for m in range(N, 0, -max(1, N // 200))]
+    assert all(decisions[decisions.index(True):])
+
+
+def test_fp32_row_copies_are_still_charged_where_they_are_made(lib):
+    c = cfg_of(THIN, compute="f32")
+    N, n = sweep_counts(2, 62, 64)
+    assert binding.radix_dedup_decision(c, 64, N, n) and not binding.radix_dedup_decision(c, 64, N, n, fused_attention=False)
+
+
 def test_gate_rejects_bad_arguments(lib):
     c = cfg_of(synth.QWEN3_0_6B)
     import ctypes as C
