@@ -601,7 +601,8 @@ int build_index_impl(const int32_t* tok, const int32_t* pos, const int32_t* cu_s
     hipLaunchKernelGGL(chain, dim3(1), dim3(IDX_THREADS), 0, stream, tok, pos, cu_seqlens, B, N, I_scatter,
                        hdr, ldr, dep, bdep, mis, myslot, cbase, slot_owner, slot_min, H, n_compact_dev, first_done, host);
     if (N > 0) {
-        const bool few = N < 1 << 18;           // workgroups for every CU come first
+        // few: workgroups for every CU come first; nor may the count of workgroups leave 32 bits
+        const bool few = N < 1 << 18 || N > 0x7FFFFFFF - 1023;
         auto finalize = few ? index_finalize_kernel<1> : index_finalize_kernel<4>;
         hipLaunchKernelGGL(finalize, dim3(ceil_div(N, few ? 256 : 1024)), dim3(256), 0, stream, tok, pos,
                            cu_seqlens, B, N, I_scatter, I_gather, hdr, bdep, cbase, first_done && in_lds ? mis : nullptr, host);

@@ -172,3 +172,15 @@ def test_calls_that_fail_inside_a_capture_keep_no_words():
         assert rc < 0 and n_host.value == -1
     assert lib.radix_debug_index_host_slots() == 64
     assert binding.radix_build_index(tok, None, cu, ws)[3] == n
+
+
+def test_a_batch_near_the_largest_number_of_tokens():
+    N = 2 ** 31 - 600
+    tok = torch.zeros(N, dtype=torch.int32, device="cuda")
+    cu = torch.tensor([0, N], dtype=torch.int32, device="cuda")
+    ws = binding.alloc_workspace(binding.radix_index_workspace_bytes(1))
+    S, G, _, n = binding.radix_build_index(tok, None, cu, ws)
+    assert n == N
+    for a in range(0, N, 1 << 28):
+        want = torch.arange(a, min(N, a + (1 << 28)), dtype=torch.int32, device="cuda")
+        assert torch.equal(S[a:a + (1 << 28)], want) and torch.equal(G[a:a + (1 << 28)], want), a
