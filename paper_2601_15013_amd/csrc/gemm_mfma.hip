@@ -716,6 +716,14 @@ int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double*
     return v;
 }
 
+// Which loop a 256x128 tile runs: that of gemm_small.hip, whose epilogue goes through LDS, for heads, written fp32 rows and, where
+// rows of A are short, rows added to - straight from the accumulators those cost as much as three to four k-tiles more.  us, large
+// loop / this one: M 50000: N 640 K 640 74.8 / 71.8, N 640 K 1280 120.8 / 114.0; M 24000: N 384 K 384 28.3 / 24.6, N 1024 K 2048
+// 106.8 / 108.7; M 130000 N 1024 K 3072 899 / 893, M 8200 78.0 / 83.3: from K 2048 on neither is better, from 3072 on the large one.
+bool small_256x128(int K, int epilogue) {
+    return epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT || epilogue == EPI_STORE_F32 || (epilogue == EPI_RESIDUAL && K < 2048);
+}
+
 // Tiles of a product: rows [0, m1) in tiles of shape v1, the rest (if any) in a second launch of shape v2.  The large
 // tiles are at their best when the last round of workgroups is full; where M leaves a round nearly empty - 8240 rows
 // are 33 row tiles of 256, and 32 of them are whole rounds of the chip - the rows past the last full round go to smaller
@@ -771,9 +779,8 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
     if (nf.ss_in && (nf.n_slots_in <= 0 || nf.n_slots_in % 2 != 0 || ((uintptr_t)nf.ss_in & 7) != 0)) return RADIX_ERR_UNSUPPORTED;
     const bool folded = nf.ss_in != nullptr || epilogue == EPI_RESIDUAL_NORM;
     if (folded && variant >= 11) return RADIX_ERR_UNSUPPORTED;
-    const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
     auto launch = [&](int v, const void* a, int m, void* o) -> int {
-        if ((v >= 11 && v < 20) || (v == 20 && (rope || epilogue == EPI_STORE_F32))) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
+        if ((v >= 11 && v < 20) || (v == 20 && small_256x128(K, epilogue))) return launch_gemm_small(a, W, m, Nout, K, epilogue, o, op_dtype, v, stream, qe, w_k, amap);
         if (op_dtype == RADIX_BF16) return launch_dt<RADIX_BF16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         return RADIX_ERR_UNSUPPORTED;

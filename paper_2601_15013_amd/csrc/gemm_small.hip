@@ -373,14 +373,12 @@ int launch_small_cfg(const void* A, const void* W, int M, int Nout, int K, int w
 #define RADIX_LAUNCH(E)                                                                                          \
     hipLaunchKernelGGL((gemm_small_kernel<DT, BM, BN, WAVES_M, WAVES_N, NS, E>), grid, block, 0, stream,         \
                        (const T*)A, (const T*)W, M, Nout, K, out, tiles_m, tiles_n, band, w_k, qe, amap)
-    constexpr bool ALL = BM < 256;          // 256x128: heads and fp32 rows only, the others in gemm_mfma.hip
+    constexpr bool ALL = BM < 256;          // 256x128: heads and fp32 rows only (small_256x128), the others in gemm_mfma.hip
     switch (epilogue) {
         case EPI_STORE:
             if constexpr (ALL) { RADIX_LAUNCH(EPI_STORE); return RADIX_OK; }
             break;
-        case EPI_RESIDUAL:
-            if constexpr (ALL) { RADIX_LAUNCH(EPI_RESIDUAL); return RADIX_OK; }
-            break;
+        case EPI_RESIDUAL: RADIX_LAUNCH(EPI_RESIDUAL); return RADIX_OK;
         case EPI_STORE_F32: RADIX_LAUNCH(EPI_STORE_F32); return RADIX_OK;
         case EPI_SWIGLU:
             if constexpr (ALL && BN % 64 == 0) { RADIX_LAUNCH(EPI_SWIGLU); return RADIX_OK; }
