@@ -638,7 +638,10 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 // heads, fp32 rows added to, fp32 rows written, which short_k does not tell apart) and, per 64 columns of K, step_us + share_us times the share of the CUs that it occupies (the clock and
 // the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
 // 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us if that is more.
-// A launch that does not fill its last round pays for it in full, until there are many rounds.
+// A launch that does not fill its last round pays for it in full; where several workgroups run on a CU, only up to eight rounds.
+// (One per CU: 12 products of the 0.6B, 4B and 8B shapes at 22 row counts, 5 to 22 rounds.  Counted like this, launches of 8 to 22
+// rounds take 0.98 to 1.03 of the model's time on average, at every fill of the last round; with the rounds beyond eight counted
+// in fractions, nearly empty last rounds took 1.04 to 1.08 of it.)
 // The constants are least-squares fits of the logarithm to timed launches on MI355X (fp16 operands), in two sets because rows
 // of A shorter than 1024 leave a launch mostly epilogue and start-up, which long rows say little about:
 //   long_k, K >= 1024: 336 (product, row count) pairs of the four projections of the 0.6B, 4B and 8B shapes and four others
@@ -681,7 +684,6 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
     const double kt = K / 64;
     if (sh.per_cu == 1) {
         auto round_us = [&](double busy) { return c.fixed_us + epi + kt * (c.step_us + c.share_us * busy); };
-        if (tiles >= 8LL * cus) return c.launch_us + (double)tiles / cus * round_us(1.0);
         const int rest = (int)(tiles % cus);
         return c.launch_us + (double)(tiles / cus) * round_us(1.0) + (rest ? round_us((double)rest / cus) : 0.0);
     }
@@ -727,18 +729,22 @@ bool small_256x128(int K, int epilogue) {
 // Tiles of a product: rows [0, m1) in tiles of shape v1, the rest (if any) in a second launch of shape v2.  The large
 // tiles are at their best when the last round of workgroups is full; where M leaves a round nearly empty - 8240 rows
 // are 33 row tiles of 256, and 32 of them are whole rounds of the chip - the rows past the last full round go to smaller
-// tiles (M 8240, K 1024, N 4096: 111 us in one launch of 256x256, 93 us split; K 3072, N 1024: 79 and 62 us).
+// tiles (M 8240, K 1024, N 4096: 111 us in one launch of 256x256, 93 us split; K 3072, N 1024: 79 and 62 us; with more rounds:
+// M 16436, N 6144, K 2560 444 and 426, M 47176, N 2560, K 4096 912 and 857).
 struct GemmPlan { int v1, m1, v2; };
 GemmPlan plan_gemm(int cus, int M, int Nout, int K, int epilogue) {
     double whole = 0.0;
     GemmPlan p = {best_tile(cus, M, Nout, K, epilogue, false, &whole), M, 0};
     if (M <= 256) return p;
     double best = 0.97 * whole;             // what a split has to beat: a launch more, and the model's own error
+    // weights too large for the memory-side cache come from HBM again in a second launch, which is as much as the last of many
+    // rounds costs (300 and 1300 rows of a head of 151936 columns: 542 -> 614 and 570 -> 630 us)
+    const bool weights_pass = (long long)Nout * K * 2 > 256LL << 20;
     for (const TileShape& sh : tile_shapes) {
         if (sh.bm < 128 || !tile_usable(sh, Nout, K, epilogue)) continue;
         const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
         const long long rounds = row_tiles * per_row / cus;
-        if (rounds < 1 || rounds >= 8) continue;
+        if (rounds < 1 || (rounds >= 8 && weights_pass)) continue;
         const long long m1 = rounds * cus / per_row * sh.bm;
         if (m1 < sh.bm || m1 >= M) continue;
         double t1 = 0.0, t2 = 0.0;              // rows that fill rounds of this tile may still run faster in another one

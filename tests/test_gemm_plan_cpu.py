@@ -127,3 +127,42 @@ def test_short_rows_get_a_tile_near_the_best_measured_one(plan, product):
     rc, (v1, _, _, m1, _, _, _) = plan(*product)
     assert rc == 0 and m1 == product[0]
     assert SHORT_K[product][v1] <= 1.1 * min(SHORT_K[product].values())
+
+
+# us of products of 8 to 20 rounds of workgroups on one MI355X (fp16 operands), by (tile, its rows, tile of the rows left): every large
+# tile alone, and with its last, partly filled round given to smaller ones
+MANY_ROUNDS = {
+    (16436, 6144, 2560, QKV_ROPE): {(4, 16384, 13): 425.5, (4, 16436, 0): 444.2, (18, 16384, 13): 560.7, (18, 16436, 0): 563.1,
+        (19, 16384, 13): 523.0, (19, 16436, 0): 525.5, (20, 16384, 13): 529.5, (20, 16436, 0): 526.6, (23, 14208, 4): 436.6,
+        (23, 16436, 0): 453.4},
+    (24763, 6144, 1024, SWIGLU): {(4, 24576, 17): 251.1, (4, 24763, 0): 266.2, (18, 24576, 17): 356.2, (18, 24763, 0): 357.9,
+        (19, 24576, 17): 314.5, (19, 24763, 0): 319.1, (20, 24576, 17): 276.1, (20, 24763, 0): 279.9, (22, 23840, 20): 273.8,
+        (22, 24763, 0): 271.4, (23, 24576, 17): 261.4, (23, 24763, 0): 269.5, (24, 23744, 20): 260.1, (24, 24763, 0): 264.1},
+    (6171, 24576, 4096, SWIGLU): {(4, 6144, 13): 904.8, (4, 6171, 0): 951.3, (18, 6144, 13): 1245.9, (18, 6171, 0): 1266.1,
+        (19, 6144, 13): 1108.0, (19, 6171, 0): 1122.4, (20, 6144, 13): 1006.1, (20, 6171, 0): 1023.8, (22, 5920, 20): 983.4,
+        (22, 6171, 0): 989.1, (23, 6144, 13): 947.9, (23, 6171, 0): 972.4, (24, 5824, 23): 954.1, (24, 6171, 0): 961.9},
+    (47176, 2560, 4096, RESIDUAL): {(4, 45824, 18): 857.3, (4, 47176, 0): 912.1, (18, 45824, 18): 1143.7,
+        (18, 47176, 0): 1121.1, (19, 45824, 18): 1018.9, (19, 47176, 0): 1022.6, (20, 45824, 18): 995.5, (20, 47176, 0): 998.3,
+        (22, 44960, 20): 958.1, (22, 47176, 0): 951.9, (23, 44160, 20): 912.5, (23, 47176, 0): 919.8, (24, 45696, 18): 914.8,
+        (24, 47176, 0): 962.9},
+    (29476, 4096, 12288, RESIDUAL): {(4, 28672, 18): 2210.3, (4, 29476, 0): 2313.3, (18, 28672, 18): 3075.7,
+        (18, 29476, 0): 3032.6, (19, 28672, 18): 2683.4, (19, 29476, 0): 2720.4, (20, 28672, 18): 2554.5,
+        (20, 29476, 0): 2591.5, (22, 28160, 20): 2477.2, (22, 29476, 0): 2475.4, (23, 27648, 20): 2359.5,
+        (23, 29476, 0): 2389.9, (24, 28672, 18): 2361.1, (24, 29476, 0): 2440.7},
+    (117949, 1024, 3072, RESIDUAL): {(4, 114688, 18): 690.6, (4, 117949, 0): 729.4, (18, 114688, 18): 972.6,
+        (18, 117949, 0): 958.3, (19, 114688, 18): 828.3, (19, 117949, 0): 831.6, (20, 114688, 18): 843.6,
+        (20, 117949, 0): 848.4, (22, 112640, 20): 774.3, (22, 117949, 0): 766.2, (23, 110592, 20): 733.5,
+        (23, 117949, 0): 742.2, (24, 114688, 18): 730.1, (24, 117949, 0): 762.2},
+}
+
+
+@pytest.mark.parametrize("product", sorted(MANY_ROUNDS))
+def test_the_last_of_many_rounds_is_counted(plan, product):
+    rc, (v1, _, _, m1, v2, _, _) = plan(*product)
+    assert rc == 0
+    assert MANY_ROUNDS[product][v1, m1, v2] <= 1.01 * min(MANY_ROUNDS[product].values())
+
+
+def test_weights_beyond_the_cache_are_not_read_twice(plan):
+    for m, k in ((300, 4096), (1300, 1024)):
+        assert plan(m, 151936, k, STORE_F32)[1][3] == m
