@@ -635,8 +635,8 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
 // in rounds.  Where that is one, a round costs fixed_us + epi_us (first loads, epilogue, by what it writes: 16-bit rows, q|k|v
-// heads, fp32 rows added to, fp32 rows written, which short_k does not tell apart) and, per 64 columns of K, step_us + share_us times the share of the CUs that it occupies (the clock and
-// the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
+// heads, fp32 rows added to, fp32 rows written) and, per 64 columns of K, step_us + share_us times the share of the CUs that it
+// occupies (the clock and the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
 // 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us if that is more.
 // A launch that does not fill its last round pays for it in full; where several workgroups run on a CU, only up to eight rounds.
 // (One per CU: 12 products of the 0.6B, 4B and 8B shapes at 22 row counts, 5 to 22 rounds.  Counted like this, launches of 8 to 22
@@ -649,37 +649,37 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 //     they pick takes 0.5 % longer than the best one (a tenth of them more than 1 %, the worst 23 %).  Written fp32 rows from
 //     60 more (heads of 151936 columns, K 1024 .. 4096, and N 8192, M 8 .. 4500): 0.4 %, the worst 10 %.  They leave 256x128 tiles
 //     through LDS (gemm_small.hip): 151936 columns, K 1024, M 1000: 421 us, straight from the accumulators 592.
-//   short_k: 23 products of K 64 .. 768 at 25 row counts, tiles within 1.4 of the best.  Within 9 %; the picked tile
-//     takes 2.4 % (K 64 and 128), 1.3 % (256 to 384) and 0.7 % (512 to 768) longer than the best, where long_k's pick took 13,
-//     10 and 6 %; bf16 operands, not in the fit, 2.7, 1.2 and 0.7 %.
+//   short_k: 53 products of K 64 .. 768 at 23 and 25 row counts from 1 to 130000; not least squares alone, but the time lost by what
+//     is picked and, less, the model's error for tiles within 1.4 of the best, which is 6 to 13 %.  The picked tile takes 0.5 %
+//     longer than the best (a tenth of them more than 1.5 %, the worst 21 %).  bf16 operands, which were not in the fit, gain as much
+//     over the plans before as fp16 ones (3.6 % over 562 launches).
 // The 256x256 tile wins where it fills the chip; the tiles of 160, 192 and 224 rows where that leaves less of the last round
 // empty: M 8300, N 1024: K 3072 70.1 / 57.3 us (256 / 160 rows), K 2048 54.4 / 43.0; M 5000, N 7168, K 5120: 338 / 294 (192 rows);
-// 129 of the 336 pairs have one of the three as their best.  Their constants are 2 % above the fit: among many estimates one that
-// is low by chance would win, and the older tiles are the safer choice.
+// 129 of the 336 pairs have one of the three as their best; short rows: M 16500, N 4096, K 768 (gate/up)
+// 114.6 / 105.7 (224 rows).  Their constants of long_k are 2 % above the fit: among many estimates one that is low by chance would win, and the older tiles are the safer choice.
 struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[4]; };
 struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
 constexpr int LONG_K = 1024;
-constexpr TileCost NOT_SHORT = {};                  // never chosen at short rows (tile_usable)
 const TileShape tile_shapes[] = {
-    { 4, 256, 256, 1, {1.95,  4.74, 0.776, 0.714, {0.37, 6.56, 12.93,  4.25}}, {0.00, 4.85, 1.502, 0.000, {0.00, 8.09, 16.90}}},
-    {11,  32,  16, 3, {2.00,  0.00, 0.113, 0.079, {0.62, 0.50,  0.00,  0.70}}, {1.88, 0.90, 0.081, 0.059, {0.02, 0.00, 0.07}}},
-    {12,  32,  32, 2, {1.74,  0.00, 0.130, 0.110, {0.51, 0.50,  0.00,  1.50}}, {1.75, 1.03, 0.080, 0.089, {0.05, 0.00, 0.04}}},
-    {13,  32, 128, 2, {1.74,  0.00, 0.339, 0.244, {0.99, 0.46,  0.00,  2.20}}, {1.95, 0.26, 0.238, 0.181, {0.59, 1.56, 0.92}}},
-    {14,  32,  64, 2, {1.61,  0.00, 0.191, 0.157, {1.89, 6.30,  0.00,  1.80}}, {1.69, 0.77, 0.150, 0.131, {0.26, 0.00, 0.38}}},
-    {15,  64,  32, 2, {1.09,  0.00, 0.183, 0.151, {1.00, 1.00,  0.17,  1.15}}, {1.66, 0.89, 0.015, 0.122, {0.21, 0.00, 0.36}}},
-    {16,  64,  64, 2, {3.13,  0.00, 0.084, 0.214, {0.17, 0.55,  0.00,  1.10}}, {1.88, 0.38, 0.191, 0.160, {0.52, 0.00, 0.88}}},
-    {17,  64, 128, 2, {1.88,  0.00, 0.443, 0.334, {0.36, 0.79,  0.00,  2.50}}, {1.95, 0.00, 0.340, 0.273, {0.90, 2.48, 1.63}}},
-    {18, 128, 128, 1, {1.75,  2.63, 0.367, 0.155, {0.48, 2.12,  1.46,  3.40}}, {1.13, 0.00, 0.505, 0.000, {2.45, 7.08, 4.16}}},
-    {19, 128, 256, 1, {3.29,  3.58, 0.598, 0.306, {0.10, 5.33,  2.45,  0.85}}, {0.81, 3.71, 0.831, 0.000, {0.00, 8.13, 3.35}}},
-    {20, 256, 128, 1, {2.40,  2.15, 0.551, 0.295, {0.34, 9.36,  6.02,  6.80}}, {0.79, 4.30, 0.796, 0.000, {0.00, 8.64, 3.65}}},
-    {22, 160, 256, 1, {3.44,  2.44, 0.663, 0.411, {0.33, 0.51,  6.95,  3.60}}, NOT_SHORT},
-    {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41,  3.35}}, NOT_SHORT},
-    {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22,  3.90}}, NOT_SHORT},
+    { 4, 256, 256, 1, {1.95,  4.74, 0.776, 0.714, {0.37, 6.56, 12.93,  4.25}}, {2.27, 4.35, 0.883, 0.290, {1.80, 8.59, 14.65, 8.82}}},
+    {11,  32,  16, 3, {2.00,  0.00, 0.113, 0.079, {0.62, 0.50,  0.00,  0.70}}, {1.46, 0.31, 0.038, 0.038, {0.57, 0.00, 0.78, 0.56}}},
+    {12,  32,  32, 2, {1.74,  0.00, 0.130, 0.110, {0.51, 0.50,  0.00,  1.50}}, {1.04, 0.55, 0.133, 0.117, {0.36, 0.00, 0.34, 0.45}}},
+    {13,  32, 128, 2, {1.74,  0.00, 0.339, 0.244, {0.99, 0.46,  0.00,  2.20}}, {1.51, 0.79, 0.018, 0.193, {0.36, 1.02, 0.92, 0.48}}},
+    {14,  32,  64, 2, {1.61,  0.00, 0.191, 0.157, {1.89, 6.30,  0.00,  1.80}}, {1.45, 0.61, 0.009, 0.150, {0.14, 0.00, 0.54, 0.33}}},
+    {15,  64,  32, 2, {1.09,  0.00, 0.183, 0.151, {1.00, 1.00,  0.17,  1.15}}, {1.24, 0.86, 0.024, 0.129, {0.27, 0.00, 0.38, 0.34}}},
+    {16,  64,  64, 2, {3.13,  0.00, 0.084, 0.214, {0.17, 0.55,  0.00,  1.10}}, {1.27, 0.61, 0.015, 0.160, {0.69, 0.00, 1.18, 0.71}}},
+    {17,  64, 128, 2, {1.88,  0.00, 0.443, 0.334, {0.36, 0.79,  0.00,  2.50}}, {1.31, 0.56, 0.017, 0.270, {0.93, 1.86, 1.40, 1.12}}},
+    {18, 128, 128, 1, {1.75,  2.63, 0.367, 0.155, {0.48, 2.12,  1.46,  3.40}}, {0.20, 1.94, 0.172, 0.339, {1.45, 3.65, 3.96, 2.57}}},
+    {19, 128, 256, 1, {3.29,  3.58, 0.598, 0.306, {0.10, 5.33,  2.45,  0.85}}, {2.19, 3.52, 0.099, 0.898, {0.04, 6.79, 4.96, 2.63}}},
+    {20, 256, 128, 1, {2.40,  2.15, 0.551, 0.295, {0.34, 9.36,  6.02,  6.80}}, {0.50, 3.09, 0.385, 0.346, {0.68, 11.33, 6.35, 5.19}}},
+    {22, 160, 256, 1, {3.44,  2.44, 0.663, 0.411, {0.33, 0.51,  6.95,  3.60}}, {0.70, 2.61, 0.460, 0.397, {1.72, 0.00, 9.98, 7.06}}},
+    {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41,  3.35}}, {1.03, 3.96, 0.589, 0.434, {0.66, 6.46, 11.11, 5.19}}},
+    {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22,  3.90}}, {1.82, 3.89, 0.581, 0.597, {1.13, 0.00, 12.52, 5.64}}},
 };
 double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
     const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
     const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 : epilogue == EPI_RESIDUAL ? 2 :
-                                epilogue == EPI_STORE_F32 ? (K >= LONG_K ? 3 : 2) : 0];
+                                epilogue == EPI_STORE_F32 ? 3 : 0];
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
     const double kt = K / 64;
     if (sh.per_cu == 1) {
@@ -698,9 +698,9 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
 
 bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
     if (Nout % sh.bn != 0) return false;
-    // chosen where they were measured: long rows of A; results added to fp32 rows of any width, others of 2048 columns and more
+    // of long rows of A, chosen where they were measured: results added to fp32 rows of any width, others of 2048 columns and more
     // (measured from 4096 on)
-    if (sh.variant >= 22 && (K < LONG_K || (epilogue != EPI_RESIDUAL && Nout < 2048))) return false;
+    if (sh.variant >= 22 && K >= LONG_K && epilogue != EPI_RESIDUAL && Nout < 2048) return false;
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
         return sh.bn % 128 == 0 && sh.variant != 22 && sh.variant != 24;
     if (epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_SPLIT) return sh.bn % 64 == 0;           // gate/up pairs
@@ -735,8 +735,10 @@ struct GemmPlan { int v1, m1, v2; };
 GemmPlan plan_gemm(int cus, int M, int Nout, int K, int epilogue) {
     double whole = 0.0;
     GemmPlan p = {best_tile(cus, M, Nout, K, epilogue, false, &whole), M, 0};
-    if (M <= 256) return p;
-    double best = 0.97 * whole;             // what a split has to beat: a launch more, and the model's own error
+    if (M <= 256 || K < 512) return p;
+    // what a split has to beat: a launch more, and the model's own error, which is larger where K is short (N 2048: K 640, M 8200 39.6
+    // whole, 36.2 split, and M 33000 110 and 113; below K 512 16 of 18 splits took longer than the best tile alone)
+    double best = (K >= LONG_K ? 0.97 : 0.90) * whole;
     // weights too large for the memory-side cache come from HBM again in a second launch, which is as much as the last of many
     // rounds costs (300 and 1300 rows of a head of 151936 columns: 542 -> 614 and 570 -> 630 us)
     const bool weights_pass = (long long)Nout * K * 2 > 256LL << 20;

@@ -105,20 +105,30 @@ def test_plan_counts_the_cus_of_the_device(plan):
 # us per launch of every usable tile on one MI355X (fp16 operands): products whose rows of A are short, so that most of a launch
 # is its epilogue and start-up
 SHORT_K = {
-    (16500, 384, 128, STORE): {11: 26.53, 12: 19.71, 13: 10.18, 14: 13.22, 15: 14.18, 16: 10.30, 17: 8.38, 18: 9.00, 20: 7.80},
-    (50000, 128, 64, RESIDUAL): {11: 27.23, 12: 19.73, 13: 10.98, 14: 14.92, 15: 15.56, 16: 12.78, 17: 9.27, 18: 10.73, 20: 9.35},
-    (24000, 128, 128, RESIDUAL): {11: 19.00, 12: 12.00, 13: 7.47, 14: 8.02, 15: 9.81, 16: 7.42, 17: 6.48, 18: 6.83, 20: 8.28},
-    (50000, 128, 128, SWIGLU): {13: 9.50, 14: 12.56, 16: 9.33, 17: 7.80, 18: 8.25, 20: 6.98},
-    (9216, 256, 256, RESIDUAL): {4: 21.78, 11: 18.22, 12: 13.38, 13: 7.85, 14: 8.64, 15: 11.58, 16: 7.66, 17: 7.20,
-                                 18: 7.23, 19: 9.44, 20: 9.32},
-    (6500, 384, 384, RESIDUAL): {11: 23.18, 12: 15.00, 13: 9.69, 14: 10.95, 15: 13.26, 16: 10.42, 17: 8.69, 18: 8.30, 20: 11.16},
-    (5000, 512, 512, RESIDUAL): {4: 25.98, 11: 27.56, 12: 18.34, 13: 10.69, 14: 13.07, 15: 16.94, 16: 12.24, 17: 9.52,
-                                 18: 9.15, 19: 12.28, 20: 12.32},
-    (33000, 640, 256, SWIGLU): {13: 29.04, 14: 42.73, 16: 27.02, 17: 22.53, 18: 25.82, 20: 22.07},
-    (50000, 4096, 256, STORE_F32): {4: 677.10, 11: 831.76, 12: 665.15, 13: 319.59, 14: 429.27, 15: 424.15, 16: 294.53,
-                                    17: 255.39, 18: 280.69, 19: 273.38, 20: 317.66},
-    (24000, 4096, 512, STORE_F32): {4: 348.84, 11: 535.56, 12: 444.22, 13: 230.98, 14: 308.16, 15: 296.22, 16: 213.13,
-                                    17: 176.21, 18: 189.84, 19: 165.09, 20: 191.30},
+    (16500, 384, 128, STORE): {11: 27.19, 12: 19.96, 13: 10.14, 14: 13.48, 15: 14.41, 16: 10.33, 17: 8.43, 18: 9.03, 20: 6.78},
+    (50000, 128, 64, RESIDUAL): {11: 27.15, 12: 19.81, 13: 10.94, 14: 14.93, 15: 15.68, 16: 12.78, 17: 9.42, 18: 10.85,
+                                 20: 9.45},
+    (24000, 128, 128, RESIDUAL): {11: 18.93, 12: 12.07, 13: 7.49, 14: 8.11, 15: 9.92, 16: 7.34, 17: 6.67, 18: 6.95, 20: 8.39},
+    (50000, 128, 128, SWIGLU): {13: 9.41, 14: 12.56, 16: 9.31, 17: 7.95, 18: 8.26, 20: 5.89},
+    (9216, 256, 256, RESIDUAL): {4: 21.70, 11: 18.58, 12: 13.48, 13: 7.91, 14: 8.67, 15: 11.66, 16: 7.65, 17: 7.30, 18: 7.48,
+                                 19: 9.40, 20: 9.47, 22: 14.38, 23: 16.54, 24: 18.54},
+    (6500, 384, 384, RESIDUAL): {11: 23.45, 12: 15.01, 13: 9.60, 14: 10.92, 15: 13.15, 16: 10.23, 17: 8.60, 18: 8.43,
+                                 20: 11.06},
+    (5000, 512, 512, RESIDUAL): {4: 25.53, 11: 28.01, 12: 18.49, 13: 10.58, 14: 13.01, 15: 17.14, 16: 12.58, 17: 9.50,
+                                 18: 9.36, 19: 12.02, 20: 12.40, 22: 17.30, 23: 19.85, 24: 22.28},
+    (33000, 640, 256, SWIGLU): {13: 31.32, 14: 45.02, 16: 28.93, 17: 23.87, 18: 27.14, 20: 19.26},
+    (50000, 4096, 256, STORE_F32): {4: 258.90, 11: 868.03, 12: 681.55, 13: 308.73, 14: 436.30, 15: 427.77, 16: 276.63,
+                                    17: 240.12, 18: 299.58, 19: 269.80, 20: 279.84, 22: 307.86, 23: 288.55, 24: 263.45},
+    (24000, 4096, 512, STORE_F32): {4: 152.58, 11: 580.75, 12: 462.51, 13: 228.76, 14: 307.87, 15: 295.20, 16: 206.86,
+                                    17: 166.45, 18: 181.10, 19: 185.87, 20: 182.67, 22: 179.53, 23: 164.64, 24: 152.84},
+    (24000, 384, 384, RESIDUAL): {11: 52.32, 12: 42.93, 13: 23.98, 14: 29.53, 15: 29.17, 16: 23.11, 17: 20.87, 18: 27.49,
+                                  20: 26.41},
+    (6000, 512, 512, RESIDUAL): {4: 25.95, 11: 33.51, 12: 21.49, 13: 11.26, 14: 15.16, 15: 19.84, 16: 14.39, 17: 10.72,
+                                 18: 10.84, 19: 12.44, 20: 13.37, 22: 17.73, 23: 20.14, 24: 22.78},
+    (8700, 3072, 512, SWIGLU): {4: 34.51, 13: 59.08, 14: 83.27, 16: 54.25, 17: 41.13, 18: 46.77, 19: 43.91, 20: 38.86,
+                                22: 34.86, 23: 38.55, 24: 32.22},
+    (3300, 3840, 640, SWIGLU): {4: 20.87, 13: 36.99, 14: 49.36, 16: 33.13, 17: 28.04, 18: 35.38, 19: 26.73, 20: 22.40,
+                                22: 25.80, 23: 29.73, 24: 20.02},
 }
 
 
