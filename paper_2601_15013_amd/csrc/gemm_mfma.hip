@@ -696,11 +696,8 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
     return c.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
 }
 
-bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
+bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
     if (Nout % sh.bn != 0) return false;
-    // of long rows of A, chosen where they were measured: results added to fp32 rows of any width, others of 2048 columns and more
-    // (measured from 4096 on)
-    if (sh.variant >= 22 && K >= LONG_K && epilogue != EPI_RESIDUAL && Nout < 2048) return false;
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
         return sh.bn % 128 == 0 && sh.variant != 22 && sh.variant != 24;
     if (epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_SPLIT) return sh.bn % 64 == 0;           // gate/up pairs
@@ -711,7 +708,7 @@ bool tile_usable(const TileShape& sh, int Nout, int K, int epilogue) {
 int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double* us) {
     int v = 0;
     for (const TileShape& sh : tile_shapes) {
-        if (!tile_usable(sh, Nout, K, epilogue) || (whole && M % sh.bm != 0)) continue;
+        if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
         const double t = tile_time(sh, cus, M, Nout, K, epilogue);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
     }
@@ -743,7 +740,7 @@ GemmPlan plan_gemm(int cus, int M, int Nout, int K, int epilogue) {
     // rounds costs (300 and 1300 rows of a head of 151936 columns: 542 -> 614 and 570 -> 630 us)
     const bool weights_pass = (long long)Nout * K * 2 > 256LL << 20;
     for (const TileShape& sh : tile_shapes) {
-        if (sh.bm < 128 || !tile_usable(sh, Nout, K, epilogue)) continue;
+        if (sh.bm < 128 || !tile_usable(sh, Nout, epilogue)) continue;
         const long long row_tiles = M / sh.bm, per_row = Nout / sh.bn;
         const long long rounds = row_tiles * per_row / cus;
         if (rounds < 1 || (rounds >= 8 && weights_pass)) continue;
@@ -852,7 +849,7 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
     if (M <= 0 || Nout <= 0 || K <= 0 || epilogue < 0 || m1 <= 0 || m1 > M) return RADIX_ERR_BAD_SIZE;
     double t1 = -1.0, t2 = -1.0;
     for (const TileShape& sh : tile_shapes) {
-        if (!tile_usable(sh, Nout, K, epilogue)) continue;
+        if (!tile_usable(sh, Nout, epilogue)) continue;
         if (sh.variant == v1) t1 = tile_time(sh, device_cus(), m1, Nout, K, epilogue);
         if (m1 < M && sh.variant == v2) t2 = tile_time(sh, device_cus(), M - m1, Nout, K, epilogue);
     }
@@ -876,8 +873,7 @@ extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int
     if (variant != 0) {
         bool known = false;
         for (const TileShape& sh : tile_shapes)
-            known = known || (sh.variant == variant && tile_usable(sh, Nout, LONG_K, epilogue));
-        if (variant >= 22 && variant <= 24) known = Nout % 256 == 0 && (!rope || variant == 23);
+            known = known || (sh.variant == variant && tile_usable(sh, Nout, epilogue));
         if (!known) return RADIX_ERR_UNSUPPORTED;
     }
     const QkvEpilogue qe = {gq, gk, cos_tab, sin_tab, pos, n_q_heads, n_kv_heads, qk_norm, 1e-6f};

@@ -176,3 +176,20 @@ def test_the_last_of_many_rounds_is_counted(plan, product):
 def test_weights_beyond_the_cache_are_not_read_twice(plan):
     for m, k in ((300, 4096), (1300, 1024)):
         assert plan(m, 151936, k, STORE_F32)[1][3] == m
+
+
+# the same for fewer than 2048 columns, all rows in one tile
+NARROW = {
+    (8700, 1024, 1024, SWIGLU): {4: 24.9, 16: 29.8, 17: 27.4, 18: 30.0, 19: 33.5, 20: 29.1, 22: 19.6, 23: 21.3, 24: 23.8},
+    (6000, 1536, 2048, SWIGLU): {4: 46.3, 16: 55.0, 17: 50.2, 18: 53.8, 19: 60.3, 20: 50.8, 22: 35.7, 23: 39.2, 24: 43.1},
+    (8700, 1024, 4096, STORE): {4: 82.5, 16: 105.2, 17: 94.7, 18: 93.0, 19: 107.0, 20: 93.9, 22: 65.9, 23: 71.3, 24: 79.1},
+    (8700, 1024, 2048, QKV_ROPE): {4: 51.3, 17: 53.4, 18: 56.4, 19: 63.4, 20: 70.9, 23: 43.2},
+    (16500, 1280, 4096, QKV_ROPE): {4: 183.5, 17: 215.6, 18: 205.5, 19: 192.8, 20: 194.6, 23: 157.1},
+}
+
+
+@pytest.mark.parametrize("product", sorted(NARROW))
+def test_narrow_products_get_a_tile_near_the_best_measured_one(plan, product):
+    rc, (v1, _, _, m1, _, _, _) = plan(*product)
+    assert rc == 0 and m1 == product[0]
+    assert NARROW[product][v1] <= 1.05 * min(NARROW[product].values())

@@ -192,7 +192,7 @@ def test_a_split_product_reads_its_rows_through_the_map(n_valid):
 @pytest.mark.parametrize("epilogue", EPILOGUES)
 def test_a_split_product_equals_the_unsplit_one(epilogue):
     nout, K = (4096, 1024) if epilogue in ROPE else (1024, 3072)
-    for M in (8240, 8672):
+    for M in (8240, 8672, 16436):
         if split_of(M, nout, K, epilogue) == M:
             continue
         p = Product("f16", M, nout, K, K, epilogue, seed=M)
