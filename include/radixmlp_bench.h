@@ -47,6 +47,8 @@ int radix_timing_collect(float* total_ms_host, int32_t* launches_host);
  * Shapes: 4 is 256x256, 22 to 24 are 160, 192 and 224 rows of 256 columns, 20 is 256x128, 11 to 19 are the smaller ones.
  * radix_debug_gemm_plan_cus: the same for a device (a partition) of `cus` CUs instead of the present one.
  * radix_debug_gemm_plan_us: the time that the cost model behind that choice gives such a split (v2 is not read if m1 == M).
+ * radix_debug_gemm_plan_folded: the tile of a product that consumes a folded norm (epilogue 0, 2 or 3) or prepares one (6): 1 and 4 are
+ * 256x256 with four and eight wavefronts, 2 128x128, 3 128x256.  Or a negative status.
  * radix_debug_index_first_round: 1 if the index builder spreads its first round over the whole chip for B sequences of N
  * tokens together, 0 if one workgroup runs it, or a negative status.
  * radix_debug_index_host_slots: how many of the words of pinned memory through which radix_build_index answers are free (64 when
@@ -57,6 +59,7 @@ int radix_debug_gemm_plan(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, 
 int radix_debug_gemm_plan_cus(int32_t cus, int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t* v1, int32_t* bm1,
                               int32_t* bn1, int32_t* m1, int32_t* v2, int32_t* bm2, int32_t* bn2);
 int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int32_t epilogue, int32_t v1, int32_t m1, int32_t v2, double* us);
+int radix_debug_gemm_plan_folded(int32_t M, int32_t Nout, int32_t K, int32_t epilogue);
 int radix_debug_gemm_tile(int32_t bid, int32_t tiles_m, int32_t tiles_n, int32_t band, int32_t* tm, int32_t* tn);
 int radix_debug_gemm_band(int32_t tile_rows, int32_t K, int32_t tiles_n);
 int radix_debug_index_first_round(int32_t B, int32_t N);

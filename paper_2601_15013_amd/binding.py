@@ -25,7 +25,7 @@ EXPORTS = (
     "radix_lm_head_workspace_bytes", "radix_lm_head",
     "radix_index_select_rows", "radix_device_status", "radix_status_string",
     "radix_timing_enable", "radix_timing_collect", "radix_debug_gemm_tile", "radix_debug_gemm_band", "radix_debug_gemm_plan", "radix_debug_gemm_plan_cus",
-    "radix_debug_gemm_plan_us",
+    "radix_debug_gemm_plan_us", "radix_debug_gemm_plan_folded",
     "radix_debug_index_first_round", "radix_debug_index_host_slots", "radix_debug_gemm_run", "radix_debug_gemm_run_folded",
 )
 

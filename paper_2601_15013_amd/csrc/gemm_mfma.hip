@@ -595,31 +595,6 @@ int device_cus() {
 template <int DT>
 int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int epilogue, void* out, int variant,
               const QkvEpilogue& qe, const ARowMap& amap, const NormFusion& nf, hipStream_t stream) {
-    // Tile choice for launches with a folded norm (the others: plan_gemm): workgroups run one per CU in rounds, a round
-    // costs a fixed part
-    // (launch, first loads, epilogue) plus the k-tiles at the rate measured for that shape (microseconds per
-    // 32-wide k-tile on MI355X, random fp16 operands): a launch that does not fill its last round pays for it
-    // in full, which is what decides between the shapes for small M * Nout.  Consumers run in eight wavefronts (two per SIMD,
-    // 256 registers each).  The epilogue that prepares a norm holds a row block twice and needs a wavefront block 128 columns wide:
-    // four wavefronts of 512 registers, or 128 rows.
-    if (variant == 0) {
-        const int n_cu = device_cus();
-        const bool produces = epilogue == EPI_RESIDUAL_NORM, heads = epilogue == EPI_QKV_ROPE;
-        struct Shape { int variant, bm, bn, wave_cols; bool consumer, producer; double fixed_us, ktile_us; };
-        static const Shape shapes[4] = {{4, 256, 256, 128, true, false, 8.0, 0.832}, {1, 256, 256, 128, false, true, 9.0, 0.83},
-                                        {3, 128, 256, 128, true, true, 6.5, 0.54}, {2, 128, 128, 64, true, false, 5.0, 0.29}};
-        double best = 0.0;
-        for (const Shape& sh : shapes) {
-            if (Nout % sh.bn != 0 || !(produces ? sh.producer : sh.consumer)) continue;
-            if ((heads || produces) && sh.wave_cols != 128) continue;                // need 128-wide wavefront blocks
-            const double tiles = (double)ceil_div(M, sh.bm) * (Nout / sh.bn);
-            double rounds = tiles / n_cu;
-            if (rounds < 8.0) rounds = (double)(long long)(rounds + 0.999999);   // few rounds: the last one counts whole
-            const double t = rounds * (sh.fixed_us + (K / 32) * sh.ktile_us);
-            if (variant == 0 || t < best) { best = t; variant = sh.variant; }
-        }
-        if (variant == 0) return RADIX_ERR_UNSUPPORTED;
-    }
     const bool rope = epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT;
     if (variant == 20) return launch_cfg<DT, 256, 128, 4, 2>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
     if (variant == 22) return launch_cfg<DT, 160, 256, 2, 4>(A, W, M, Nout, K, w_k, epilogue, out, qe, amap, nf, stream);
@@ -676,9 +651,9 @@ const TileShape tile_shapes[] = {
     {23, 192, 256, 1, {2.42,  4.06, 0.731, 0.444, {0.00, 4.57,  9.41,  3.35}}, {1.03, 3.96, 0.589, 0.434, {0.66, 6.46, 11.11, 5.19}}},
     {24, 224, 256, 1, {3.16,  3.86, 0.799, 0.569, {0.24, 0.31, 10.22,  3.90}}, {1.82, 3.89, 0.581, 0.597, {1.13, 0.00, 12.52, 5.64}}},
 };
-double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
-    const TileCost& c = K >= LONG_K ? sh.long_k : sh.short_k;
-    const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 : epilogue == EPI_RESIDUAL ? 2 :
+double tile_time(const TileShape& sh, const TileCost& c, int cus, int M, int Nout, int K, int epilogue) {
+    const double epi = c.epi_us[epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT ? 1 :
+                                epilogue == EPI_RESIDUAL || epilogue == EPI_RESIDUAL_NORM ? 2 :
                                 epilogue == EPI_STORE_F32 ? 3 : 0];
     const long long tiles = (long long)ceil_div(M, sh.bm) * (Nout / sh.bn);
     const double kt = K / 64;
@@ -696,6 +671,10 @@ double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilo
     return c.launch_us + full * round_us(sh.per_cu) + (rest > 0 ? round_us(rest) : 0.0);
 }
 
+double tile_time(const TileShape& sh, int cus, int M, int Nout, int K, int epilogue) {
+    return tile_time(sh, K >= LONG_K ? sh.long_k : sh.short_k, cus, M, Nout, K, epilogue);
+}
+
 bool tile_usable(const TileShape& sh, int Nout, int epilogue) {
     if (Nout % sh.bn != 0) return false;
     if (epilogue == EPI_QKV_ROPE || epilogue == EPI_QKV_ROPE_SPLIT)                               // whole heads
@@ -711,6 +690,29 @@ int best_tile(int cus, int M, int Nout, int K, int epilogue, bool whole, double*
         if (!tile_usable(sh, Nout, epilogue) || (whole && M % sh.bm != 0)) continue;
         const double t = tile_time(sh, cus, M, Nout, K, epilogue);
         if (v == 0 || t < *us) { *us = t; v = sh.variant; }
+    }
+    return v;
+}
+
+// Tiles of a product with a folded norm, in one launch.  Consumers run in eight wavefronts (two per SIMD, 256 registers each); the
+// epilogue that prepares a norm holds a row block twice and needs a wavefront block 128 columns wide: four wavefronts of 512
+// registers, or 128 rows.  Constants as above, K of any length, from 22 products (K 256 .. 12288, both kinds of epilogue) at 17 row
+// counts from 20 to 44000: within 8 % of a launch, and the tile they pick takes 0.1 % longer than the best one (the worst 14 %).
+const TileShape folded_shapes[] = {
+    {4, 256, 256, 1, {1.59,  5.62, 0.974, 0.575, {0.82, 7.95, 0.00, 0.00}}, {}},
+    {3, 128, 256, 1, {1.28,  2.94, 0.534, 0.357, {0.93, 4.31, 9.82, 0.00}}, {}},
+    {2, 128, 128, 1, {1.28,  2.06, 0.309, 0.217, {0.81, 0.00, 0.00, 0.00}}, {}},
+    {1, 256, 256, 1, {0.00, 18.36, 1.235, 0.721, {0.00, 0.00, 8.12, 0.00}}, {}},
+};
+int folded_tile(int cus, int M, int Nout, int K, int epilogue) {
+    const bool prepares = epilogue == EPI_RESIDUAL_NORM, heads = epilogue == EPI_QKV_ROPE;
+    int v = 0;
+    double best = 0.0;
+    for (const TileShape& sh : folded_shapes) {
+        if (Nout % sh.bn != 0 || (prepares ? sh.variant == 4 : sh.variant == 1)) continue;
+        if ((heads || prepares) && sh.bn != 256) continue;                       // wavefront blocks of 128 columns
+        const double t = tile_time(sh, sh.long_k, cus, M, Nout, K, epilogue);
+        if (v == 0 || t < best) { best = t; v = sh.variant; }
     }
     return v;
 }
@@ -790,7 +792,8 @@ int launch_gemm_mfma(const void* A, const void* W, int M, int Nout, int K, int e
         if (op_dtype == RADIX_F16) return launch_dt<RADIX_F16>(a, W, m, Nout, K, w_k, epilogue, o, v, qe, amap, nf, stream);
         return RADIX_ERR_UNSUPPORTED;
     };
-    if (variant != 0 || folded) return launch(variant, A, M, out);
+    if (folded && variant == 0) variant = folded_tile(device_cus(), M, Nout, K, epilogue);
+    if (folded || variant != 0) return launch(variant, A, M, out);
     if (K % GEMM_BK != 0) return RADIX_ERR_UNSUPPORTED;
     const GemmPlan plan = plan_gemm(device_cus(), M, Nout, K, epilogue);
     if (plan.v1 == 0) return RADIX_ERR_UNSUPPORTED;
@@ -856,6 +859,12 @@ extern "C" int radix_debug_gemm_plan_us(int32_t M, int32_t Nout, int32_t K, int3
     if (t1 < 0.0 || (m1 < M && t2 < 0.0)) return RADIX_ERR_UNSUPPORTED;
     *us = m1 < M ? t1 + t2 : t1;
     return RADIX_OK;
+}
+extern "C" int radix_debug_gemm_plan_folded(int32_t M, int32_t Nout, int32_t K, int32_t epilogue) {
+    if (M <= 0 || Nout <= 0 || K <= 0) return RADIX_ERR_BAD_SIZE;
+    if (epilogue != EPI_STORE && epilogue != EPI_SWIGLU && epilogue != EPI_QKV_ROPE && epilogue != EPI_RESIDUAL_NORM) return RADIX_ERR_UNSUPPORTED;
+    const int v = folded_tile(device_cus(), M, Nout, K, epilogue);
+    return v ? v : RADIX_ERR_UNSUPPORTED;
 }
 // One product on the device with the tile named (0: what the plan picks), for tests that compare the tiles.
 extern "C" int radix_debug_gemm_run(const void* A, const void* W, int32_t M, int32_t Nout, int32_t K, int32_t w_k, int32_t epilogue,

@@ -7,7 +7,7 @@ import pytest
 
 from paper_2601_15013_amd import binding
 
-STORE, RESIDUAL, SWIGLU, QKV_ROPE, STORE_F32, SWIGLU_SPLIT, QKV_ROPE_SPLIT = 0, 1, 2, 3, 4, 5, 7
+STORE, RESIDUAL, SWIGLU, QKV_ROPE, STORE_F32, SWIGLU_SPLIT, RESIDUAL_NORM, QKV_ROPE_SPLIT = range(8)
 
 
 @pytest.fixture(scope="module")
@@ -193,3 +193,30 @@ def test_narrow_products_get_a_tile_near_the_best_measured_one(plan, product):
     rc, (v1, _, _, m1, _, _, _) = plan(*product)
     assert rc == 0 and m1 == product[0]
     assert NARROW[product][v1] <= 1.05 * min(NARROW[product].values())
+
+
+# the same for products that consume or prepare a folded norm
+FOLDED = {
+    (3000, 4096, 12288, RESIDUAL_NORM): {1: 365.5, 3: 317.0},
+    (4400, 4096, 4096, RESIDUAL_NORM): {1: 267.2, 3: 185.2},
+    (9000, 1024, 3072, RESIDUAL_NORM): {1: 107.1, 3: 95.5},
+    (1000, 2560, 9728, RESIDUAL_NORM): {1: 270.0, 3: 110.2},
+    (16500, 2560, 9728, RESIDUAL_NORM): {1: 881.9, 3: 822.6},
+    (9000, 1024, 256, QKV_ROPE): {3: 19.2, 4: 22.0},
+    (2200, 24576, 4096, SWIGLU): {2: 544.5, 3: 437.6, 4: 424.3},
+    (9000, 6144, 1024, SWIGLU): {2: 155.1, 3: 126.4, 4: 121.1},
+    (9000, 4096, 1024, QKV_ROPE): {3: 106.2, 4: 112.5},
+}
+
+
+@pytest.mark.parametrize("product", sorted(FOLDED))
+def test_folded_norms_get_a_tile_near_the_best_measured_one(plan, product):
+    v = binding.load_library().radix_debug_gemm_plan_folded(*product)
+    assert FOLDED[product][v] <= 1.05 * min(FOLDED[product].values())
+
+
+def test_folded_plan_rejects_what_no_tile_runs(plan):
+    lib = binding.load_library()
+    assert lib.radix_debug_gemm_plan_folded(0, 256, 64, STORE) == -2
+    for nout, epilogue in ((128, QKV_ROPE), (384, RESIDUAL_NORM), (64, STORE), (256, RESIDUAL), (256, STORE_F32)):
+        assert lib.radix_debug_gemm_plan_folded(8, nout, 64, epilogue) == -3, (nout, epilogue)
