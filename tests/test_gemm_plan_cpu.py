@@ -202,7 +202,7 @@ FOLDED = {
     (9000, 1024, 3072, RESIDUAL_NORM): {1: 107.1, 3: 95.5},
     (1000, 2560, 9728, RESIDUAL_NORM): {1: 270.0, 3: 110.2},
     (16500, 2560, 9728, RESIDUAL_NORM): {1: 881.9, 3: 822.6},
-    (9000, 1024, 256, QKV_ROPE): {3: 19.2, 4: 22.0},
+    (24000, 1024, 256, QKV_ROPE): {3: 33.1, 4: 40.0},
     (2200, 24576, 4096, SWIGLU): {2: 544.5, 3: 437.6, 4: 424.3},
     (9000, 6144, 1024, SWIGLU): {2: 155.1, 3: 126.4, 4: 121.1},
     (9000, 4096, 1024, QKV_ROPE): {3: 106.2, 4: 112.5},
