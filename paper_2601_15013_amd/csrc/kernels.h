@@ -136,8 +136,8 @@ __host__ __device__ inline GemmTile gemm_tile_of(int bid, int tiles_m, int tiles
 // of a band are read again for every group of column tiles, and what serves those re-reads is the 256 MB
 // memory-side cache shared by all XCDs: the eight bands in flight must leave room in it for the weights, so long
 // rows (large K) take a narrower band.  Measured on MI355X, us per launch with bands of 8 / 4 / 2 / 1:
-// M 45120, N 4096, K 12288: 4210 / 4168 / 4134 / 4109; N 24576, K 4096: 7109 / 7025 / 7105 / 7821;
-// N 6144, K 4096: 1827 / 1841 / 1840 / 1929.
+// M 45120, N 4096, K 12288: 3543 / 3439 / 3444 / 3443; N 24576, K 4096: 6731 / 6689 / 6794 / 6998;
+// N 6144, K 4096: 1774 / 1764 / 1780 / 1839; M 16436, N 2560, K 9728: 705 / 693 / 685 / 683; M 50432, N 6144, K 1024: 531 / 533 / 538 / 549.
 inline int gemm_band_rows(int bm, int K, int elem_bytes, int tiles_n) {
     int band = 8;
     while (band > 1 && 8.0 * band * bm * (double)K * elem_bytes > 64.0 * 1024 * 1024) band /= 2;
