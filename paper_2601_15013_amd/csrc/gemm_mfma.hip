@@ -611,8 +611,9 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 // ---- tile choice.  Time of a launch with tile shape s, in microseconds: workgroups run `per_cu` at a time on each CU
 // in rounds.  Where that is one, a round costs fixed_us + epi_us (first loads, epilogue, by what it writes: 16-bit rows, q|k|v
 // heads, fp32 rows added to, fp32 rows written) and, per 64 columns of K, step_us + share_us times the share of the CUs that it
-// occupies (the clock and the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us, n epi_us and, per
-// 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us if that is more.
+// occupies (the clock and the memory-side cache are shared by all).  Where several run on a CU, a round of n per CU costs fixed_us,
+// n epi_us and, per 64 columns, step_us (what a k-tile takes when nothing else runs on the CU: a chain of latencies) or n share_us
+// if that is more.
 // A launch that does not fill its last round pays for it in full; where several workgroups run on a CU, only up to eight rounds.
 // (One per CU: 12 products of the 0.6B, 4B and 8B shapes at 22 row counts, 5 to 22 rounds.  Counted like this, launches of 8 to 22
 // rounds take 0.98 to 1.03 of the model's time on average, at every fill of the last round; with the rounds beyond eight counted
@@ -630,8 +631,8 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 //     over the plans before as fp16 ones (3.6 % over 562 launches).
 // The 256x256 tile wins where it fills the chip; the tiles of 160, 192 and 224 rows where that leaves less of the last round
 // empty: M 8300, N 1024: K 3072 70.1 / 57.3 us (256 / 160 rows), K 2048 54.4 / 43.0; M 5000, N 7168, K 5120: 338 / 294 (192 rows);
-// 129 of the 336 pairs have one of the three as their best; short rows: M 16500, N 4096, K 768 (gate/up)
-// 114.6 / 105.7 (224 rows).  Their constants of long_k are 2 % above the fit: among many estimates one that is low by chance would win, and the older tiles are the safer choice.
+// M 16500, N 4096, K 768 114.6 / 105.7 (224 rows); 129 of the 336 pairs have one of the three as their best.  Their constants of long_k
+// are 2 % above the fit: among many estimates one that is low by chance would win, and the older tiles are the safer choice.
 struct TileCost { double launch_us, fixed_us, step_us, share_us, epi_us[4]; };
 struct TileShape { int variant, bm, bn, per_cu; TileCost long_k, short_k; };
 constexpr int LONG_K = 1024;
