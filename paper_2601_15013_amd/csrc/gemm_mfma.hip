@@ -627,8 +627,8 @@ int launch_dt(const void* A, const void* W, int M, int Nout, int K, int w_k, int
 //     through LDS (gemm_small.hip): 151936 columns, K 1024, M 1000: 421 us, straight from the accumulators 592.
 //   short_k: 53 products of K 64 .. 768 at 23 and 25 row counts from 1 to 130000; not least squares alone, but the time lost by what
 //     is picked and, less, the model's error for tiles within 1.4 of the best, which is 6 to 13 %.  The picked tile takes 0.5 %
-//     longer than the best (a tenth of them more than 1.5 %, the worst 21 %).  bf16 operands, which were not in the fit, gain as much
-//     over the plans before as fp16 ones (3.6 % over 562 launches).
+//     longer than the best (a tenth of them more than 1.5 %, the worst 21 %), and on 732 pairs outside the fit 0.5 % (2.5 %, 12 %).  bf16
+//     operands, which were not in the fit, gain as much over the plans before as fp16 ones (3.6 % over 562 launches).
 // The 256x256 tile wins where it fills the chip; the tiles of 160, 192 and 224 rows where that leaves less of the last round
 // empty: M 8300, N 1024: K 3072 70.1 / 57.3 us (256 / 160 rows), K 2048 54.4 / 43.0; M 5000, N 7168, K 5120: 338 / 294 (192 rows);
 // M 16500, N 4096, K 768 114.6 / 105.7 (224 rows); 129 of the 336 pairs have one of the three as their best.  Their constants of long_k
